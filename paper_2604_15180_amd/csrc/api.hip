@@ -88,7 +88,7 @@ Layout bwd_layout(int B, int H, int N, int d, int t) {
     L.scnt = off; off += align256(BH * N * 2 * 4);
     L.gflag = off; off += align256(BH * ((size_t)N / 128 + 1) * 4);
     L.kcnt = off; off += align256(BH * N * 4 + 8);               // and two counters: row groups on the matrix path, set mask bits
-    L.klist = off; off += align256(BH * N * (size_t)(KEY_LIST_CAP * 16));
+    L.klist = off; off += align256(BH * N * (size_t)KEY_LIST_CAP * sizeof(KeyEntry));
     L.defer = off; off += align256(BH * N * 4);
     L.colcnt = off; off += align256(BH * T * 4);                 // query tiles per key tile's mask column (dkdv_kernel's parts)
     L.total = off;

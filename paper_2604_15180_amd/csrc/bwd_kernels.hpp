@@ -7,6 +7,7 @@
 // With y = (alpha-1) s - tau on the support:  P = y^r,  U = y^(r-1),  r = 1/(alpha-1).
 #pragma once
 #include "common.hpp"
+#include "gather.hpp"
 
 namespace ea {
 
@@ -699,8 +700,8 @@ __global__ __launch_bounds__(NW * 64) void dkdv_kernel(Params p) {
 //                     lists stay short is flagged; dq_kernel and dkdv_kernel skip flagged groups.
 //   bwd_rows_kernel : per row, over its listed support: dP_j = <dO_r, V_j>, delta, and
 //                     dQ_r = sum_j dS_j K_j / sqrt(d) (Alg. 3, row by row); every entry is also
-//                     filed under its key: (row, u dP, u, P).
-//   bwd_cols_kernel : per key, over the entries filed under it, with dS = u dP - u delta_row:
+//                     filed under its key: (row, dS, P).
+//   bwd_cols_kernel : per key, over the entries filed under it:
 //                     dK_j += sum dS Q_r / sqrt(d), dV_j += sum P dO_r (Alg. 2, column by
 //                     column), added to what dkdv_kernel
 //                     stored for the other row groups (or, when none was left to it, written as
@@ -709,7 +710,7 @@ __global__ __launch_bounds__(NW * 64) void dkdv_kernel(Params p) {
 //                     dK, dV with atomics after bwd_cols_kernel.
 // All three read the caller's Q, K, V, dO (not the 16-bit copies) and work in fp32.
 // The gather path pays while a marked 64 x 64 tile holds only a few non-zeros: the group is flagged
-// when its lists hold at most BWD_ENTRIES_PER_TILE entries per marked tile (and no list is full);
+// when its lists hold at most bwd_entries_per_tile entries per marked tile (and no list is full);
 // or BWD_ENTRIES_PER_ROW per row (and no list is full); the sweep is left early once the entries
 // so far run a quarter above that rate.
 template <class E, int D, int QB, int AM, int NW>
@@ -762,12 +763,8 @@ __global__ __launch_bounds__(NW * 64) void bwd_list_kernel(Params p) {
     // entries the whole group may list (a group with few marked tiles - the first rows of a causal
     // head - still has one entry or more per row, and is cheap either way: it goes with the rest,
     // so that the matrix kernels' input copies are not made for its sake alone)
-    // (the matrix kernels' time per tile goes with D, the gather's time per entry hardly does -
-    // measured break-even: about 32 entries per tile at D = 128, 8 at D = 64; the power functions
-    // of general alpha weigh on every entry)
-    constexpr int PER_TILE_X128 = BWD_ENTRIES_PER_TILE * D * D / 128 / (AM == ALPHA_GEN ? 2 : 1);
     constexpr int PER_ROW_X128 = BWD_ENTRIES_PER_ROW * D * D / 128 / (AM == ALPHA_GEN ? 2 : 1);
-    const int budget = max(PER_TILE_X128 * gsum[1] / 128,
+    const int budget = max(bwd_entries_per_tile(D, sizeof(elem)) / (AM == ALPHA_GEN ? 2 : 1) * gsum[1],
                            gsum[1] <= BWD_FEW_TILES ? PER_ROW_X128 * min(BR, N - (int)((long)I * BR)) / 128 : 0);
 
     Owned<E, D, QB> qf;
@@ -876,7 +873,7 @@ __global__ __launch_bounds__(NW * 64) void bwd_list_kernel(Params p) {
 // the support (raw score, key index), with the counts beside it.  This kernel takes the place of
 // bwd_list_kernel's sweep: per row group of the backward it applies the same rule - at most so many
 // support entries per marked tile, or per row where few tiles are marked - to the forward's counts.
-template <int D, int AM>
+template <class E, int D, int AM>
 __global__ __launch_bounds__(128) void bwd_decide_kernel(Params p) {
     __shared__ int gsum[2];
     const int tid = threadIdx.x;
@@ -901,9 +898,8 @@ __global__ __launch_bounds__(128) void bwd_decide_kernel(Params p) {
     }
     __syncthreads();
     if (tid == 0) {
-        constexpr int PER_TILE_X128 = BWD_ENTRIES_PER_TILE * D * D / 128 / (AM == ALPHA_GEN ? 2 : 1);
-        constexpr int PER_ROW_X128 = BWD_ENTRIES_PER_ROW * D * D / 128 / (AM == ALPHA_GEN ? 2 : 1);
-        const int budget = max(PER_TILE_X128 * gsum[1] / 128,
+            constexpr int PER_ROW_X128 = BWD_ENTRIES_PER_ROW * D * D / 128 / (AM == ALPHA_GEN ? 2 : 1);
+        const int budget = max(bwd_entries_per_tile(D, sizeof(typename E::elem)) / (AM == ALPHA_GEN ? 2 : 1) * gsum[1],
                                gsum[1] <= BWD_FEW_TILES ? PER_ROW_X128 * min(BR, N - I * BR) / 128 : 0);
         gather = gather && gsum[0] <= budget;
         p.gflag[(long)bh * G + I] = gather;
@@ -912,23 +908,31 @@ __global__ __launch_bounds__(128) void bwd_decide_kernel(Params p) {
     }
 }
 
-// Sixteen lanes per row; lane `sub` holds elements [sub * D/16, (sub + 1) * D/16) of the row's
-// vectors.  SCALED: dkdv_kernel works on dO / max|dO|, so the delta handed to it is in those units.
+// Sixteen lanes per row (GatherLanes).  Per row, over its entries: dP_j = <dO_r, V_j>, delta = sum u dP / sum u,
+// dQ_r = sum_j dS_j K_j / sqrt(d) with dS = u (dP - delta); every entry is filed under its key as
+// (row, dS, P).  dP of the first KEEP entries stays in registers between the two passes; a longer
+// row computes it a second time.  An entry whose key's list is full is marked (top bit of its key
+// index) and left to bwd_hot_kernel, which adds it to dK, dV atomically once bwd_cols_kernel has
+// stored them.  SCALED: dkdv_kernel works on dO / max|dO|, so the delta handed to it is in those units.
 template <class E, int D, int AM, bool SCALED>
 __global__ __launch_bounds__(256) void bwd_rows_kernel(Params p) {
     using elem = typename E::elem;
-    constexpr int EPT = D / 16, CH = 2;      // entries in flight per lane group
-    typedef elem vvec __attribute__((ext_vector_type(EPT)));
-    typedef float ovec __attribute__((ext_vector_type(4)));
-    const int tid = threadIdx.x, sub = tid & 15, rsel = tid >> 4;
-    // a work-group takes GATHER_ROWS rows of a row group (one or a few per 16 lanes): the rows are
+    using L = GatherLanes<E, D>;
+    using vec = typename L::vec;
+    constexpr int EPT = L::EPT, KEEPC = 3, BT = 4;     // chunks kept in registers; rows of V or K in flight per lane
+    static_assert(L::STEPS % BT == 0, "a chunk is a whole number of batches");
+    const int tid = threadIdx.x, sub = tid & 15, rsel = tid >> 4, lane = tid & 63;
+    // a work-group takes GATHER_ROWS rows of a row group (one per 16 lanes): the rows are
     // chains of dependent loads, so many short work-groups hide their latency better than few long ones
+    static_assert(GATHER_ROWS == 16, "one row per sixteen lanes");
     const int N = p.N, G = (N + p.grows - 1) / p.grows, parts = p.grows / GATHER_ROWS;
     int bh, I;
     map_block(blockIdx.x, p.BH, G * parts, bh, I);
     const int part = I % parts;
     I /= parts;
     if (!p.gflag[(long)bh * G + I]) return;
+    const int row = I * p.grows + part * GATHER_ROWS + rsel;
+    if (row >= N) return;                              // (N is a multiple of 64: whole work-groups)
     const HeadConsts hc = head_consts(p, bh);
     const float c = hc.c, r = hc.r;
     float amax = 1.f;
@@ -936,116 +940,136 @@ __global__ __launch_bounds__(256) void bwd_rows_kernel(Params p) {
         amax = __uint_as_float(p.scal[0]);
         if (!(amax > 0.f)) amax = 1.f;
     }
-    const long hoff = (long)bh * N * D;
-    const elem* Qh = (const elem*)p.Q + hoff;
-    const elem* Kh = (const elem*)p.K + hoff + sub * EPT;
-    const elem* Vh = (const elem*)p.V + hoff + sub * EPT;
-    const elem* Gh = (const elem*)p.dO + hoff;
-    const int cap8 = p.list_cap * 8;         // bytes of one lane list
-    const char* lists_h = (const char*)p.lists + (size_t)bh * N * (size_t)(2 * cap8);
-    const int row_end = min(N, I * p.grows + (part + 1) * GATHER_ROWS);
-    for (int row = I * p.grows + part * GATHER_ROWS + rsel; row < row_end; row += 16) {
-        const long gi = (long)bh * N + row;
-        const float tau = p.tau[gi];
-        const int s0 = p.scnt[gi * 2], tot = s0 + p.scnt[gi * 2 + 1];
-        const char* l0 = lists_h + (size_t)row * (size_t)(2 * cap8);     // the second list follows the first
-        auto entry = [&](int i) { return *(const uint2*)(l0 + (i < s0 ? i * 8 : cap8 + (i - s0) * 8)); };
-        const vvec gv = *(const vvec*)(Gh + (long)row * D + sub * EPT);
-        float g[EPT];
+    const long hoff = (long)bh * N * D, gi = (long)bh * N + row;
+    const elem* Kh = (const elem*)p.K + hoff + L::column(sub);
+    const elem* Vh = (const elem*)p.V + hoff + L::column(sub);
+    const int cap8 = p.list_cap * 8;                   // bytes of one lane list
+    char* l0 = (char*)p.lists + (size_t)gi * (size_t)(2 * cap8);        // the second list follows the first
+    const float tau = p.tau[gi];
+    const int s0 = p.scnt[gi * 2], tot = s0 + p.scnt[gi * 2 + 1];
+    const vec gv = *(const vec*)((const elem*)p.dO + hoff + (long)row * D + L::column(sub));
+    int nmax = tot;                                    // the longest of the wave's four rows
+    nmax = max(nmax, __shfl_xor(nmax, 16));
+    nmax = max(nmax, __shfl_xor(nmax, 32));
+    nmax = __builtin_amdgcn_readfirstlane(nmax);
+
+    auto entry_ptr = [&](int i) { return l0 + (i < s0 ? i * 8 : cap8 + (i - s0) * 8); };
+    struct Entry { uint32_t key; float u, pr; };
+    auto load_entry = [&](int i) {
+        uint2 e = make_uint2(0u, 0u);
+        if (i < tot) e = *(const uint2*)entry_ptr(i);
+        const float y = fmaf(c, __uint_as_float(e.x), -tau);
+        const bool in = i < tot && y > 0.f;
+        Entry x;
+        x.key = e.y;
+        x.u = in ? pow_r1<AM>(y, r) : 0.f;
+        x.pr = in ? pow_r<AM>(y, r) : 0.f;
+        return x;
+    };
+    // dP of a chunk's entries, each left in the lane that holds the entry
+    auto chunk_dP = [&](uint32_t key, int left) {
+        float dP = 0.f;
+        unroll_steps<L::STEPS / BT>([&](auto b) {
+            constexpr int S0 = decltype(b)::value * BT;
+            if (S0 * L::PAR >= left) return;
+            vec v[BT];
+            unroll_steps<BT>([&](auto u) { v[decltype(u)::value] = *(const vec*)(Vh + (size_t)(L::template of_step<S0 + decltype(u)::value>(key) * (uint32_t)D)); });
+            unroll_steps<BT>([&](auto u) {
+                constexpr int S = S0 + decltype(u)::value;
+                const float t = L::entry_sum(dot_share<E, EPT>(gv, v[decltype(u)::value], 0.f));
+                if (L::template holds<S>(sub)) dP = t;
+            });
+        });
+        return dP;
+    };
+    Entry ent[KEEPC];
+    float dP[KEEPC];
+    int slot[KEEPC];
+    float num = 0.f, den = 0.f;
+    unroll_steps<KEEPC>([&](auto cc) {
+        constexpr int C = decltype(cc)::value;
+        if (16 * C >= nmax) return;
+        const int i = 16 * C + L::entry_of(sub);
+        ent[C] = load_entry(i);
+        slot[C] = 0;
+        if (i < tot) slot[C] = atomicAdd(&p.kcnt[(long)bh * N + ent[C].key], 1);
+        dP[C] = chunk_dP(ent[C].key, nmax - 16 * C);
+        num = fmaf(ent[C].u, dP[C], num);
+        den += ent[C].u;
+    });
+    for (int i0 = 16 * KEEPC; i0 < nmax; i0 += 16) {
+        const Entry e = load_entry(i0 + L::entry_of(sub));
+        num = fmaf(e.u, chunk_dP(e.key, nmax - i0), num);
+        den += e.u;
+    }
+    num = group_sum<16>(num);
+    den = group_sum<16>(den);
+    const float delta = den > 0.f ? num / den : 0.f;
+
+    float x[EPT];
+    int ndefer = 0;
 #pragma unroll
-        for (int k = 0; k < EPT; ++k) g[k] = (float)gv[k];
-        // One pass over the entries, CH at a time so that their chains of dependent memory
-        // operations (entry, rows of V and K, slot in the key's list) overlap:
-        //   delta = sum u dP / sum u, and the two sums dQ is made of:
-        //   dQ sqrt(d) = sum_j u_j (dP_j - delta) K_j = XA - delta XB;
-        // every entry is filed under its key as (row, u dP, u, P): dS = u dP - u delta is formed
-        // by bwd_cols_kernel, which reads the row's delta once this kernel has stored it.  An
-        // entry whose key's list is full is marked (top bit of its key index) and left to
-        // bwd_hot_kernel, which adds it to dK, dV atomically once bwd_cols_kernel has stored them.
-        float xa[EPT], xb[EPT], num = 0.f, den = 0.f;
-        int ndefer = 0;
-#pragma unroll
-        for (int k = 0; k < EPT; ++k) { xa[k] = 0.f; xb[k] = 0.f; }
-        for (int i0 = 0; i0 < tot; i0 += CH) {
-            uint2 e[CH];
-            vvec vv[CH], kv[CH];
-            int slot[CH];
-#pragma unroll
-            for (int u = 0; u < CH; ++u) e[u] = i0 + u < tot ? entry(i0 + u) : make_uint2(0u, 0u);
-#pragma unroll
-            for (int u = 0; u < CH; ++u) {
-#pragma unroll
-                for (int k = 0; k < EPT; ++k) { vv[u][k] = (elem)0.f; kv[u][k] = (elem)0.f; }
-                slot[u] = 0;
-                if (i0 + u < tot) {
-                    vv[u] = *(const vvec*)(Vh + (long)e[u].y * D);
-                    kv[u] = *(const vvec*)(Kh + (long)e[u].y * D);
-                    if (sub == 0) slot[u] = atomicAdd(&p.kcnt[(long)bh * N + e[u].y], 1);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < CH; ++u) {
-                float dot = 0.f;
-#pragma unroll
-                for (int k = 0; k < EPT; ++k) dot = fmaf(g[k], (float)vv[u][k], dot);
-                const float dP = group_sum<16>(dot);
-                const float y = fmaf(c, __uint_as_float(e[u].x), -tau);
-                const bool in = i0 + u < tot && y > 0.f;
-                const float uu = in ? pow_r1<AM>(y, r) : 0.f;
-                const float pr = in ? pow_r<AM>(y, r) : 0.f;
-                const float t = uu * dP;
-                num += t; den += uu;
-#pragma unroll
-                for (int k = 0; k < EPT; ++k) { xa[k] = fmaf(t, (float)kv[u][k], xa[k]); xb[k] = fmaf(uu, (float)kv[u][k], xb[k]); }
-                const int sl = __shfl(slot[u], (tid & 63) & ~15);
-                if (i0 + u < tot) {
-                    if (sl < KEY_LIST_CAP) {
-                        if (sub == 0)
-                            ((uint4*)p.klist)[((long)bh * N + e[u].y) * KEY_LIST_CAP + sl] =
-                                make_uint4((uint32_t)row, __float_as_uint(t), __float_as_uint(uu), __float_as_uint(pr));
-                    } else {
-                        const int i = i0 + u;
-                        if (sub == 0)
-                            *(uint32_t*)(const_cast<char*>(l0) + (i < s0 ? i * 8 : cap8 + (i - s0) * 8) + 4) = e[u].y | 0x80000000u;
-                        ++ndefer;
-                    }
-                }
-            }
+    for (int k = 0; k < EPT; ++k) x[k] = 0.f;
+    // file a chunk's entries under their keys and add their share of dQ
+    auto finish_chunk = [&](const Entry& e, float dPe, int sl, int i0) {
+        const float dS = e.u * (dPe - delta);
+        const int i = i0 + L::entry_of(sub);
+        if (i < tot) {
+            if (sl < KEY_LIST_CAP) ((KeyEntry*)p.klist)[((long)bh * N + e.key) * KEY_LIST_CAP + sl] = KeyEntry{(uint32_t)row, dS, e.pr};
+            else { *(uint32_t*)(entry_ptr(i) + 4) = e.key | 0x80000000u; ndefer = 1; }
         }
-        const float delta = den > 0.f ? num / den : 0.f;
-        {
-            float* out = p.dQ + gi * D + sub * EPT;
+        unroll_steps<L::STEPS / BT>([&](auto b) {
+            constexpr int S0 = decltype(b)::value * BT;
+            if (S0 * L::PAR >= nmax - i0) return;
+            vec v[BT];
+            unroll_steps<BT>([&](auto u) { v[decltype(u)::value] = *(const vec*)(Kh + (size_t)(L::template of_step<S0 + decltype(u)::value>(e.key) * (uint32_t)D)); });
+            unroll_steps<BT>([&](auto u) { add_scaled<EPT>(x, L::template of_step<S0 + decltype(u)::value>(dS), v[decltype(u)::value]); });
+        });
+    };
+    unroll_steps<KEEPC>([&](auto cc) {
+        constexpr int C = decltype(cc)::value;
+        if (16 * C < nmax) finish_chunk(ent[C], dP[C], slot[C], 16 * C);
+    });
+    for (int i0 = 16 * KEEPC; i0 < nmax; i0 += 16) {
+        const Entry e = load_entry(i0 + L::entry_of(sub));
+        int sl = 0;
+        if (i0 + L::entry_of(sub) < tot) sl = atomicAdd(&p.kcnt[(long)bh * N + e.key], 1);
+        finish_chunk(e, chunk_dP(e.key, nmax - i0), sl, i0);
+    }
 #pragma unroll
-            for (int k = 0; k < EPT; k += 4)
-                *(ovec*)(out + k) = ovec{(xa[k] - delta * xb[k]) * p.inv_sqrt_d, (xa[k + 1] - delta * xb[k + 1]) * p.inv_sqrt_d,
-                                         (xa[k + 2] - delta * xb[k + 2]) * p.inv_sqrt_d, (xa[k + 3] - delta * xb[k + 3]) * p.inv_sqrt_d};
-        }
-        if (sub == 0) {
-            p.delta[gi] = -delta / amax;
-            p.ntau[gi] = -tau / hc.rho;
-        }
-        if (sub == 0) p.defer[gi] = ndefer;
+    for (int k = 0; k < EPT; ++k) x[k] = L::halves_sum(x[k]) * p.inv_sqrt_d;
+    L::store(p.dQ + gi * D, x, sub);
+    const unsigned long long deferred = __ballot(ndefer != 0);
+    if (sub == 0) {
+        p.delta[gi] = -delta / amax;
+        p.ntau[gi] = -tau / hc.rho;
+        p.defer[gi] = __popcll((deferred >> (lane & 48)) & 0xffffull);
     }
 }
 
 // The entries bwd_rows_kernel marked: keys that more rows attend to than a key's list holds.  Run
-// after bwd_cols_kernel; sixteen lanes per row recompute the entry's dS and P (delta is the row's
-// stored one) and add its share to the key's rows of dK, dV with fp32 atomics, lane-interleaved
+// after bwd_cols_kernel; a work-group looks through the rows of one row group for deferred entries (most
+// groups hold none and leave after one load per row); sixteen lanes then take a row at a time,
+// recompute the entry's dS and P (delta is the row's stored one) and add its share to the key's
+// rows of dK, dV with fp32 atomics, lane-interleaved
 // (lane `sub` takes elements sub, sub + 16, ...: an instruction then covers whole 64-byte pieces).
 template <class E, int D, int AM, bool SCALED>
 __global__ __launch_bounds__(256) void bwd_hot_kernel(Params p) {
     using elem = typename E::elem;
-    constexpr int EPT = D / 16;
+    constexpr int EPT = D / 16, MAX_GROWS = 128;
     typedef elem vvec __attribute__((ext_vector_type(EPT)));
+    __shared__ int rows_s[MAX_GROWS];
+    __shared__ int nrows;
     const int tid = threadIdx.x, sub = tid & 15, rsel = tid >> 4;
-    // a work-group takes GATHER_ROWS rows of a row group (one or a few per 16 lanes): the rows are
-    // chains of dependent loads, so many short work-groups hide their latency better than few long ones
-    const int N = p.N, G = (N + p.grows - 1) / p.grows, parts = p.grows / GATHER_ROWS;
+    const int N = p.N, G = (N + p.grows - 1) / p.grows;
     int bh, I;
-    map_block(blockIdx.x, p.BH, G * parts, bh, I);
-    const int part = I % parts;
-    I /= parts;
+    map_block(blockIdx.x, p.BH, G, bh, I);
     if (!p.gflag[(long)bh * G + I]) return;
+    if (tid == 0) nrows = 0;
+    __syncthreads();
+    if (tid < p.grows && I * p.grows + tid < N && p.defer[(long)bh * N + I * p.grows + tid] != 0) rows_s[atomicAdd(&nrows, 1)] = I * p.grows + tid;
+    __syncthreads();
+    if (nrows == 0) return;
     const HeadConsts hc = head_consts(p, bh);
     const float c = hc.c, r = hc.r;
     float amax = 1.f;
@@ -1059,10 +1083,9 @@ __global__ __launch_bounds__(256) void bwd_hot_kernel(Params p) {
     const elem* Gh = (const elem*)p.dO + hoff;
     const int cap8 = p.list_cap * 8;
     const char* lists_h = (const char*)p.lists + (size_t)bh * N * (size_t)(2 * cap8);
-    const int row_end = min(N, I * p.grows + (part + 1) * GATHER_ROWS);
-    for (int row = I * p.grows + part * GATHER_ROWS + rsel; row < row_end; row += 16) {
+    for (int q = rsel; q < nrows; q += 16) {
+        const int row = rows_s[q];
         const long gi = (long)bh * N + row;
-        if (p.defer[gi] == 0) continue;
         const float tau = p.tau[gi], delta = -p.delta[gi] * amax;
         const int s0 = p.scnt[gi * 2], tot = s0 + p.scnt[gi * 2 + 1];
         char* l0 = const_cast<char*>(lists_h) + (size_t)row * (size_t)(2 * cap8);
@@ -1094,124 +1117,122 @@ __global__ __launch_bounds__(256) void bwd_hot_kernel(Params p) {
     }
 }
 
-// Sixteen lanes per key.  Where dkdv_kernel has stored dK, dV for the other row groups, the key's
+// Sixteen lanes per key (GatherLanes).  Where dkdv_kernel has stored dK, dV for the other row groups, the key's
 // rows are read, added to, and written back; when no row group was left to dkdv_kernel (it then
 // stores nothing) the sums are the rows, and keys without entries get zeros.
-template <class E, int D, bool SCALED>
+// The entries of a key were filed in the order an integer atomic handed out their slots, which
+// changes from run to run.  They are summed in the order of their query rows instead (a row files
+// at most one entry per key, so the rows are distinct): every lane holds one entry in sixteen, finds
+// its rank among the key's rows through LDS and leaves it there in its place, and dK, dV of a key come
+// out bit-identical in every run (keys with more entries than a list holds get the rest from
+// bwd_hot_kernel's atomic additions and do not).
+template <class E, int D>
 __global__ __launch_bounds__(256) void bwd_cols_kernel(Params p) {
     using elem = typename E::elem;
-    constexpr int EPT = D / 16, CH = 4;      // entries in flight per lane group
-    typedef elem vvec __attribute__((ext_vector_type(EPT)));
-    typedef float ovec __attribute__((ext_vector_type(4)));
+    using L = GatherLanes<E, D>;
+    using vec = typename L::vec;
+    constexpr int EPT = L::EPT, BT = 4;                // rows of Q and of dO in flight per lane
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    static_assert(BWD_COLS_KEYS == 16, "one key per sixteen lanes");
+    constexpr int PER_LANE = KEY_LIST_CAP / 16;        // entries of a key's list per lane of its 16
+    __shared__ uint32_t row_s[16][KEY_LIST_CAP];
+    __shared__ float2 val_s[16][KEY_LIST_CAP];
     const int tid = threadIdx.x, sub = tid & 15, rsel = tid >> 4;
     const int N = p.N, G = (N + BWD_COLS_KEYS - 1) / BWD_COLS_KEYS;
     int bh, I;
     map_block(blockIdx.x, p.BH, G, bh, I);
-    const long hoff = (long)bh * N * D;
-    const elem* Qh = (const elem*)p.Q + hoff + sub * EPT;
-    const elem* Gh = (const elem*)p.dO + hoff + sub * EPT;
-    const int key_end = min(N, (I + 1) * BWD_COLS_KEYS);
+    const int key = I * BWD_COLS_KEYS + rsel;
+    if (key >= N) return;                              // (N is a multiple of 64: whole work-groups)
+    const long kj = (long)bh * N + key, hoff = (long)bh * N * D;
+    const elem* Qh = (const elem*)p.Q + hoff + L::column(sub);
+    const elem* Gh = (const elem*)p.dO + hoff + L::column(sub);
     const bool fresh = *p.nplain == 0;
-    float amax = 1.f;                        // the stored deltas are in units of max|dO| (see bwd_rows_kernel)
-    if constexpr (SCALED) {
-        amax = __uint_as_float(p.scal[0]);
-        if (!(amax > 0.f)) amax = 1.f;
+    const int cnt = min(p.kcnt[kj], KEY_LIST_CAP);
+    int nmax = cnt;                                    // the longest list of the wave's four keys
+    nmax = max(nmax, __shfl_xor(nmax, 16));
+    nmax = max(nmax, __shfl_xor(nmax, 32));
+    nmax = __builtin_amdgcn_readfirstlane(nmax);
+    if (nmax == 0 && !fresh) return;
+    const KeyEntry* el = (const KeyEntry*)p.klist + kj * KEY_LIST_CAP;
+    auto wave_fence = [] {                             // (the 16 lanes of a key sit in one wave, whose LDS operations execute in issue order)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    KeyEntry e[PER_LANE];
+    int rank[PER_LANE];
+    unroll_steps<PER_LANE>([&](auto qq) {
+        constexpr int q = decltype(qq)::value;
+        e[q] = KeyEntry{0xffffffffu, 0.f, 0.f};
+        rank[q] = 0;
+        if (16 * q < nmax && sub + 16 * q < cnt) { e[q] = el[sub + 16 * q]; row_s[rsel][sub + 16 * q] = e[q].row; }
+    });
+    wave_fence();
+    if (nmax <= 16) {
+        for (int j = 0; j < nmax; ++j) rank[0] += j < cnt && row_s[rsel][j] < e[0].row;
+    } else if (nmax <= 48) {
+        for (int j = 0; j < nmax; ++j) {
+            const uint32_t rj = j < cnt ? row_s[rsel][j] : 0xffffffffu;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) rank[q] += rj < e[q].row;
+        }
+    } else {
+        for (int j = 0; j < nmax; ++j) {
+            const uint32_t rj = j < cnt ? row_s[rsel][j] : 0xffffffffu;
+#pragma unroll
+            for (int q = 0; q < PER_LANE; ++q) rank[q] += rj < e[q].row;
+        }
     }
-    // The entries of a key were filed in the order an integer atomic handed out their slots, which
-    // changes from run to run.  They are summed in the order of their query rows instead (a row
-    // files at most one entry per key, so the rows are distinct): for a list longer than one batch
-    // the rank of every entry among the key's rows, found by the key's 16 lanes through LDS, gives
-    // the slot to read at each step (a short list is sorted in registers, below), and
-    // dK, dV of a key come out bit-identical in every run (keys with more entries than a list
-    // holds get the rest from bwd_hot_kernel's atomic additions and do not).
-    __shared__ int rows_s[16][KEY_LIST_CAP];
-    __shared__ unsigned char order_s[16][KEY_LIST_CAP];
-    constexpr int PER_LANE = KEY_LIST_CAP / 16;      // entries of a key's list per lane of its 16
-    static_assert(KEY_LIST_CAP <= 256 && (KEY_LIST_CAP & (KEY_LIST_CAP - 1)) == 0 && KEY_LIST_CAP >= 16, "slot indices are bytes, and masked");
-    for (int key = I * BWD_COLS_KEYS + rsel; key < key_end; key += 16) {
-        const long kj = (long)bh * N + key;
-        const int cnt = min(p.kcnt[kj], KEY_LIST_CAP);
-        if (cnt == 0 && !fresh) continue;
-        const uint4* el = (const uint4*)p.klist + kj * KEY_LIST_CAP;
-        if (cnt > CH) {
-            int myrow[PER_LANE], rank[PER_LANE];
-#pragma unroll
-            for (int q = 0; q < PER_LANE; ++q) {
-                const int i = sub + 16 * q;
-                myrow[q] = i < cnt ? (int)((const uint32_t*)(el + i))[0] : INT_MAX;
-                rank[q] = 0;
-                if (i < cnt) rows_s[rsel][i] = myrow[q];
-            }
-            // (the 16 lanes of a key sit in one wave, whose LDS operations execute in issue order)
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            for (int j = 0; j < cnt; ++j) {
-                const int rj = rows_s[rsel][j];
-#pragma unroll
-                for (int q = 0; q < PER_LANE; ++q) rank[q] += rj < myrow[q];
-            }
-#pragma unroll
-            for (int q = 0; q < PER_LANE; ++q)
-                if (sub + 16 * q < cnt) order_s[rsel][rank[q]] = (unsigned char)(sub + 16 * q);
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_fence();
+    unroll_steps<PER_LANE>([&](auto qq) {
+        constexpr int q = decltype(qq)::value;
+        if (16 * q < nmax && sub + 16 * q < cnt) {
+            row_s[rsel][rank[q]] = e[q].row;
+            val_s[rsel][rank[q]] = make_float2(e[q].dS, e[q].pr);
         }
-        float ak[EPT], av[EPT];
+    });
+    wave_fence();
+    float ak[EPT], av[EPT];
 #pragma unroll
-        for (int k = 0; k < EPT; ++k) { ak[k] = 0.f; av[k] = 0.f; }
-        for (int i0 = 0; i0 < cnt; i0 += CH) {
-            uint4 e[CH];
-            vvec qv[CH], gv[CH];
-            float nd[CH];                     // -delta / max|dO| of the entry's row
+    for (int k = 0; k < EPT; ++k) { ak[k] = 0.f; av[k] = 0.f; }
+    for (int i0 = 0; i0 < nmax; i0 += 16) {
+        const int i = i0 + L::entry_of(sub);
+        uint32_t row = 0u;
+        float2 w = make_float2(0.f, 0.f);              // dS, P
+        if (i < cnt) { row = row_s[rsel][i]; w = val_s[rsel][i]; }
+        unroll_steps<L::STEPS / BT>([&](auto b) {
+            constexpr int S0 = decltype(b)::value * BT;
+            if (S0 * L::PAR >= nmax - i0) return;
+            vec qv[BT], gv[BT];
+            unroll_steps<BT>([&](auto u) {
+                constexpr int U = decltype(u)::value;
+                const size_t off = (size_t)(L::template of_step<S0 + U>(row) * (uint32_t)D);
+                qv[U] = *(const vec*)(Qh + off);
+                gv[U] = *(const vec*)(Gh + off);
+            });
+            unroll_steps<BT>([&](auto u) {
+                constexpr int U = decltype(u)::value;
+                add_scaled<EPT>(ak, L::template of_step<S0 + U>(w.x), qv[U]);
+                add_scaled<EPT>(av, L::template of_step<S0 + U>(w.y), gv[U]);
+            });
+        });
+    }
+    if (cnt == 0 && !fresh) return;
 #pragma unroll
-            for (int u = 0; u < CH; ++u)
-                e[u] = i0 + u < cnt ? el[cnt > CH ? (int)order_s[rsel][i0 + u] & (KEY_LIST_CAP - 1) : u] : make_uint4(0xffffffffu, 0u, 0u, 0u);
-            if (cnt <= CH) {
-                // a short list is put in row order in registers (no second trip to memory): a
-                // sorting network of five exchanges; the unused slots, row 0xffffffff, end up last
-                auto exchange = [&](int i, int j) {
-                    if (e[j].x < e[i].x) { const uint4 t = e[i]; e[i] = e[j]; e[j] = t; }
-                };
-                static_assert(CH == 4 || CH == 2, "networks for two and for four entries");
-                if constexpr (CH == 4) { exchange(0, 1); exchange(2, 3); exchange(0, 2); exchange(1, 3); exchange(1, 2); }
-                else exchange(0, 1);
-            }
-#pragma unroll
-            for (int u = 0; u < CH; ++u)
-                if (i0 + u >= cnt) e[u] = make_uint4(0u, 0u, 0u, 0u);
-#pragma unroll
-            for (int u = 0; u < CH; ++u) {
-#pragma unroll
-                for (int k = 0; k < EPT; ++k) { qv[u][k] = (elem)0.f; gv[u][k] = (elem)0.f; }
-                nd[u] = 0.f;
-                if (i0 + u < cnt) {
-                    qv[u] = *(const vvec*)(Qh + (long)e[u].x * D);
-                    gv[u] = *(const vvec*)(Gh + (long)e[u].x * D);
-                    nd[u] = p.delta[(long)bh * N + e[u].x];
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < CH; ++u) {
-                // dS = u dP - u delta; P (all zero past the end)
-                const float dS = fmaf(__uint_as_float(e[u].z), nd[u] * amax, __uint_as_float(e[u].y)), pr = __uint_as_float(e[u].w);
-#pragma unroll
-                for (int k = 0; k < EPT; ++k) { ak[k] = fmaf(dS, (float)qv[u][k], ak[k]); av[k] = fmaf(pr, (float)gv[u][k], av[k]); }
-            }
-        }
-        float* dk = p.dK + kj * D + sub * EPT;
-        float* dv = p.dV + kj * D + sub * EPT;
+    for (int k = 0; k < EPT; ++k) { ak[k] = L::halves_sum(ak[k]) * p.inv_sqrt_d; av[k] = L::halves_sum(av[k]); }
+    float* dk = p.dK + kj * D;
+    float* dv = p.dV + kj * D;
+    if (!fresh) {
+        // (a lane adds what it will store: with two entries side by side each half stores half of its share)
 #pragma unroll
         for (int k = 0; k < EPT; k += 4) {
-            ovec a = ovec{0.f, 0.f, 0.f, 0.f}, b = a;
-            if (!fresh) { a = *(ovec*)(dk + k); b = *(ovec*)(dv + k); }
+            const f4 a = *(const f4*)(dk + L::column(sub) + k), b = *(const f4*)(dv + L::column(sub) + k);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) { a[q] = fmaf(ak[k + q], p.inv_sqrt_d, a[q]); b[q] += av[k + q]; }
-            *(ovec*)(dk + k) = a;
-            *(ovec*)(dv + k) = b;
+            for (int q = 0; q < 4; ++q) { ak[k + q] += a[q]; av[k + q] += b[q]; }
         }
     }
+    L::store(dk, ak, sub);
+    L::store(dv, av, sub);
 }
 
 static __global__ void mask_popcount_kernel(const int32_t* mask, long nwords, int32_t* out) {

@@ -10,21 +10,25 @@ constexpr int MAX_W = 64;       // mask words per row
 // A row group's output comes from the gather kernel when its candidate lists average at most
 // GATHER_LIST_MAX entries per row and its supports at most GATHER_SUP_MAX keys per row.
 constexpr int GATHER_LIST_MAX = 320, GATHER_SUP_MAX = 48;
-// Backward: support entries per lane list (two lists per row), entries per key in the lists by key,
-// and the non-zeros per marked 64 x 64 tile up to which a row group takes the gather path.
-// Work-group sizes of the gather kernels: each 16 lanes take one row (or key) at a time, a chain of
-// dependent loads; 16 rows or keys per work-group (one per 16 lanes) measured 10 - 20 % faster than
-// 128 - 256 per work-group, whose lanes walked 8 - 16 such chains one after the other.
 // Query tiles per part of a mask column in dkdv_kernel from 65536 tokens on (half that below;
 // every part pays the column walk, the owned K, V fragments and atomic adds of its results, and an
 // empty part a work-group's launch: parts of 32 or 16 tiles measured slower at every length).
 constexpr int COL_PART = 128;
-constexpr int GATHER_ROWS = 16;          // rows per work-group of gather_out / bwd_rows / bwd_hot
+// Work-group sizes of the gather kernels: each 16 lanes take one row (or key), a chain of
+// dependent loads; 16 rows or keys per work-group (one per 16 lanes) measured 10 - 20 % faster than
+// 128 - 256 per work-group, whose lanes walked 8 - 16 such chains one after the other.
+constexpr int GATHER_ROWS = 16;          // rows per work-group of gather_out / bwd_rows
 constexpr int BWD_COLS_KEYS = 16;        // keys per work-group of bwd_cols_kernel
-constexpr int BWD_LIST_CAP = 64, KEY_LIST_CAP = 128, BWD_ENTRIES_PER_TILE = 32, BWD_ENTRIES_PER_ROW = 6, BWD_FEW_TILES = 40;
+// Backward: support entries per lane list (two lists per row), entries per key in the lists by key,
+// and the non-zeros per marked 64 x 64 tile up to which a row group takes the gather path.
+constexpr int BWD_LIST_CAP = 64, KEY_LIST_CAP = 128, BWD_ENTRIES_PER_ROW = 6, BWD_FEW_TILES = 40;
+constexpr int bwd_entries_per_tile(int d, int) { return 32 * d / 128 * d / 128; }
 // The gather kernels' fixed cost is a few passes over dK and dV; below this many marked tiles per
 // 64-row block (at head dim 128; twice as many at 64) the matrix kernels' whole time is less.
 constexpr int BWD_MIN_TILES_PER_BLOCK = 16;
+
+// An entry of a key's list: the query row and its dS and P there.
+struct KeyEntry { uint32_t row; float dS, pr; };
 
 constexpr int ALPHA_15 = 0, ALPHA_20 = 1, ALPHA_GEN = 2;
 constexpr int LIST_CAP = 256;   // candidate entries per (row, lane half)
@@ -74,7 +78,7 @@ struct Params {
     int32_t* nplain;      // backward: number of row groups that stay with dq_kernel / dkdv_kernel
     int32_t* nmarked;     // backward: set bits of the whole mask
     int32_t* defer;       // backward [BH][N]: entries of the row left to bwd_hot_kernel
-    void* klist;          // backward [BH][N][KEY_LIST_CAP]: (query row, u dP, u, P), 16 bytes each
+    void* klist;          // backward [BH][N][KEY_LIST_CAP] KeyEntry
     int32_t* oflag;       // [BH][T] 1 = some row of this 64-row block has more candidates than its lists hold
     unsigned long long* stats;
     // bits of non-negative floats kept in the workspace (atomicMax on the bit patterns):

@@ -11,6 +11,7 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "gather.hpp"
 
 namespace ea {
 
@@ -1088,16 +1089,15 @@ __global__ __launch_bounds__(NW * 64) void out_kernel(Params p) {
 // Phase 4 for sparse row groups: O_r = sum over the row's support of p_j V_j, from the support
 // entries (raw score, key index) that tau_list_kernel left at the front of the row's two lists.
 // With a handful of non-zeros per row this is a gather of a few rows of V, not a matrix product:
-// sixteen lanes per row, each with D / 16 elements of the row of O; four entries, then their rows
-// of V, are requested together.  V is read in the caller's element type.
+// sixteen lanes per row (GatherLanes).  V is read in the caller's element type.
 template <class E, int D, int AM>
 __global__ __launch_bounds__(256) void gather_out_kernel(Params p) {
     using elem = typename E::elem;
-    constexpr int EPT = D / 16, GCH = 2;              // entries in flight per lane group (measured: 2 beats 1, 4 and 8)
-    typedef elem vvec __attribute__((ext_vector_type(EPT)));
-    typedef float ovec __attribute__((ext_vector_type(4)));
+    using L = GatherLanes<E, D>;
+    using vec = typename L::vec;
+    constexpr int EPT = L::EPT, BT = 4;               // rows of V in flight per lane
     const int tid = threadIdx.x, sub = tid & 15, rsel = tid >> 4;
-    // a work-group takes GATHER_ROWS rows of a row group (one or a few per 16 lanes): the rows are
+    // a work-group takes GATHER_ROWS rows of a row group (one per 16 lanes): the rows are
     // chains of dependent loads, so many short work-groups hide their latency better than few long ones
     const int N = p.N, G = (N + p.grows - 1) / p.grows, parts = p.grows / GATHER_ROWS;
     int bh, I;
@@ -1105,46 +1105,39 @@ __global__ __launch_bounds__(256) void gather_out_kernel(Params p) {
     const int part = I % parts;
     I /= parts;
     if (!p.gflag[(long)bh * G + I]) return;
+    const int row = I * p.grows + part * GATHER_ROWS + rsel;
+    if (row >= N) return;                             // (N is a multiple of 64: whole work-groups)
     const HeadConsts hc = head_consts(p, bh);
     const float c = hc.c, r = hc.r;
-    const elem* Vh = (const elem*)p.V + (long)bh * N * D + sub * EPT;
-    const char* lists_h = (const char*)p.lists + (size_t)bh * N * (2 * LIST_CAP * 8);
-    const int row_end = min(N, I * p.grows + (part + 1) * GATHER_ROWS);
-    for (int row = I * p.grows + part * GATHER_ROWS + rsel; row < row_end; row += 16) {
-        const long gi = (long)bh * N + row;
-        const float tau = p.tau[gi];
-        const int s0 = p.scnt[gi * 2], tot = s0 + p.scnt[gi * 2 + 1];
-        const char* l0 = lists_h + (size_t)row * (2 * LIST_CAP * 8);      // the second list follows the first
-        float acc[EPT];
+    const elem* Vh = (const elem*)p.V + (long)bh * N * D + L::column(sub);
+    const long gi = (long)bh * N + row;
+    const float tau = p.tau[gi];
+    const int s0 = p.scnt[gi * 2], tot = s0 + p.scnt[gi * 2 + 1];
+    const char* l0 = (const char*)p.lists + (size_t)gi * (2 * LIST_CAP * 8);      // the second list follows the first
+    int nmax = tot;                                   // the longest of the wave's four rows
+    nmax = max(nmax, __shfl_xor(nmax, 16));
+    nmax = max(nmax, __shfl_xor(nmax, 32));
+    nmax = __builtin_amdgcn_readfirstlane(nmax);
+    float acc[EPT];
 #pragma unroll
-        for (int k = 0; k < EPT; ++k) acc[k] = 0.f;
-        for (int i0 = 0; i0 < tot; i0 += GCH) {
-            uint2 e[GCH];
-            vvec v[GCH];
-#pragma unroll
-            for (int u = 0; u < GCH; ++u) {
-                const int i = i0 + u;
-                e[u] = make_uint2(0u, 0u);
-                if (i < tot) e[u] = *(const uint2*)(l0 + (i < s0 ? i * 8 : LIST_CAP * 8 + (i - s0) * 8));
-            }
-#pragma unroll
-            for (int u = 0; u < GCH; ++u) {
-#pragma unroll
-                for (int k = 0; k < EPT; ++k) v[u][k] = (elem)0.f;
-                if (i0 + u < tot) v[u] = *(const vvec*)(Vh + (long)e[u].y * D);
-            }
-#pragma unroll
-            for (int u = 0; u < GCH; ++u) {
-                const float y = fmaf(c, __uint_as_float(e[u].x), -tau);
-                const float pr = (i0 + u < tot && y > 0.f) ? pow_r<AM>(y, r) : 0.f;
-#pragma unroll
-                for (int k = 0; k < EPT; ++k) acc[k] = fmaf(pr, (float)v[u][k], acc[k]);
-            }
-        }
-        float* out = p.O + gi * D + sub * EPT;
-#pragma unroll
-        for (int k = 0; k < EPT; k += 4) *(ovec*)(out + k) = ovec{acc[k], acc[k + 1], acc[k + 2], acc[k + 3]};
+    for (int k = 0; k < EPT; ++k) acc[k] = 0.f;
+    for (int i0 = 0; i0 < nmax; i0 += 16) {
+        const int i = i0 + L::entry_of(sub);
+        uint2 e = make_uint2(0u, 0u);
+        if (i < tot) e = *(const uint2*)(l0 + (i < s0 ? i * 8 : LIST_CAP * 8 + (i - s0) * 8));
+        const float y = fmaf(c, __uint_as_float(e.x), -tau);
+        const float pr = (i < tot && y > 0.f) ? pow_r<AM>(y, r) : 0.f;
+        unroll_steps<L::STEPS / BT>([&](auto b) {
+            constexpr int S0 = decltype(b)::value * BT;
+            if (S0 * L::PAR >= nmax - i0) return;
+            vec v[BT];
+            unroll_steps<BT>([&](auto u) { v[decltype(u)::value] = *(const vec*)(Vh + (size_t)(L::template of_step<S0 + decltype(u)::value>(e.y) * (uint32_t)D)); });
+            unroll_steps<BT>([&](auto u) { add_scaled<EPT>(acc, L::template of_step<S0 + decltype(u)::value>(pr), v[decltype(u)::value]); });
+        });
     }
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) acc[k] = L::halves_sum(acc[k]);
+    L::store(p.O + gi * D, acc, sub);
 }
 
 // All causally visible tiles set: the working mask handed to out_kernel<MASK_ONLY>.

@@ -148,7 +148,7 @@ struct Ops {
             if (p.fwd_gflag) {
                 // the forward's lists were handed over: no sweep, only the decision per row group
                 static_assert(32 * QBB * NW_BLIST <= 128, "one thread per row of a group");
-                rc = launch(bwd_decide_kernel<D, AM>, groups(p, NW_BLIST, QBB), 128, s, po);
+                rc = launch(bwd_decide_kernel<E, D, AM>, groups(p, NW_BLIST, QBB), 128, s, po);
             } else {
                 rc = launch(bwd_list_kernel<E, D, QBB, AM, NW_BLIST>, groups(p, NW_BLIST, QBB), NW_BLIST * 64, s, po);
             }
@@ -195,9 +195,10 @@ struct Ops {
             ScopedKernelTime t(EA_TIMER_BWD_GATHER, s);
             rc = launch(bwd_rows_kernel<E, D, AM, E2::SCALED>, dim3(p.BH * ((p.N + p.grows - 1) / p.grows) * (p.grows / GATHER_ROWS)), 256, s, po);
             if (rc) return rc;
-            rc = launch(bwd_cols_kernel<E, D, E2::SCALED>, dim3(p.BH * ((p.N + BWD_COLS_KEYS - 1) / BWD_COLS_KEYS)), 256, s, po);
+            rc = launch(bwd_cols_kernel<E, D>, dim3(p.BH * ((p.N + BWD_COLS_KEYS - 1) / BWD_COLS_KEYS)), 256, s, po);
             if (rc) return rc;
-            rc = launch(bwd_hot_kernel<E, D, AM, E2::SCALED>, dim3(p.BH * ((p.N + p.grows - 1) / p.grows) * (p.grows / GATHER_ROWS)), 256, s, po);
+            static_assert(32 * QBB * NW_BLIST <= 128, "rows of a group bwd_hot_kernel looks through");
+            rc = launch(bwd_hot_kernel<E, D, AM, E2::SCALED>, dim3(p.BH * ((p.N + p.grows - 1) / p.grows)), 256, s, po);
             if (rc) return rc;
         }
         return EA_OK;
