@@ -741,7 +741,7 @@ __global__ __launch_bounds__(NW * 64) void bwd_list_kernel(Params p) {
 
     // a mask with few marked tiles altogether: the matrix kernels are done before the gather
     // kernels' passes over dK, dV would be
-    if ((long)*p.nmarked * D < (long)BWD_MIN_TILES_PER_BLOCK * 128 * p.BH * T) {
+    if ((long)*p.nmarked < (long)BWD_MIN_TILES_PER_BLOCK * p.BH * T) {
         if (tid == 0) {
             p.gflag[(long)bh * ((N + BR - 1) / BR) + I] = 0;
             atomicAdd(p.nplain, 1);
@@ -764,7 +764,7 @@ __global__ __launch_bounds__(NW * 64) void bwd_list_kernel(Params p) {
     // head - still has one entry or more per row, and is cheap either way: it goes with the rest,
     // so that the matrix kernels' input copies are not made for its sake alone)
     constexpr int PER_ROW_X128 = BWD_ENTRIES_PER_ROW * D * D / 128 / (AM == ALPHA_GEN ? 2 : 1);
-    const int budget = max(bwd_entries_per_tile(D, sizeof(elem)) / (AM == ALPHA_GEN ? 2 : 1) * gsum[1],
+    const int budget = max(bwd_entries_per_tile(D, sizeof(elem)) * gsum[1],
                            gsum[1] <= BWD_FEW_TILES ? PER_ROW_X128 * min(BR, N - (int)((long)I * BR)) / 128 : 0);
 
     Owned<E, D, QB> qf;
@@ -881,7 +881,7 @@ __global__ __launch_bounds__(128) void bwd_decide_kernel(Params p) {
     int bh, I;
     map_block(blockIdx.x, p.BH, G, bh, I);
     const int fwd_grows = (int)p.fwd_scal[2];
-    bool gather = (long)*p.nmarked * D >= (long)BWD_MIN_TILES_PER_BLOCK * 128 * p.BH * T && fwd_grows > 0
+    bool gather = (long)*p.nmarked >= (long)BWD_MIN_TILES_PER_BLOCK * p.BH * T && fwd_grows > 0
                   && p.fwd_gflag[(long)bh * ((N + fwd_grows - 1) / fwd_grows) + (I * BR) / fwd_grows] != 0;
     if (tid < 2) gsum[tid] = 0;
     __syncthreads();
@@ -899,7 +899,7 @@ __global__ __launch_bounds__(128) void bwd_decide_kernel(Params p) {
     __syncthreads();
     if (tid == 0) {
             constexpr int PER_ROW_X128 = BWD_ENTRIES_PER_ROW * D * D / 128 / (AM == ALPHA_GEN ? 2 : 1);
-        const int budget = max(bwd_entries_per_tile(D, sizeof(typename E::elem)) / (AM == ALPHA_GEN ? 2 : 1) * gsum[1],
+        const int budget = max(bwd_entries_per_tile(D, sizeof(typename E::elem)) * gsum[1],
                                gsum[1] <= BWD_FEW_TILES ? PER_ROW_X128 * min(BR, N - I * BR) / 128 : 0);
         gather = gather && gsum[0] <= budget;
         p.gflag[(long)bh * G + I] = gather;

@@ -8,8 +8,11 @@ namespace ea {
 constexpr int MAX_T = 2048;     // N <= 131072
 constexpr int MAX_W = 64;       // mask words per row
 // A row group's output comes from the gather kernel when its candidate lists average at most
-// GATHER_LIST_MAX entries per row and its supports at most GATHER_SUP_MAX keys per row.
-constexpr int GATHER_LIST_MAX = 320, GATHER_SUP_MAX = 48;
+// GATHER_LIST_MAX entries per row (480 of the 512 they hold) and its supports at most GATHER_SUP_MAX keys per row: the
+// gather takes about 0.02 ns per entry, the matrix kernel 3.2 ns per marked tile at head dim 128 (8192 tokens,
+// sigma = 0.8, about 60 keys per row: gather 105 us, matrix 292 us; near 200 keys per row, alpha = 1.25 at
+// sigma = 1, the two are level: 343 and 315 us).
+constexpr int GATHER_LIST_MAX = 480, GATHER_SUP_MAX = 96;
 // Query tiles per part of a mask column in dkdv_kernel from 65536 tokens on (half that below;
 // every part pays the column walk, the owned K, V fragments and atomic adds of its results, and an
 // empty part a work-group's launch: parts of 32 or 16 tiles measured slower at every length).
@@ -19,13 +22,22 @@ constexpr int COL_PART = 128;
 // 128 - 256 per work-group, whose lanes walked 8 - 16 such chains one after the other.
 constexpr int GATHER_ROWS = 16;          // rows per work-group of gather_out / bwd_rows
 constexpr int BWD_COLS_KEYS = 16;        // keys per work-group of bwd_cols_kernel
-// Backward: support entries per lane list (two lists per row), entries per key in the lists by key,
-// and the non-zeros per marked 64 x 64 tile up to which a row group takes the gather path.
-constexpr int BWD_LIST_CAP = 64, KEY_LIST_CAP = 128, BWD_ENTRIES_PER_ROW = 6, BWD_FEW_TILES = 40;
-constexpr int bwd_entries_per_tile(int d, int) { return 32 * d / 128 * d / 128; }
-// The gather kernels' fixed cost is a few passes over dK and dV; below this many marked tiles per
-// 64-row block (at head dim 128; twice as many at 64) the matrix kernels' whole time is less.
-constexpr int BWD_MIN_TILES_PER_BLOCK = 16;
+// Backward: support entries per lane list (two lists per row) and entries per key in the lists by key.
+constexpr int BWD_LIST_CAP = 64, KEY_LIST_CAP = 128;
+// Non-zeros per marked 64 x 64 tile up to which a row group's backward takes the gather path.  Gather
+// and matrix time of both directions: about 0.09 ns per entry and 6.3 ns per tile at head dim 64 (64 heads of 4096 tokens,
+// sigma = 1.5: with a limit of 8 / 32 / 64 / 128 the backward takes 945 / 480 / 335 / 350 us), 0.13 and
+// 13.4 ns at head dim 128, where the gather's rows are twice as long and keys with full lists come in first (16384 tokens,
+// sigma = 1, 32 / 64 / 128: 2220 / 2215 / 2330 us).  The power functions of general alpha weigh on both sides alike.
+// fp32 matrix products run at a sixteenth of the 16-bit rate, 72 ns per tile: 16 heads of 2048 tokens at d = 64,
+// sigma = 1, backward with 40 / 128 / 512: 640 / 295 / 150 us.
+constexpr int bwd_entries_per_tile(int d, int elem_bytes) { return elem_bytes == 4 ? 512 : d == 64 ? 64 : 40; }
+// ... or, in a group with at most BWD_FEW_TILES marked tiles, BWD_ENTRIES_PER_ROW per row (at head dim 128).
+constexpr int BWD_ENTRIES_PER_ROW = 6, BWD_FEW_TILES = 40;
+// The gather kernels' fixed cost is a few passes over dK and dV, 0.3 - 0.45 ns per row: what the matrix
+// kernels need for about two tiles per 64-row block.  Below that the mask as a whole stays with them.
+// (8192 tokens, d = 64, block-structured inputs with 5 tiles per block: matrix 773, gather 650 us a step.)
+constexpr int BWD_MIN_TILES_PER_BLOCK = 2;
 
 // An entry of a key's list: the query row and its dS and P there.
 struct KeyEntry { uint32_t row; float dS, pr; };

@@ -532,3 +532,28 @@ def test_values_beyond_fp16_range_are_clamped_and_counted(ea):
             assert got == ((2, 2) if big else (0, 0))
     finally:
         ea.entmax_attn_gather_enable(True)
+
+
+@pytest.mark.parametrize("dtype,d,N,top", [("bf16", 64, 4096, 4.0), ("bf16", 128, 4096, 4.0), ("f32", 64, 2048, 1.4), ("f32", 128, 2048, 1.4)])
+def test_gathered_rows_of_every_length(ea, dtype, d, N, top):
+    # the gather kernels work in chunks of sixteen entries, keep three chunks of a row in registers
+    # and put a key's entries in order by sixteens: queries scaled from row to row give supports from one key to
+    # well over a hundred, side by side in one wave, and keys with one to dozens of entries
+    B, H, alpha, causal = 1, 1, 1.5, False
+    q, k, v, do = workloads.gaussian_qkv(B, H, N, d, dtype, 1.0, seed=131)
+    scale = torch.linspace(0.55, top, 64).repeat(N // 64)[torch.randperm(N, generator=torch.Generator().manual_seed(7))]
+    q = (q.float() * scale[None, None, :, None]).to(q.dtype)
+    Q, K, V, dO = (t.cuda() for t in (q, k, v, do))
+    wf = torch.empty(ea.entmax_attn_workspace_bytes(B, H, N, d, dtype, causal, False), dtype=torch.uint8, device="cuda")
+    wb = torch.empty(ea.entmax_attn_workspace_bytes(B, H, N, d, dtype, causal, True), dtype=torch.uint8, device="cuda")
+    O, tau, mask = ea.entmax_attn_fwd(Q, K, V, alpha, causal, workspace=wf)
+    dQ, dK, dV = ea.entmax_attn_bwd(Q, K, V, O, dO, tau, alpha, causal, block_mask=mask, workspace=wb, fwd_workspace=wf)
+    torch.cuda.synchronize()
+    rows = (ea.read_stats(wf)["gather_rows"], ea.read_stats(wb)["bwd_gather_rows"])
+    X = (alpha - 1.0) * (parity.to_np64(q)[0, 0] @ parity.to_np64(k)[0, 0].T) / np.sqrt(d)
+    support = (X > parity.to_np64(tau)[0, 0][:, None]).sum(1)
+    print(f"  every length {dtype} d={d}: rows by gather {rows} of {N}; supports {support.min()} .. {support.max()}, mean {support.mean():.1f}", flush=True)
+    assert rows == (N, N) and support.min() <= 4 and support.max() > 64
+    ref, info = parity.check_forward(q, k, v, alpha, causal, O, tau, mask, label=f"lengths {dtype} {d}", rounding_slack=dtype == "f32")
+    _, ginfo = parity.check_backward(q, k, v, do, alpha, causal, dQ, dK, dV, label=f"lengths {dtype} {d}", tau_ref=ref["tau"])
+    print("  ", info, ginfo, flush=True)
