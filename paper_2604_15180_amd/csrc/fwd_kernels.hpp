@@ -18,46 +18,66 @@ namespace ea {
 // ---- histogram solve (App. C.3), one thread per row ------------------------------------------
 // The row's histogram is a window of SLOTS consecutive bins of an absolute grid of width h,
 // kept in a circular buffer: bin k of the window (left edge k h above the window's origin) is
-// H[(rot + k) % SLOTS].  Returns the root tau_h of f_h(tau) = -1 + sum_k H_k [k h - tau]_+^r
-// (Eq. 9) in units above the origin; -h for an empty histogram.
-template <int AM, int SLOTS, int BITS>
-EA_DEV float solve_histogram(const uint32_t* H, int rot, int shift, float h, float r) {
-    // counters of BITS bits at bit `shift` of each word (two rows share a word when BITS == 16)
-    auto count = [&](int k) {
-        const uint32_t w = H[(rot + k) & (SLOTS - 1)] >> shift;
-        return (float)(BITS == 32 ? w : (w & ((1u << (BITS & 31)) - 1u)));
-    };
-    if constexpr (AM == ALPHA_15 || AM == ALPHA_20) {
-        // Descending scan keeping S0, S1, S2 of the bins met so far.  The active set is the largest
-        // one whose root lies below the left edge e of its lowest non-empty bin, i.e. (f_h falls
-        // with tau) the largest one with f_h(e) < 0; f_h(e) is a polynomial in the three sums, so
-        // the scan needs no division, and the root is formed once, from the sums of that set.
-        float S0 = 0.f, S1 = 0.f, S2 = 0.f, B0 = 0.f, B1 = 0.f, B2 = 0.f;
-#pragma unroll 8
-        for (int k = SLOTS - 1; k >= 0; --k) {
-            const float cnt = count(k);
+// H[(rot + k) % SLOTS].
+//
+// Descending scan keeping S0, S1, S2 (count, sum and sum of squares of the left edges) of the bins met so far, for a
+// lower bound of f_h that has a closed-form root.  With y_k = k h - tau, r = 1/(alpha-1), and 0 < y <= 1 inside the window:
+//   MOM 1:  sum y^r >= sum y                          (r <= 1; equality at alpha = 2)
+//   MOM 2:  sum y^r >= sum y^2                        (r <= 2; equality at alpha = 1.5)
+//   MOM 3:  sum y^r >= S0 (sum y^2 / S0)^(r/2)        (r >= 2, power means), which reaches 1 where sum y^2 does S0^(1 - 2/r)
+// The active set is the largest one whose root lies below the left edge e of its lowest non-empty
+// bin, i.e. the largest one whose bound at e is below 1: a polynomial in the three sums, so
+// the scan needs no division, and the root is formed once, from the sums of that set.  Returns that
+// root, in units above the origin - the root tau_h of f_h (Eq. 9) itself where equality holds, else
+// a value below it; -h for an empty histogram.  A scan ends as soon as every lane's set is complete.
+template <int MOM, int SLOTS, int BITS>
+EA_DEV float histogram_moment_root(const uint32_t* H, int rot, int shift, float h, float r) {
+    float S0 = 0.f, S1 = 0.f, S2 = 0.f, B0 = 0.f, B1 = 0.f, B2 = 0.f;
+    const float q = 1.f - 2.f / r;
+    for (int k8 = SLOTS - 8; k8 >= 0; k8 -= 8) {
+        bool below = true;
+#pragma unroll
+        for (int k = k8 + 7; k >= k8; --k) {
+            // counters of BITS bits at bit `shift` of each word (two rows share a word when BITS == 16)
+            const uint32_t w = H[(rot + k) & (SLOTS - 1)] >> shift;
+            const float cnt = (float)(BITS == 32 ? w : (w & ((1u << (BITS & 31)) - 1u)));
             const float e = k * h;
             S0 += cnt; S1 = fmaf(cnt, e, S1); S2 = fmaf(cnt * e, e, S2);
             float fe;
-            if constexpr (AM == ALPHA_20) fe = S1 - e * S0 - 1.f;
-            else fe = fmaf(e, fmaf(e, S0, -2.f * S1), S2) - 1.f;
+            if constexpr (MOM == 1) fe = S1 - e * S0 - 1.f;
+            else fe = fmaf(e, fmaf(e, S0, -2.f * S1), S2) - (MOM == 2 ? 1.f : __builtin_amdgcn_exp2f(q * __builtin_amdgcn_logf(S0)));
+            below = fe < 0.f || S0 == 0.f;             // (S0 = 0: log2 is -inf and fe is -0 or NaN)
             if (cnt > 0.f && fe < 0.f) { B0 = S0; B1 = S1; B2 = S2; }
         }
-        if (B0 == 0.f) return -h;
-        if constexpr (AM == ALPHA_20) return (B1 - 1.f) / B0;
-        const float mean = B1 / B0;
-        return mean - sqrtf(fmaxf(mean * mean - (B2 - 1.f) / B0, 0.f));
-    } else {
-        // general alpha: bisection of f_h on [-h, (SLOTS-1) h]; for alpha <= 2 then Newton from the
-        // left end (f_h is convex and decreasing there, so Newton from the left is monotone and
-        // stays at or below the root); for alpha > 2 f_h is not convex, so the bisection is run
-        // further instead and its left end, where f_h >= 0, is returned
+        if (!__any(below)) break;                      // (the bound only rises towards lower edges)
+    }
+    if (B0 == 0.f) return -h;
+    if constexpr (MOM == 1) return (B1 - 1.f) / B0;
+    const float mean = B1 / B0;
+    const float target = MOM == 2 ? 1.f : __builtin_amdgcn_exp2f(q * __builtin_amdgcn_logf(B0));
+    return mean - sqrtf(fmaxf(mean * mean - (B2 - target) / B0, 0.f));
+}
+// A lower bound of the histogram's root for general alpha, from the closed forms alone
+template <int SLOTS, int BITS>
+EA_DEV float histogram_lower_bound(const uint32_t* H, int rot, int shift, float h, float r) {
+    if (r >= 2.f) return histogram_moment_root<3, SLOTS, BITS>(H, rot, shift, h, r);
+    if (r >= 1.f) return histogram_moment_root<2, SLOTS, BITS>(H, rot, shift, h, r);
+    return histogram_moment_root<1, SLOTS, BITS>(H, rot, shift, h, r);
+}
+// The root tau_h of f_h(tau) = -1 + sum_k H_k [k h - tau]_+^r (Eq. 9) in units above the origin;
+// -h for an empty histogram.
+template <int AM, int SLOTS, int BITS>
+EA_DEV float solve_histogram(const uint32_t* H, int rot, int shift, float h, float r) {
+    if constexpr (AM == ALPHA_15) return histogram_moment_root<2, SLOTS, BITS>(H, rot, shift, h, r);
+    else if constexpr (AM == ALPHA_20) return histogram_moment_root<1, SLOTS, BITS>(H, rot, shift, h, r);
+    else {
         auto eval = [&](float tau, float& f1) {
             float f = -1.f; f1 = 0.f;
             for (int k = SLOTS - 1; k >= 0; --k) {
                 const float y = k * h - tau;
                 if (y <= 0.f) break;
-                const float cnt = count(k);
+                const uint32_t w = H[(rot + k) & (SLOTS - 1)] >> shift;
+                const float cnt = (float)(BITS == 32 ? w : (w & ((1u << (BITS & 31)) - 1u)));
                 if (cnt == 0.f) continue;
                 const float pr1 = pow_r1<AM>(y, r);
                 f += cnt * pr1 * y;
@@ -65,19 +85,27 @@ EA_DEV float solve_histogram(const uint32_t* H, int rot, int shift, float h, flo
             }
             return f;
         };
-        float lo = -h, hi = (SLOTS - 1) * h, d1;
-        const int nbis = r < 1.f ? 22 : 12;
-        for (int i = 0; i < nbis; ++i) {
-            const float mid = 0.5f * (lo + hi);
-            if (eval(mid, d1) >= 0.f) lo = mid; else hi = mid;
+        float d1;
+        if (r < 1.f) {
+            // alpha > 2: f_h is not convex; bisection of [-h, (SLOTS-1) h], whose left end, where f_h >= 0, is returned
+            float lo = -h, hi = (SLOTS - 1) * h;
+            for (int i = 0; i < 22; ++i) {
+                const float mid = 0.5f * (lo + hi);
+                if (eval(mid, d1) >= 0.f) lo = mid; else hi = mid;
+            }
+            return lo;
         }
-        float tau = lo;
-        for (int i = 0; i < 4 && !(r < 1.f); ++i) {
+        // alpha <= 2: f_h is convex and decreasing, so Newton from the left is monotone and
+        // stays at or below the root; from the closed-form bound it needs three or four steps
+        // (bisecting first took sixteen evaluations)
+        float tau = histogram_lower_bound<SLOTS, BITS>(H, rot, shift, h, r);
+        for (int i = 0; i < 12; ++i) {
             const float f = eval(tau, d1);
-            if (d1 >= 0.f) break;
-            const float nt = tau - f / d1;
-            if (!(nt > tau) || nt > hi) break;
-            tau = nt;
+            const float nt = tau - f / d1;             // (d1 = 0, an empty histogram: NaN or inf, not taken)
+            const bool moves = d1 < 0.f && nt > tau && nt <= (SLOTS - 1) * h;
+            const bool far = moves && nt - tau > 1e-7f;
+            if (moves) tau = nt;
+            if (!__any(far)) break;
         }
         return tau;
     }
@@ -448,26 +476,6 @@ __global__ __launch_bounds__(NW * 64) void tau_kernel(Params p) {
     }
 }
 
-// A cheap lower bound of the histogram's root for general alpha, used while the sweep is under way:
-// the largest bin edge e_j with f_h(e_j) >= 0 (f_h falls with tau, so tau_h >= e_j), found by
-// bisection over j.  At a bin edge f_h needs no power function: f_h(e_j) = sum_{k>j} H_k pw[k-j] - 1
-// with the table pw[m] = (m h)^r.  Returns -h when even the window's bottom edge is too high.
-template <int SLOTS, int BITS>
-EA_DEV float histogram_edge_bound(const uint32_t* H, int rot, int shift, float h, const float* pw) {
-    auto count = [&](int k) {
-        const uint32_t w = H[(rot + k) & (SLOTS - 1)] >> shift;
-        return (float)(BITS == 32 ? w : (w & ((1u << (BITS & 31)) - 1u)));
-    };
-    int lo = -1, hi = SLOTS - 1;          // f_h(e_hi) = -1 < 0: no bin lies above the top one
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        float f = -1.f;
-        for (int k = mid + 1; k < SLOTS; ++k) f = fmaf(count(k), pw[k - mid], f);
-        if (f >= 0.f) lo = mid; else hi = mid;
-    }
-    return (float)lo * h;
-}
-
 // ---- threshold kernel with candidate lists -----------------------------------------------------
 // Phases 1-3 of Alg. 1 from ONE dense sweep.  By Eq. 5, tau* >= max - 1 (in units of (alpha-1) s),
 // and both the maximum and tau* over a prefix of the keys are at most their values over all keys,
@@ -502,7 +510,6 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 
     constexpr int HIST_WORDS = PAIR ? SM::HIST_WORDS / 2 : SM::HIST_WORDS;
     constexpr int CB = PAIR ? 16 : SM::CBITS;            // bits per counter
     __shared__ __align__(256) uint32_t hist[HIST_WORDS];
-    __shared__ float pw[AM == ALPHA_GEN ? SLOTS : 1];             // (m h)^r, general alpha only
     // used only once the sweep is over: they live in the key-tile ring
     static_assert(2 * MR * MAX_W * 4 + MR * 4 + 96 <= NBUF * KT::BYTES, "post-sweep arrays must fit in the ring");
     uint32_t* const wm = (uint32_t*)kring;                        // working mask (tiles above tau_0)
@@ -530,9 +537,6 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 
     Owned<E, D, QB> qf;
     load_owned<E, D, QB>(qf, Qh, active ? qw0 : 0, lane);
     for (int i = tid; i < HIST_WORDS; i += THREADS) hist[i] = 0u;
-    if constexpr (AM == ALPHA_GEN) {
-        if (tid < SLOTS) pw[tid] = tid == 0 ? 0.f : pow_r<AM>((float)tid * (1.f / NB), r);
-    }
 
     // this lane's lists (per-lane 64-bit addresses: a scalar base would have to be fetched from
     // spilled scalar registers at every append)
@@ -555,7 +559,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 
     // (with one row per lane, both lanes solve the same), then the two lanes of a row swap.  Returns
     // per row block tau_0 = max(tau_h, max - 1) less the fp32 slack, and the bracket's upper end.
     // (coarse: while the sweep runs only a lower bound is wanted; for general alpha, whose exact
-    // solve costs hundreds of power functions, the best bin edge then stands in for the root)
+    // solve takes power functions per bin, the closed-form bound then stands in for the root)
     auto histogram_bound = [&](float (&lo)[QB], float (&up)[QB], bool coarse) {
         lds_settle();
         const int sq = (QB == 2) ? h : 0;
@@ -566,7 +570,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 
         const float origin = (float)a_lo * hb;                        // left edge of the window
         float tau_h;
         if (AM == ALPHA_GEN && coarse)
-            tau_h = histogram_edge_bound<SLOTS, CB>((const uint32_t*)hrow, a_lo & (SLOTS - 1), hshift(sq), hb, pw) + origin;
+            tau_h = histogram_lower_bound<SLOTS, CB>((const uint32_t*)hrow, a_lo & (SLOTS - 1), hshift(sq), hb, r) + origin;
         else
             tau_h = solve_histogram<AM, SLOTS, CB>((const uint32_t*)hrow, a_lo & (SLOTS - 1), hshift(sq), hb, r) + origin;
         const float slack = 1e-6f + 2.5e-7f * fabsf(origin);          // fp32 rounding of bins and closed form

@@ -12,13 +12,13 @@ namespace ea {
 constexpr int QB = 1;        // 32*QB owned rows per wave
 // waves per work-group (NW) and LDS buffer sets (NBUF) per kernel; a group owns 32*QB*NW rows
 constexpr int NW_TAU = 4, NBUF_TAU = 2, QB_TAU = 2;
-// list-based threshold kernel: 8 waves (512 rows with two rows per lane), one group per CU, a ring
-// of 4 key tiles so that a tile has three tile times to arrive
-constexpr int NW_TAUL = 4, NBUF_TAUL = 3;
-// 16-bit inputs, alpha 1.5 or 2: the list kernel runs as 8 waves x 32 rows with the histograms of
-// two waves sharing words (four waves per SIMD: 3.3 / 2.0 / 1.7 / 1.6 -> 3.2 / 1.7 / 1.5 / 1.5 ms over
-// the benchmark's sigma sweep against 4 waves x 64 rows at two per SIMD)
-constexpr bool TAUL_PAIRED = true;
+// list-based threshold kernel: one row per lane, two tile buffers.  16-bit inputs: 8 waves, the
+// histograms of two waves sharing words (256 rows, four waves per SIMD; against 4 waves x 64 rows at two per
+// SIMD 3.3 / 2.0 / 1.7 / 1.6 -> 3.2 / 1.7 / 1.5 / 1.5 ms over the benchmark's sigma sweep, and 1.20 -> 0.99 ms at
+// alpha = 1.25, 32 heads of 8192 tokens, d = 64).  fp32 inputs (tiles and operands twice as large): 4 waves.
+constexpr int NBUF_TAUL = 2;
+template <class E> constexpr int NW_TAUL = E::EPL == 8 ? 8 : 4;
+template <class E> constexpr int PAIR_TAUL = E::EPL == 8 ? 1 : 0;
 constexpr int NW_OUT = 4, NBUF_OUT = 2;
 constexpr int NW_DQ = 2, NBUF_DQ = 2;
 constexpr int NW_DKDV = 2, NBUF_DKDV = 2;
@@ -79,17 +79,9 @@ struct Ops {
             ScopedKernelTime t(EA_TIMER_TAU, s);
             // one dense sweep that lists each row's candidate scores, then histogram, solve and
             // refinement on the lists
-            constexpr int QBL = (E::EPL == 8) ? QB_TAU : 1;
-            constexpr int NBL = (E::EPL == 8) ? NBUF_TAUL : 2;       // fp32 tiles are twice as large
-            static_assert((32 * QBL * NW_TAUL) % (32 * QB * NW_OUT) == 0, "an output group lies inside one row group of the list kernel");
-            p.grows = 32 * QBL * NW_TAUL;
-            if constexpr (E::EPL == 8 && TAUL_PAIRED && AM != ALPHA_GEN) {
-                // eight one-row waves, paired histograms, two tile buffers: four waves per SIMD
-                // (general alpha, with its table of powers and heavier solves, measured slower so)
-                p.grows = 32 * 8;
-                rc = launch(tau_list_kernel<E, D, 1, AM, NBINS, 8, 2, 1>, groups(p, 8, 1), 8 * 64, s, p);
-            } else
-            rc = launch(tau_list_kernel<E, D, QBL, AM, NBINS, NW_TAUL, NBL>, groups(p, NW_TAUL, QBL), NW_TAUL * 64, s, p);
+            static_assert((32 * NW_TAUL<E>) % (32 * QB * NW_OUT) == 0, "an output group lies inside one row group of the list kernel");
+            p.grows = 32 * NW_TAUL<E>;
+            rc = launch(tau_list_kernel<E, D, 1, AM, NBINS, NW_TAUL<E>, NBUF_TAUL, PAIR_TAUL<E>>, groups(p, NW_TAUL<E>, 1), NW_TAUL<E> * 64, s, p);
             if (rc) return rc;
             // sweep-based fallback for row blocks whose lists overflowed (exits at once elsewhere);
             // two rows per lane (packed 16-bit histogram counters) while a bin cannot overflow

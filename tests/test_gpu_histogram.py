@@ -193,3 +193,11 @@ def test_right_edge_binning_gives_a_sparser_approximation(ea, dtype, d, alpha, s
     print("  right edge:", dict(tau_above=float((t - ts).mean()), row_sum_mean=float(sums.mean()), row_sum_min=float(sums.min()),
                                dO_vs_exact=float(np.abs(parity.to_np64(O) - ref["O"]).max()),
                                tiles=int(got.sum()), tiles_exact=int(exact.sum())), flush=True)
+
+
+@pytest.mark.parametrize("dtype,d,alpha,scale,causal", [("bf16", 64, 1.1, 2.0, True), ("bf16", 128, 1.4, 1.0, False), ("bf16", 64, 1.6, 1.0, True),
+                                                        ("bf16", 128, 1.75, 3.0, True), ("f32", 64, 1.75, 1.0, False), ("bf16", 64, 2.5, 2.0, True)])
+def test_histogram_root_from_each_closed_form_bound(ea, dtype, d, alpha, scale, causal):
+    # the scan's closed-form bound by 1/(alpha-1): power means from 2 on, the square below, the plain sum below 1
+    # - the refined bound while the sweep runs, and where the Newton solve of the full histogram starts
+    test_histogram_root_brackets_the_threshold(ea, dtype, d, alpha, "gauss", scale, causal)
