@@ -224,7 +224,7 @@ __global__ __launch_bounds__(1024) void decode_entmax_kernel(DecodeParams p) {
     const bool over = total > CAP;          // then every evaluation streams the kept logits instead
     const int nc = min(total, CAP);
     if (tid == 0) {
-        const float tau_h = solve_histogram<AM, SLOTS, 32>(hist, 0, 0, hb, r) + lower;
+        const float tau_h = solve_histogram<AM, SLOTS, 32, false, true>(hist, 0, 0, hb, r) + lower;
         const float slack = 1e-6f + 2.5e-7f * fabsf(lower);
         bc[0] = fmaxf(tau_h - slack, lower);
         bc[1] = tau_h + hb + slack;
