@@ -7,12 +7,11 @@ namespace ea {
 
 constexpr int MAX_T = 2048;     // N <= 131072
 constexpr int MAX_W = 64;       // mask words per row
-// A row group's output comes from the gather kernel when its candidate lists average at most
-// GATHER_LIST_MAX entries per row (480 of the 512 they hold) and its supports at most GATHER_SUP_MAX keys per row: the
-// gather takes about 0.02 ns per entry, the matrix kernel 3.2 ns per marked tile at head dim 128 (8192 tokens,
-// sigma = 0.8, about 60 keys per row: gather 105 us, matrix 292 us; near 200 keys per row, alpha = 1.25 at
+// A row group's output comes from the gather kernel when its supports average at most GATHER_SUP_MAX keys per
+// row: the gather takes about 0.02 ns per entry, the matrix kernel 3.2 ns per marked tile at head dim 128 (8192
+// tokens, sigma = 0.8, about 60 keys per row: gather 105 us, matrix 292 us; near 200 keys per row, alpha = 1.25 at
 // sigma = 1, the two are level: 343 and 315 us).
-constexpr int GATHER_LIST_MAX = 480, GATHER_SUP_MAX = 96;
+constexpr int GATHER_SUP_MAX = 96;
 // Query tiles per part of a mask column in dkdv_kernel from 65536 tokens on (half that below;
 // every part pays the column walk, the owned K, V fragments and atomic adds of its results, and an
 // empty part a work-group's launch: parts of 32 or 16 tiles measured slower at every length).

@@ -573,7 +573,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 
     uint32_t* const wm = (uint32_t*)kring;                        // working mask (tiles above tau_0)
     uint32_t* const fmk = (uint32_t*)(kring + MR * MAX_W * 4);    // final mask (tiles of the support)
     int* const over_s = (int*)(kring + 2 * MR * MAX_W * 4);
-    int* const gsum = (int*)(kring + 2 * MR * MAX_W * 4 + ((MR * 4 + 7) & ~7));   // list entries, support size, obstacles
+    int* const gsum = (int*)(kring + 2 * MR * MAX_W * 4 + ((MR * 4 + 7) & ~7));   // [1] support size, [2] obstacles
     unsigned long long* const blk_stats = (unsigned long long*)(kring + 2 * MR * MAX_W * 4 + ((MR * 4 + 7) & ~7) + 16);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -786,7 +786,10 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) nmax = max(nmax, __shfl_xor(nmax, off));
         // refinement (Sec. 3.2): evaluations of f, f', f'' over the listed scores; each lane walks
-        // its own lists, sixteen entries per row block at a time with all loads in flight together
+        // its own lists, sixteen entries per row block at a time with all loads in flight together.
+        // The first evaluation, at tau_0 <= tau* (every later threshold lies above it), moves the entries it
+        // finds above the threshold to the front of their list: those that follow read a fraction of it
+        // (steps: sigma = 1, 16384 tokens, lists of about 120 entries, 4886 -> 4780 us; fp32, 256 tokens, 123 -> 113).
         SecantPrev prev[QB];
         // (alpha > 2: a row with a score within the tolerance of its root ends up bisecting, since f
         // rises vertically there; the sweeps over the lists are cheap, those of the output kernel
@@ -795,8 +798,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 
         for (int sweep = 0; sweep < nsweeps; ++sweep) {
             float F[QB], G[QB], Hs[QB];
             uint32_t lastj[QB];
+            int front[QB];
 #pragma unroll
-            for (int qb = 0; qb < QB; ++qb) { F[qb] = G[qb] = Hs[qb] = 0.f; lastj[qb] = 0xffffffffu; }
+            for (int qb = 0; qb < QB; ++qb) { F[qb] = G[qb] = Hs[qb] = 0.f; lastj[qb] = 0xffffffffu; front[qb] = 0; }
             for (int i0 = 0; i0 < nmax; i0 += 16) {
                 uint4 e[QB][8];
 #pragma unroll
@@ -806,13 +810,15 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 
                         e[qb][u] = make_uint4(0u, 0u, 0u, 0u);
                         if (i0 + 2 * u < mycnt[qb]) e[qb][u] = *(const uint4*)(lptr[qb] + (i0 + 2 * u) * 8);
                     }
+                // (all sixteen are in registers before the first is overwritten; front <= i0 + u)
 #pragma unroll
                 for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
                     for (int u = 0; u < 16; ++u) {
-                        const uint32_t bits = (u & 1) ? e[qb][u >> 1].z : e[qb][u >> 1].x;
-                        const uint32_t j = ((u & 1) ? e[qb][u >> 1].w : e[qb][u >> 1].y) >> 6;      // key tile
-                        const float y = fmaf(c, __uint_as_float(bits), -thr[qb]);
+                        uint2 ent;
+                        ent.x = (u & 1) ? e[qb][u >> 1].z : e[qb][u >> 1].x;
+                        ent.y = (u & 1) ? e[qb][u >> 1].w : e[qb][u >> 1].y;
+                        const float y = fmaf(c, __uint_as_float(ent.x), -thr[qb]);
                         if (i0 + u < mycnt[qb] && y > 0.f) {
                             if constexpr (AM == ALPHA_15) { F[qb] = fmaf(y, y, F[qb]); G[qb] += y; Hs[qb] += 1.f; }
                             else if constexpr (AM == ALPHA_20) { F[qb] += y; G[qb] += 1.f; }
@@ -820,10 +826,21 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 
                                 const float p2 = pow_r2<AM>(y, r);
                                 Hs[qb] += p2; G[qb] = fmaf(p2, y, G[qb]); F[qb] = fmaf(p2 * y, y, F[qb]);
                             }
-                            // first evaluation, at tau_0 <= tau*: its tiles are the working mask
-                            if (sweep == 0 && j != lastj[qb]) { atomicOr(&wm[myrow * W + (j >> 5)], 1u << (j & 31)); lastj[qb] = j; }
+                            if (sweep == 0) {
+                                *(uint2*)(lptr[qb] + 8 * front[qb]) = ent;
+                                ++front[qb];
+                                const uint32_t j = ent.y >> 6;            // its tiles are the working mask
+                                if (j != lastj[qb]) { atomicOr(&wm[myrow * W + (j >> 5)], 1u << (j & 31)); lastj[qb] = j; }
+                            }
                         }
                     }
+            }
+            if (sweep == 0) {
+                nmax = 0;
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) { mycnt[qb] = front[qb]; nmax = max(nmax, front[qb]); }
+#pragma unroll
+                for (int off = 32; off >= 1; off >>= 1) nmax = max(nmax, __shfl_xor(nmax, off));
             }
             int pending = 0;
 #pragma unroll
@@ -859,21 +876,17 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 
     if (__any(any_over) && lane == 0) atomicOr(&over_s[myrow], 1);
 
     // ---- sparse row groups: the support itself, for the gather kernel ---------------------------
-    // Where the lists are short, the entries above the final tau - the row's support, a handful of
-    // keys - are moved to the front of their list, with their key indices; gather_out_kernel then
+    // The entries above the final tau - the row's support, a handful of keys - are moved to the front of their list, with their key indices; gather_out_kernel then
     // forms O from those rows of V alone, and the block-sparse output kernel skips the row group.
     {
-        int len = 0, obstacle = any_over;
+        int obstacle = any_over;
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb) { len += mycnt[qb]; obstacle |= !done[qb]; }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) len += __shfl_xor(len, off);
-        if (lane == 0) atomicAdd(&gsum[0], len);
+        for (int qb = 0; qb < QB; ++qb) obstacle |= !done[qb];
         if (__any(obstacle) && lane == 0) atomicOr(&gsum[2], 1);
     }
     __syncthreads();
     const int nrows = min(BR, N - (int)q0);
-    const bool sparse = p.gflag && gsum[2] == 0 && gsum[0] <= GATHER_LIST_MAX * nrows;
+    const bool sparse = p.gflag && gsum[2] == 0;
     if (sparse) {
         int nsup = 0;
         if (active) {
