@@ -55,35 +55,34 @@ EA_DEV float histogram_moment_root(const uint32_t* H, int rot, int shift, float 
         if constexpr (MOM == 2) return d < (I)(NB * NB);
         return (float)d * (h * h) < __builtin_amdgcn_exp2f(q * __builtin_amdgcn_logf((float)S0));
     };
-    I c0[NCH], c1[NCH], c2[NCH];
     const int half = PAIRED ? (int)(__lane_id() >> 5) : 0;
-#pragma unroll
-    for (int m = 0; m < NCH; m += PAIRED ? 2 : 1) {
-        I a0 = 0, a1 = 0, a2 = 0;                      // (distances inside the chunk)
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            const I c = (I)histogram_count<BITS>(H, (rot + NB - 8 * (m + half) - b) & (SLOTS - 1), shift);
-            a0 += c; a1 += (I)b * c; a2 += (I)(b * b) * c;
-        }
-        const int t0 = 8 * (m + half);
-        a2 += (I)t0 * (2 * a1 + (I)t0 * a0);
-        a1 += (I)t0 * a0;
-        if constexpr (PAIRED) {
-            auto both = [](int v, I& lo, I& hi) {
-                const auto x = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
-                lo = (I)(int)x[0]; hi = (I)(int)x[1];
-            };
-            both((int)a0, c0[m], c0[m + 1]); both((int)a1, c1[m], c1[m + 1]); both((int)a2, c2[m], c2[m + 1]);
-        } else { c0[m] = a0; c1[m] = a1; c2[m] = a2; }
-    }
     I S0 = 0, S1 = 0, S2 = 0, B0 = 0, B1 = 0, B2 = 0;
     int full = 0;                                      // chunks wholly inside the set
     bool grows = true;
-#pragma unroll
-    for (int m = 0; m < NCH; ++m) {
-        S0 += c0[m]; S1 += c1[m]; S2 += c2[m];
+    auto try_chunk = [&](int m, I a0, I a1, I a2) {
+        S0 += a0; S1 += a1; S2 += a2;
         grows = grows && (S0 == 0 || inside(S0, S1, S2, 8 * m + 7));
         if (grows) { B0 = S0; B1 = S1; B2 = S2; full = m + 1; }
+    };
+#pragma unroll 1
+    for (int m = 0; m < NCH; m += PAIRED ? 2 : 1) {    // (unrolled, the loads of all chunks cost registers that the caller's score tile holds)
+        const int t0 = 8 * (m + half);
+        I a0 = 0, a1 = 0, a2 = 0;                      // (distances inside the chunk at first)
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            const I c = (I)histogram_count<BITS>(H, (rot + NB - t0 - b) & (SLOTS - 1), shift);
+            a0 += c; a1 += (I)b * c; a2 += (I)(b * b) * c;
+        }
+        a2 += (I)t0 * (2 * a1 + (I)t0 * a0);
+        a1 += (I)t0 * a0;
+        if constexpr (PAIRED) {
+            const auto x0 = __builtin_amdgcn_permlane32_swap((uint32_t)a0, (uint32_t)a0, false, false);
+            const auto x1 = __builtin_amdgcn_permlane32_swap((uint32_t)a1, (uint32_t)a1, false, false);
+            const auto x2 = __builtin_amdgcn_permlane32_swap((uint32_t)a2, (uint32_t)a2, false, false);
+            try_chunk(m, (int)x0[0], (int)x1[0], (int)x2[0]);
+            try_chunk(m + 1, (int)x0[1], (int)x1[1], (int)x2[1]);
+        } else try_chunk(m, a0, a1, a2);
+        if (!__any(grows)) break;
     }
     S0 = B0; S1 = B1; S2 = B2;
 #pragma unroll
@@ -538,14 +537,20 @@ __global__ __launch_bounds__(NW * 64) void tau_kernel(Params p) {
 // Phases 1-3 of Alg. 1 from ONE dense sweep.  By Eq. 5, tau* >= max - 1 (in units of (alpha-1) s),
 // and both the maximum and tau* over a prefix of the keys are at most their values over all keys,
 // so a score that lies below a lower bound of the prefix's threshold when it is met can never lie
-// above the final one.  Every other score - a handful per row when attention is sparse - is
-// (a) counted in the row's LDS histogram (Eq. 6-8; absolute bin grid with a sliding window, as in
-// tau_kernel) and (b) appended, with its key tile, to a list private to the lane that computed it
-// (each lane sees 16 of every 32 keys of its row, so a row has two lists; no atomics, no ordering
-// between lanes).  The lower bound starts as (running maximum - 1); each time a list has grown by
-// a fixed number of entries the histogram is solved (Eq. 9) and its root tau_h, a lower bound of the
-// prefix's tau* by Prop. 1, becomes the new bound.  Scores that were skipped lie below the bound and
+// above the final one.  Every other score - a handful per row when attention is sparse - is appended, with
+// its key, to a list private to the lane that computed it (each lane sees 16 of every 32 keys of its row, so
+// a row has two lists; no atomics, no ordering between lanes).  The lower bound starts as (running maximum - 1);
+// each time a list has grown by a fixed number of entries, the row's LDS histogram of the listed scores (Eq. 6-8;
+// absolute bin grid with a sliding window, as in tau_kernel) is solved (Eq. 9), and its root tau_h, a lower
+// bound of the prefix's tau* by Prop. 1, becomes the new bound.  Scores that were skipped lie below the bound and
 // contribute nothing to f at or above it, so f there, and with it Prop. 1, is that of all scores.
+// The histogram is made from the lists when it is first wanted, by a wave's lanes side by side, and kept up
+// entry by entry from then on (or from the start, where the first tile shows that the lists will be long): the
+// work per entry is done for one or two lanes at a time, and moving the window with every new maximum took
+// a third of the vector instructions of sparse rows.  Bound: vector issue (about 110 vector instructions per
+// tile and wave at sigma = 4 beside 16 MFMAs, 380 at sigma = 1, before the histogram was put off and the work
+// per entry cut from 14 instructions to 9).  Kernel, d = 128, 16384 tokens, sigma = 3 / 1: 1230 -> 1070 / 2302 -> 2187 us;
+// alpha = 2, 8192 tokens, d = 64: 378 -> 297 us; 65536 tokens, planted keys: 3767 -> 3440 us.
 // After the sweep the lists hold a superset of the row's support as exact fp32 scores, and the
 // rest happens on them: the refinement iterations of Sec. 3.2 from tau_0 = tau_h, each an
 // evaluation of f, f', f'' over the listed true scores instead of another sweep of Q K^T.  The key
@@ -558,12 +563,18 @@ __global__ __launch_bounds__(NW * 64) void tau_kernel(Params p) {
 // four and, with half the accumulator and operand registers, four waves fit a SIMD.
 template <class E, int D, int QB, int AM, int NB, int NW, int NBUF, int PAIR = 0>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 4 : 1))) void tau_list_kernel(Params p) {
-    static_assert(!PAIR || (QB == 1 && NW % 2 == 0), "paired histograms: one row per lane, an even number of waves");
+    static_assert(QB == 1 && (!PAIR || NW % 2 == 0), "one row per lane; paired histograms: an even number of waves");
     using SM = TauSmem<E, D, QB, NB, NW, NBUF>;
     using KT = RowTile<E, D>;
     using elem = typename E::elem;
     constexpr int THREADS = NW * 64, BR = SM::BR, MR = SM::MR, SLOTS = SM::SLOTS;
-    constexpr int GROW = 24;              // list growth (entries per lane) between two histogram solves
+    // list growth (entries per lane) between two histogram solves (steps with 16 / 24 / 32 / 48: 4096 tokens, d = 64,
+    // 833 / 826 / 812 / 830 us; 16384 tokens, sigma = 1, 4631 / 4620 / 4615 / 4700 us)
+    constexpr int GROW = 32;
+    // groups of eight scores of a wave's first tile (of 256) with a candidate from which its entries are counted
+    // at once.  Most waves of sparse rows never need the histogram while they sweep: 64 / 96 / 112 / 128 give
+    // 3136 tokens, sigma = 2: 170 / 157 / 146 / 145 us; 4096 tokens, sigma = 1.5: 826 / 828 / 829 / 843 us.
+    constexpr int FIRST_TILE_BUSY = 112;
     __shared__ __align__(1024) char kring[NBUF * KT::BYTES];
     constexpr int HIST_WORDS = PAIR ? SM::HIST_WORDS / 2 : SM::HIST_WORDS;
     constexpr int CB = PAIR ? 16 : SM::CBITS;            // bits per counter
@@ -596,153 +607,165 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 
     load_owned<E, D, QB>(qf, Qh, active ? qw0 : 0, lane);
     for (int i = tid; i < HIST_WORDS; i += THREADS) hist[i] = 0u;
 
-    // this lane's lists (per-lane 64-bit addresses: a scalar base would have to be fetched from
-    // spilled scalar registers at every append)
+    // this lane's list: byte offsets from the head's lists
     char* const lists_h = (char*)p.lists + (size_t)bh * N * (2 * LIST_CAP * 8);
-    char* lptr[QB];
-    int cnt[QB], trig[QB], a_top[QB], bottom4[QB];
-    float run[QB], lowraw[QB], k4[QB];
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        lptr[qb] = lists_h + (size_t)(((active ? qw0 : 0) + 32 * qb + n) * 2 + h) * (size_t)(LIST_CAP * 8);
-        cnt[qb] = 0; trig[qb] = GROW;
-        run[qb] = -INFINITY; lowraw[qb] = -3.0e38f;
-        k4[qb] = 0.f; bottom4[qb] = 0; a_top[qb] = INT_MIN;
-    }
+    const uint32_t list0 = (uint32_t)(((active ? (int)qw0 : 0) + n) * 2 + h) * (uint32_t)(LIST_CAP * 8);
+    char* const lptr = lists_h + list0;
+    int cnt = 0, trig = GROW, a_top = INT_MIN;
+    float run = -INFINITY, lowraw = -3.0e38f;
     const int hwave = PAIR ? (wave >> 1) : wave;         // whose buffer, and which half of its words
-    auto hshift = [&](int qb) { return PAIR ? 16 * (wave & 1) : (CB * qb & 31); };
-    char* const hrow = (char*)(hist + (hwave * 32 + n) * SLOTS);
+    const int hshift = PAIR ? 16 * (wave & 1) : 0;
+    uint32_t one;                                        // (one count, in a vector register: the LDS addition takes no scalar)
+    asm("v_mov_b32 %0, %1" : "=v"(one) : "s"(1u << hshift));
+    uint32_t* const hrow = hist + (hwave * 32 + n) * SLOTS;
+    const uint32_t hrow_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const uint32_t*)hrow;
+    const float inv_c = 1.f / c, cb = c * NB, c4 = 4.f * cb;
+    float k4 = 0.f, top_raw = -INFINITY;
+    int bottom4 = 0;
+    bool counting = false;                               // the same for all lanes: entries are counted as they are listed
 
-    // Root of the row's histogram (Eq. 9) as it stands: lane (n, h) solves row block qb = h of row n
-    // (with one row per lane, both lanes solve the same), then the two lanes of a row swap.  Returns
-    // per row block tau_0 = max(tau_h, max - 1) less the fp32 slack, and the bracket's upper end.
+    // Root of the row's histogram (Eq. 9) as it stands (both lanes of a row hold the same): tau_0 =
+    // max(tau_h, max - 1) less the fp32 slack, and the bracket's upper end.
     // (coarse: while the sweep runs only a lower bound is wanted; for general alpha, whose exact
     // solve takes power functions per bin, the closed-form bound then stands in for the root)
-    auto histogram_bound = [&](float (&lo)[QB], float (&up)[QB], bool coarse) {
+    auto histogram_bound = [&](float& lo, float& up, bool coarse) {
         lds_settle();
-        const int sq = (QB == 2) ? h : 0;
-        int top = a_top[0];
-        float mx = run[0];
-        if constexpr (QB == 2) { if (h) { top = a_top[1]; mx = run[1]; } }
-        const int a_lo = top == INT_MIN ? 0 : top - (SLOTS - 1);
+        const int a_lo = a_top == INT_MIN ? 0 : a_top - (SLOTS - 1);
         const float origin = (float)a_lo * hb;                        // left edge of the window
         float tau_h;
         if (AM == ALPHA_GEN && coarse)
-            tau_h = histogram_lower_bound<SLOTS, CB, QB == 1>((const uint32_t*)hrow, a_lo & (SLOTS - 1), hshift(sq), hb, r) + origin;
+            tau_h = histogram_lower_bound<SLOTS, CB, true>(hrow, a_lo & (SLOTS - 1), hshift, hb, r) + origin;
         else
-            tau_h = solve_histogram<AM, SLOTS, CB, QB == 1>((const uint32_t*)hrow, a_lo & (SLOTS - 1), hshift(sq), hb, r) + origin;
+            tau_h = solve_histogram<AM, SLOTS, CB, true>(hrow, a_lo & (SLOTS - 1), hshift, hb, r) + origin;
         const float slack = 1e-6f + 2.5e-7f * fabsf(origin);          // fp32 rounding of bins and closed form
-        const float my_lo = fmaxf(tau_h - slack, fmaf(c, mx, -1.f)), my_up = tau_h + hb + slack;
-        const float o_lo = xhalf_other(my_lo, h), o_up = xhalf_other(my_up, h);
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-            const bool mine = (h == (QB == 2 ? qb : 0));
-            lo[qb] = mine ? my_lo : o_lo;
-            up[qb] = mine ? my_up : o_up;
-        }
+        lo = fmaxf(tau_h - slack, fmaf(c, run, -1.f));
+        up = tau_h + hb + slack;
     };
 
-    f32x16 C[2][QB];
+    // The window of live bins follows the running maximum (see tau_kernel).  Bins below the bound are of no
+    // use, so the window is moved up by as many bins more as the bound leaves free at its bottom: most
+    // of the maxima that follow then fall inside it, and slots are cleared a few times per row only.
+    auto move_window = [&] {
+        int first = 0, last = -1;                       // bins to clear: first..last (none)
+        if (run > top_raw) {
+            int nt = (int)floorf(fminf(fmaxf(cb * run, -1e9f), 1e9f));
+            const int spare = (int)floorf(fminf(fmaxf(cb * lowraw, -1e9f), 1e9f)) - 1 - (nt - (SLOTS - 1));
+            nt += min(max(spare, 0), SLOTS / 2);
+            int a_lo = nt - (SLOTS - 1), rot = a_lo & (SLOTS - 1);
+            float kk = 4.f * (float)(rot - a_lo);
+            // the maximum itself must land in the window's top slot, not wrap past it
+            if ((int)fmaf(c4, run, kk) >= 4 * rot + 4 * SLOTS) {
+                nt += 1; a_lo += 1; rot = a_lo & (SLOTS - 1); kk = 4.f * (float)(rot - a_lo);
+            }
+            if (a_top != INT_MIN) { first = max(a_top, nt - SLOTS) + 1; last = nt; }
+            a_top = nt; k4 = kk; bottom4 = 4 * rot;
+            // scores up to here lie in the window for certain (less than half a bin from its top edge)
+            top_raw = fmaxf(run, ((float)nt + 0.5f) * (hb * inv_c));
+        }
+        // the whole wave clears the slots of one rising row at a time: lane i takes slot i
+        unsigned long long todo = __ballot(h == 0 && last >= first);
+        while (todo) {
+            const int src = __ffsll((long long)todo) - 1;
+            todo &= todo - 1;
+            const int f0 = __builtin_amdgcn_readlane(first, src);
+            const int ncl = __builtin_amdgcn_readlane(last - first, src);
+            if (((lane - f0) & (SLOTS - 1)) <= ncl) {
+                uint32_t* word = hist + (hwave * 32 + src) * SLOTS + lane;
+                if constexpr (!PAIR) *word = 0u;
+                else lds_and_b32(word, hshift == 0 ? 0xffff0000u : 0x0000ffffu);
+            }
+        }
+    };
+    // Histogram of what the lists hold so far
+    auto count_lists = [&] {
+        move_window();
+        int nmax = min(cnt, LIST_CAP);
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) nmax = max(nmax, __shfl_xor(nmax, off));
+        wait_loads();                                   // this wave's stores have completed
+        for (int i0 = 0; i0 < nmax; i0 += 16) {
+            uint4 e[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                e[u] = make_uint4(0u, 0u, 0u, 0u);
+                if (i0 + 2 * u < cnt) e[u] = *(const uint4*)(lptr + (i0 + 2 * u) * 8);
+            }
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                const float sc = __uint_as_float((u & 1) ? e[u >> 1].z : e[u >> 1].x);
+                const int rel = (int)fmaf(c4, sc, k4);
+                // (an entry further than one unit below the maximum is below the window, and of no use)
+                if (i0 + u < min(cnt, LIST_CAP) && rel >= bottom4) lds_add_at(hrow_lds + (rel & (4 * SLOTS - 4)), one);
+            }
+        }
+        counting = true;
+    };
+
+    f32x16 C[2][1];
     unsigned long long ntile_done = 0;
-    const float inv_c = 1.f / c, cb = c * NB, c4 = 4.f * cb;
     auto sweep_tile = [&](int j, const char* buf) {
             if (j >= wjt) return;
-            stage1<E, D, QB, EA_FENCE, PAIR ? 0 : 8>(C, buf, qf, lane);
-            if (p.causal && (long)j * 64 + 63 > qw0) causal_hide<QB, true>(C, j * 64, (int)qw0, lane);
+            stage1<E, D, 1, EA_FENCE, PAIR ? 0 : 8>(C, buf, qf, lane);
+            if (p.causal && (long)j * 64 + 63 > qw0) causal_hide<1, true>(C, j * 64, (int)qw0, lane);
             ++ntile_done;
-            // per row block: maxima of the four groups of 8 registers, of the lane, of the row
-            float gm[QB][4], lm[QB], tm[QB];
+            // maxima of the four groups of 8 registers, of the lane, of the row
+            float gm[4];
 #pragma unroll
-            for (int qb = 0; qb < QB; ++qb) {
+            for (int g = 0; g < 4; ++g) gm[g] = max8_raw(C[g >> 1][0], 8 * (g & 1));
+            const float lm = max2_raw(max3_raw(gm[0], gm[1], gm[2]), gm[3]);
+            const float tm = xhalf_max(lm);
+            run = max2_raw(run, tm);
+            if (j == 0) {
+                // many candidates in the first tile: lists will be long, count from the start
+                int busy = 0;
 #pragma unroll
-                for (int g = 0; g < 4; ++g) gm[qb][g] = max8_raw(C[g >> 1][qb], 8 * (g & 1));
-                lm[qb] = max2_raw(max3_raw(gm[qb][0], gm[qb][1], gm[qb][2]), gm[qb][3]);
+                for (int g = 0; g < 4; ++g) busy += __popcll(__ballot(gm[g] >= run - inv_c));
+                counting = busy >= FIRST_TILE_BUSY;
             }
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) tm[qb] = xhalf_max(lm[qb]);
-            bool rise_any = false;
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) rise_any |= tm[qb] > run[qb];
-            if (__any(rise_any)) {
-#pragma unroll
-                for (int qb = 0; qb < QB; ++qb) {
-                    // the window of live bins follows the running maximum (see tau_kernel)
-                    const bool rise = tm[qb] > run[qb];
-                    int first = 0, last = -1;           // bins to clear: first..last (none)
-                    if (rise) {
-                        run[qb] = tm[qb];
-                        int nt = (int)floorf(fminf(fmaxf(cb * tm[qb], -1e9f), 1e9f));
-                        int a_lo = nt - (SLOTS - 1), rot = a_lo & (SLOTS - 1);
-                        float kk = 4.f * (float)(rot - a_lo);
-                        // the maximum itself must land in the window's top slot, not wrap past it
-                        if ((int)fmaf(c4, tm[qb], kk) >= 4 * rot + 4 * SLOTS) {
-                            nt += 1; a_lo += 1; rot = a_lo & (SLOTS - 1); kk = 4.f * (float)(rot - a_lo);
-                        }
-                        if (a_top[qb] != INT_MIN) { first = max(a_top[qb], nt - SLOTS) + 1; last = nt; }
-                        a_top[qb] = nt; k4[qb] = kk; bottom4[qb] = 4 * rot;
-                    }
-                    // the whole wave clears the slots of one rising row at a time: lane i takes slot i
-                    unsigned long long todo = __ballot(h == 0 && last >= first);
-                    while (todo) {
-                        const int src = __ffsll((long long)todo) - 1;
-                        todo &= todo - 1;
-                        const int f0 = __builtin_amdgcn_readlane(first, src);
-                        const int ncl = __builtin_amdgcn_readlane(last - first, src);
-                        if (((lane - f0) & (SLOTS - 1)) <= ncl) {
-                            uint32_t* word = hist + (hwave * 32 + src) * SLOTS + lane;
-                            if constexpr (QB == 1 && !PAIR) *word = 0u;
-                            else lds_and_b32(word, hshift(qb) == 0 ? 0xffff0000u : 0x0000ffffu);
-                        }
-                    }
-                }
-            }
+            if (counting && __any(tm > top_raw)) move_window();
             // candidates: raw scores at or above the row's current lower bound; most tiles of a
             // sparse row block hold none, and leave here
-            float lowv[QB];
-            bool maybe = false;
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) {
-                lowv[qb] = fmaxf(run[qb] - inv_c, lowraw[qb]);
-                maybe |= lm[qb] >= lowv[qb];
-            }
-            if (!__any(maybe)) return;
-            bool grown = false;
+            const float low = max2_raw(run - inv_c, lowraw);
+            if (!__any(lm >= low)) return;
             const int key0 = j * 64 + 8 * h;
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) {
-                const float low = lowv[qb];
-                if (!__any(lm[qb] >= low)) continue;
+            uint32_t at = list0 + 8u * (uint32_t)min(cnt, LIST_CAP - 1);
+            const uint32_t at_last = list0 + 8u * (uint32_t)(LIST_CAP - 1);
+            auto scan = [&](auto count) {
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
-                    if (!__any(gm[qb][g] >= low)) continue;
+                    if (!__any(gm[g] >= low)) continue;
 #pragma unroll
                     for (int v = 0; v < 8; ++v) {
-                        const float sc = C[g >> 1][qb][8 * (g & 1) + v];
+                        const float sc = C[g >> 1][0][8 * (g & 1) + v];
+                        const unsigned long long hit = __ballot(sc >= low);
+                        if (!hit) continue;
+                        asm volatile("");               // (keeps the branch above a scalar one of its own: no lane mask to save and restore)
                         if (sc >= low) {
-                            // slot of the score's bin, times 4 (a score that rounding puts a hair
-                            // below the window goes to its lowest bin)
-                            const int rel = max((int)fmaf(c4, sc, k4[qb]), bottom4[qb]);
-                            lds_add_u32(hrow + (rel & (4 * SLOTS - 4)), 1u << hshift(qb));
+                            if constexpr (decltype(count)::value) {
+                                // slot of the score's bin, times 4 (a score that rounding puts a hair
+                                // below the window goes to its lowest bin)
+                                const int rel = max((int)fmaf(c4, sc, k4), bottom4);
+                                lds_add_at(hrow_lds + (rel & (4 * SLOTS - 4)), one);
+                            }
                             // a full list keeps overwriting its last entry (its block is redone anyway)
                             uint2 ent;          // tile row of register v of group g: see causal_hide
                             ent.x = __float_as_uint(sc); ent.y = (uint32_t)(key0 + 32 * (g >> 1) + 16 * (g & 1) + v);
-                            *(uint2*)(lptr[qb] + 8u * (uint32_t)min(cnt[qb], LIST_CAP - 1)) = ent;
-                            ++cnt[qb];
+                            *(uint2*)(lists_h + at) = ent;
+                            at = min(at + 8u, at_last);
+                            ++cnt;
                         }
                     }
                 }
-                grown |= cnt[qb] >= trig[qb];
-            }
-            if (__any(grown)) {
+            };
+            if (counting) scan(std::true_type{}); else scan(std::false_type{});
+            if (__any(cnt >= trig)) {
                 // a better lower bound from the histogram so far
-                float lo[QB], up[QB];
+                if (!counting) count_lists();
+                float lo, up;
                 histogram_bound(lo, up, true);
-#pragma unroll
-                for (int qb = 0; qb < QB; ++qb) {
-                    const float braw = lo[qb] * inv_c;
-                    lowraw[qb] = braw - fabsf(braw) * 1e-6f;
-                    trig[qb] = cnt[qb] <= LIST_CAP ? cnt[qb] + GROW : INT_MAX;
-                }
+                const float braw = lo * inv_c;
+                lowraw = braw - fabsf(braw) * 1e-6f;
+                trig = cnt <= LIST_CAP ? cnt + GROW : INT_MAX;
             }
     };
     stream_tiles_ring<NBUF, KT::NINST / NW>(njt, kring, KT::BYTES,
@@ -765,7 +788,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 
     for (int qb = 0; qb < QB; ++qb) { thr[qb] = 0.f; iters[qb] = 0; done[qb] = 1; mycnt[qb] = 0; }
     if (active) {
         float blo[QB], bhi[QB];
-        histogram_bound(thr, bhi, false);
+        if (!counting) count_lists();
+        histogram_bound(thr[0], bhi[0], false);
         if (h == 0) {
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) {
@@ -777,8 +801,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 
         int nmax = 0;
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
-            any_over |= (cnt[qb] > LIST_CAP);
-            mycnt[qb] = min(cnt[qb], LIST_CAP);
+            any_over |= (cnt > LIST_CAP);
+            mycnt[qb] = min(cnt, LIST_CAP);
             nmax = max(nmax, mycnt[qb]);
             blo[qb] = thr[qb]; iters[qb] = 0; done[qb] = 0; f1_last[qb] = -1.f;
             if (p.right_edge) thr[qb] = bhi[qb];      // tau_h + h >= tau*: the right-edge root, taken as it is
@@ -808,7 +832,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 
 #pragma unroll
                     for (int u = 0; u < 8; ++u) {
                         e[qb][u] = make_uint4(0u, 0u, 0u, 0u);
-                        if (i0 + 2 * u < mycnt[qb]) e[qb][u] = *(const uint4*)(lptr[qb] + (i0 + 2 * u) * 8);
+                        if (i0 + 2 * u < mycnt[qb]) e[qb][u] = *(const uint4*)(lptr + (i0 + 2 * u) * 8);
                     }
                 // (all sixteen are in registers before the first is overwritten; front <= i0 + u)
 #pragma unroll
@@ -827,7 +851,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 
                                 Hs[qb] += p2; G[qb] = fmaf(p2, y, G[qb]); F[qb] = fmaf(p2 * y, y, F[qb]);
                             }
                             if (sweep == 0) {
-                                *(uint2*)(lptr[qb] + 8 * front[qb]) = ent;
+                                *(uint2*)(lptr + 8 * front[qb]) = ent;
                                 ++front[qb];
                                 const uint32_t j = ent.y >> 6;            // its tiles are the working mask
                                 if (j != lastj[qb]) { atomicOr(&wm[myrow * W + (j >> 5)], 1u << (j & 31)); lastj[qb] = j; }
@@ -899,7 +923,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 
 #pragma unroll
                     for (int u = 0; u < 8; ++u) {
                         e[u] = make_uint4(0u, 0u, 0u, 0u);
-                        if (i0 + 2 * u < mycnt[qb]) e[u] = *(const uint4*)(lptr[qb] + (i0 + 2 * u) * 8);
+                        if (i0 + 2 * u < mycnt[qb]) e[u] = *(const uint4*)(lptr + (i0 + 2 * u) * 8);
                     }
                     // (all sixteen are in registers before the first is overwritten; w <= i0 + u)
 #pragma unroll
@@ -908,7 +932,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 
                         ent.x = (u & 1) ? e[u >> 1].z : e[u >> 1].x;
                         ent.y = (u & 1) ? e[u >> 1].w : e[u >> 1].y;
                         if (i0 + u < mycnt[qb] && fmaf(c, __uint_as_float(ent.x), -thr[qb]) > 0.f) {
-                            *(uint2*)(lptr[qb] + 8 * w) = ent;
+                            *(uint2*)(lptr + 8 * w) = ent;
                             ++w;
                             const uint32_t j = ent.y >> 6;
                             if (j != lastj) { atomicOr(&fmk[myrow * W + (j >> 5)], 1u << (j & 31)); lastj = j; }

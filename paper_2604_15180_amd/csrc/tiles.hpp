@@ -175,6 +175,9 @@ EA_DEV void lds_add_u32(const void* p, uint32_t v) {
     const uint32_t addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
     asm volatile("ds_add_u32 %0, %1" : : "v"(addr), "v"(v) : "memory");
 }
+EA_DEV void lds_add_at(uint32_t addr, uint32_t v) {   // (LDS byte address at hand)
+    asm volatile("ds_add_u32 %0, %1" : : "v"(addr), "v"(v) : "memory");
+}
 EA_DEV void lds_and_b32(const void* p, uint32_t v) {
     const uint32_t addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
     asm volatile("ds_and_b32 %0, %1" : : "v"(addr), "v"(v) : "memory");
