@@ -201,3 +201,35 @@ def test_histogram_root_from_each_closed_form_bound(ea, dtype, d, alpha, scale, 
     # the scan's closed-form bound by 1/(alpha-1): power means from 2 on, the square below, the plain sum below 1
     # - the refined bound while the sweep runs, and where the Newton solve of the full histogram starts
     test_histogram_root_brackets_the_threshold(ea, dtype, d, alpha, "gauss", scale, causal)
+
+
+@pytest.mark.parametrize("dtype,d,alpha,causal", [("bf16", 64, 1.5, True), ("bf16", 128, 1.5, False), ("bf16", 64, 2.0, False),
+                                                  ("bf16", 128, 1.25, False), ("f32", 64, 1.5, True)])
+def test_histogram_of_rising_maxima(ea, dtype, d, alpha, causal):
+    # keys grow along the sequence, so the maximum of nearly every row rises with every tile and the window of
+    # bins keeps moving, with the bins kept spare above it taken up in between; queries grow from 32-row block to block,
+    # so that some waves count their lists' entries from the first tile, some once a list has grown, some only at the end
+    from oracle import entmax_oracle as eo
+    B, H, N = 1, 1, 1472
+    q, k, v, _ = workloads.gaussian_qkv(B, H, N, d, dtype, 1.0, seed=53)
+    block = torch.arange(N) // 32
+    q = (q.float() * torch.linspace(0.5, 3.5, 8)[block % 8][None, None, :, None]).to(q.dtype)
+    k = (k.float() * torch.linspace(0.6, 1.4, N)[None, None, :, None]).to(k.dtype)
+    ws = torch.empty(ea.entmax_attn_workspace_bytes(B, H, N, d, dtype, causal, False), dtype=torch.uint8, device="cuda")
+    O, tau, mask = ea.entmax_attn_fwd(q.cuda(), k.cuda(), v.cuda(), alpha, causal, workspace=ws)
+    tau0, upper = ea.entmax_attn_fwd_histogram_bounds(ws, B, H, N, d, dtype)
+    torch.cuda.synchronize()
+    Qn, Kn = parity.to_np64(q), parity.to_np64(k)
+    ref = eo.attn_fwd(Qn, Kn, parity.to_np64(v), alpha, causal, tile=64)
+    parity.check_forward(q, k, v, alpha, causal, O, tau, mask, ref=ref, label=f"rising maxima {dtype} {d} {alpha}")
+    t0, up, ts = parity.to_np64(tau0), parity.to_np64(upper), ref["tau"]
+    eps, nb = 3e-5 * (1.0 + np.abs(ts)), ea.entmax_attn_histogram_bins()
+    assert (t0 <= ts + eps).all() and (ts <= up + eps).all() and (up - t0 <= 1.0 / nb + 1e-4).all()
+    X = (alpha - 1.0) * (Qn[0, 0] @ Kn[0, 0].T) / np.sqrt(d)
+    want = np.empty(N)
+    for r_ in range(N):
+        th, m = grid_histogram_root(X[r_, : r_ + 1] if causal else X[r_], alpha, nb)
+        want[r_] = max(th, m - 1.0)
+    diff = np.abs(t0[0, 0] - want)
+    # a score that fp32 puts on the other side of a bin edge moves one count by one bin
+    assert (diff <= 1e-4 * (1.0 + np.abs(want))).mean() >= 0.995 and diff.max() <= 1.0 / nb + 1e-4
