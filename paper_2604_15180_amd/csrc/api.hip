@@ -87,7 +87,7 @@ Layout bwd_layout(int B, int H, int N, int d, int t) {
     L.lists = off; off += align256(BH * N * (size_t)(2 * BWD_LIST_CAP * 8));
     L.scnt = off; off += align256(BH * N * 2 * 4);
     L.gflag = off; off += align256(BH * ((size_t)N / 128 + 1) * 4);
-    L.kcnt = off; off += align256(BH * N * 4 + 8);               // and two counters: row groups on the matrix path, set mask bits
+    L.kcnt = off; off += align256(BH * N * 4 + 8);               // and a counter: row groups on the matrix path
     L.klist = off; off += align256(BH * N * (size_t)KEY_LIST_CAP * sizeof(KeyEntry));
     L.defer = off; off += align256(BH * N * 4);
     L.colcnt = off; off += align256(BH * T * 4);                 // query tiles per key tile's mask column (dkdv_kernel's parts)
@@ -328,7 +328,8 @@ int bwd_impl(const void* Q, const void* K, const void* V, const void* O, const v
     p.gflag = g_gather_enabled ? (int32_t*)(ws + L.gflag) : nullptr;
     p.kcnt = (int32_t*)(ws + L.kcnt);
     p.nplain = p.kcnt + (size_t)B * H * N;
-    p.nmarked = p.nplain + 1;
+    p.mask_parts = (int32_t*)(ws + L.delta);        // read before the first delta is written; B H N is at least MASK_PARTS
+    static_assert(MASK_PARTS <= TILE, "the partial sums fit where delta will be");
     p.klist = ws + L.klist;
     p.defer = (int32_t*)(ws + L.defer);
     p.colcnt = (int32_t*)(ws + L.colcnt);
@@ -346,8 +347,11 @@ int bwd_impl(const void* Q, const void* K, const void* V, const void* O, const v
             p.list_cap = LIST_CAP;
         }
     }
-    hipLaunchKernelGGL(zero_stats_kernel, dim3(1), dim3(256), 0, s, p.stats, EA_STATS_WORDS * EA_STATS_COPIES, p.scal);
-    EA_HIP(hipGetLastError());
+    // (otherwise bwd_begin_kernel clears the statistics)
+    if (rebuild || !p.gflag) {
+        hipLaunchKernelGGL(zero_stats_kernel, dim3(1), dim3(256), 0, s, p.stats, EA_STATS_WORDS * EA_STATS_COPIES, p.scal);
+        EA_HIP(hipGetLastError());
+    }
     if (per_head == 2) {
         p.hc_table = (const HeadConsts*)(ws + L.hc);
         if ((rc = fill_head_table(alpha_h, H, p.inv_sqrt_d, (HeadConsts*)(ws + L.hc), s))) return rc;

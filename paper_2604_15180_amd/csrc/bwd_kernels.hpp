@@ -713,6 +713,14 @@ __global__ __launch_bounds__(NW * 64) void dkdv_kernel(Params p) {
 // when its lists hold at most bwd_entries_per_tile entries per marked tile (and no list is full);
 // or BWD_ENTRIES_PER_ROW per row (and no list is full); the sweep is left early once the entries
 // so far run a quarter above that rate.
+// Set bits of the whole mask, from bwd_begin_kernel's partial sums (called by whole waves)
+EA_DEV long marked_tiles(const Params& p, int lane) {
+    static_assert(MASK_PARTS == 64, "one partial sum per lane");
+    int c = p.mask_parts[lane];
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) c += __shfl_xor(c, off);
+    return c;
+}
 template <class E, int D, int QB, int AM, int NW>
 __global__ __launch_bounds__(NW * 64) void bwd_list_kernel(Params p) {
     using elem = typename E::elem;
@@ -741,7 +749,7 @@ __global__ __launch_bounds__(NW * 64) void bwd_list_kernel(Params p) {
 
     // a mask with few marked tiles altogether: the matrix kernels are done before the gather
     // kernels' passes over dK, dV would be
-    if ((long)*p.nmarked < (long)BWD_MIN_TILES_PER_BLOCK * p.BH * T) {
+    if (marked_tiles(p, lane) < (long)BWD_MIN_TILES_PER_BLOCK * p.BH * T) {
         if (tid == 0) {
             p.gflag[(long)bh * ((N + BR - 1) / BR) + I] = 0;
             atomicAdd(p.nplain, 1);
@@ -881,7 +889,7 @@ __global__ __launch_bounds__(128) void bwd_decide_kernel(Params p) {
     int bh, I;
     map_block(blockIdx.x, p.BH, G, bh, I);
     const int fwd_grows = (int)p.fwd_scal[2];
-    bool gather = (long)*p.nmarked >= (long)BWD_MIN_TILES_PER_BLOCK * p.BH * T && fwd_grows > 0
+    bool gather = marked_tiles(p, tid & 63) >= (long)BWD_MIN_TILES_PER_BLOCK * p.BH * T && fwd_grows > 0
                   && p.fwd_gflag[(long)bh * ((N + fwd_grows - 1) / fwd_grows) + (I * BR) / fwd_grows] != 0;
     if (tid < 2) gsum[tid] = 0;
     __syncthreads();
@@ -1235,16 +1243,26 @@ __global__ __launch_bounds__(256) void bwd_cols_kernel(Params p) {
     L::store(dv, av, sub);
 }
 
-static __global__ void mask_popcount_kernel(const int32_t* mask, long nwords, int32_t* out) {
+// What the backward starts from, in one launch (three of them cost 4 - 5 us each): cleared key counters (and the
+// counter of plain row groups behind them), cleared statistics (stats null: they are cleared already), and the
+// set bits of the mask, a partial sum for each of the first MASK_PARTS blocks.
+static __global__ __launch_bounds__(256) void bwd_begin_kernel(int32_t* counters, long n, unsigned long long* stats, int nstats, unsigned int* scal,
+                                                               const int32_t* mask, long nwords, int32_t* mask_parts) {
+    __shared__ int part[4];
+    const long first = blockIdx.x * 256L + threadIdx.x, stride = (long)gridDim.x * 256;
+    for (long i = first; i < n; i += stride) counters[i] = 0;
+    if (stats) {
+        for (long i = first; i < nstats; i += stride) stats[i] = 0ull;
+        if (first < 4) scal[first] = 0u;
+    }
+    if (blockIdx.x >= MASK_PARTS) return;
     int c = 0;
-    for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < nwords; i += (long)gridDim.x * blockDim.x) c += __popc((uint32_t)mask[i]);
+    for (long i = first; i < nwords; i += MASK_PARTS * 256L) c += __popc((uint32_t)mask[i]);
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) c += __shfl_xor(c, off);
-    if ((threadIdx.x & 63) == 0 && c) atomicAdd(out, c);
-}
-
-static __global__ void zero_ints_kernel(int32_t* x, long n) {
-    for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) x[i] = 0;
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) mask_parts[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
 }
 
 }  // namespace ea

@@ -38,6 +38,8 @@ constexpr int BWD_ENTRIES_PER_ROW = 6, BWD_FEW_TILES = 40;
 // (8192 tokens, d = 64, block-structured inputs with 5 tiles per block: matrix 773, gather 650 us a step.)
 constexpr int BWD_MIN_TILES_PER_BLOCK = 2;
 
+constexpr int MASK_PARTS = 64;
+
 // An entry of a key's list: the query row and its dS and P there.
 struct KeyEntry { uint32_t row; float dS, pr; };
 
@@ -87,7 +89,7 @@ struct Params {
     const int32_t* fwd_gflag; const unsigned int* fwd_scal;   // (fwd_scal[2] = rows per row group of the forward's flags)
     int32_t* kcnt;        // backward [BH][N]: entries in each key's list
     int32_t* nplain;      // backward: number of row groups that stay with dq_kernel / dkdv_kernel
-    int32_t* nmarked;     // backward: set bits of the whole mask
+    int32_t* mask_parts;  // backward [MASK_PARTS]: set bits of the whole mask, partial sums
     int32_t* defer;       // backward [BH][N]: entries of the row left to bwd_hot_kernel
     void* klist;          // backward [BH][N][KEY_LIST_CAP] KeyEntry
     int32_t* oflag;       // [BH][T] 1 = some row of this 64-row block has more candidates than its lists hold

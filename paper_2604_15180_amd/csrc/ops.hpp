@@ -133,9 +133,8 @@ struct Ops {
         if (p.gflag) {
             ScopedKernelTime t(EA_TIMER_BWD_LIST, s);
             static_assert((32 * QBB * NW_BLIST) % (32 * QB * NW_DQ) == 0 && (32 * QBB * NW_BLIST) % 64 == 0, "a dQ group and a query tile lie inside one row group");
-            hipLaunchKernelGGL(zero_ints_kernel, dim3(256), dim3(256), 0, s, p.kcnt, (long)p.BH * p.N + 2);   // and nplain, nmarked, right behind
-            EA_HIP(hipGetLastError());
-            hipLaunchKernelGGL(mask_popcount_kernel, dim3(64), dim3(256), 0, s, p.mask, (long)p.BH * p.T * p.W, p.nmarked);
+            hipLaunchKernelGGL(bwd_begin_kernel, dim3(256), dim3(256), 0, s, p.kcnt, (long)p.BH * p.N + 1,      // (nplain is right behind)
+                               rebuild_mask ? nullptr : p.stats, STATS_WORDS * STATS_COPIES, p.scal, p.mask, (long)p.BH * p.T * p.W, p.mask_parts);
             EA_HIP(hipGetLastError());
             if (p.fwd_gflag) {
                 // the forward's lists were handed over: no sweep, only the decision per row group
