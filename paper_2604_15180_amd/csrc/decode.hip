@@ -35,6 +35,82 @@ struct DecodeParams {
     int max_iters;
 };
 
+// The histogram solve of fwd_kernels.hpp (histogram_moment_root, solve_histogram) by one whole wave for one
+// histogram of 64 bins from LDS: lane t holds the bin t below the top, the sums of every set of bins from the top are
+// one prefix sum, and an evaluation for general alpha is one power function and a sum over the lanes.  A
+// head has one histogram only; one thread walking its bins was a chain of 64 LDS reads and as many tests
+// (32 heads, 131072 keys: call 171.2 -> 167.5 us).
+// Counts go up to 2^22 (the keys of a head): S2 needs 64 bits.  Every lane returns the root.
+template <int AM>
+EA_DEV float wave_histogram_root(const uint32_t* hist, float h, float r) {
+    constexpr int NB = 63;
+    const int t = __lane_id();
+    const int cnt = (int)hist[NB - t];
+    int S0 = cnt, S1 = cnt * t;                        // (S1 <= 63 2^22)
+    long long S2 = (long long)cnt * (t * t);
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int a0 = __shfl_up(S0, off), a1 = __shfl_up(S1, off);
+        const long long a2 = __shfl_up(S2, off);
+        if (t >= off) { S0 += a0; S1 += a1; S2 += a2; }
+    }
+    const float q = 1.f - 2.f / r;
+    auto bound = [&](auto mom) {
+        constexpr int MOM = decltype(mom)::value;
+        const long long d1 = (long long)t * S0 - S1, d2 = S2 - 2ll * t * S1 + (long long)(t * t) * S0;
+        bool in;
+        if constexpr (MOM == 1) in = d1 < NB;
+        else if constexpr (MOM == 2) in = d2 < NB * NB;
+        else in = (float)d2 * (h * h) < __builtin_amdgcn_exp2f(q * __builtin_amdgcn_logf((float)S0));
+        const unsigned long long sets = __ballot(cnt > 0 && in);
+        if (!sets) return -h;
+        const int last = 63 - __clzll((long long)sets);
+        const int B0 = __shfl(S0, last), B1 = __shfl(S1, last);
+        const long long B2 = __shfl(S2, last);
+        const float n = (float)B0, inv = 1.f / n;
+        float t_root;
+        if constexpr (MOM == 1) t_root = (float)(B1 + NB) * inv;
+        else {
+            const int t0 = (int)((float)B1 * inv + 0.5f);
+            const float m1 = (float)(B1 - t0 * B0) * inv, m2 = (float)(B2 - 2ll * t0 * B1 + (long long)(t0 * t0) * B0) * inv;
+            const float target = MOM == 2 ? 1.f : __builtin_amdgcn_exp2f(q * __builtin_amdgcn_logf(n));
+            t_root = (float)t0 + (m1 + sqrtf(fmaxf(target * (float)(NB * NB) * inv - (m2 - m1 * m1), 0.f)));
+        }
+        return ((float)NB - t_root) * h;
+    };
+    if constexpr (AM == ALPHA_15) return bound(std::integral_constant<int, 2>{});
+    else if constexpr (AM == ALPHA_20) return bound(std::integral_constant<int, 1>{});
+    else {
+        auto eval = [&](float tau, float& f1) {
+            const float y = (NB - t) * h - tau;
+            const float pr1 = y > 0.f && cnt > 0 ? (float)cnt * pow_r1<AM>(y, r) : 0.f;
+            float f = pr1 * y, g = pr1;
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) { f += __shfl_xor(f, off); g += __shfl_xor(g, off); }
+            f1 = -r * g;
+            return f - 1.f;
+        };
+        float d1;
+        if (r < 1.f) {                                 // alpha > 2: bisection
+            float lo = -h, hi = NB * h;
+            for (int i = 0; i < 22; ++i) {
+                const float mid = 0.5f * (lo + hi);
+                if (eval(mid, d1) >= 0.f) lo = mid; else hi = mid;
+            }
+            return lo;
+        }
+        float tau = r >= 2.f ? bound(std::integral_constant<int, 3>{}) : bound(std::integral_constant<int, 2>{});
+        for (int i = 0; i < 12; ++i) {                 // Newton from the left
+            const float f = eval(tau, d1), nt = tau - f / d1;
+            if (!(d1 < 0.f && nt > tau && nt <= NB * h)) break;
+            const bool far = nt - tau > 1e-7f;
+            tau = nt;
+            if (!far) break;
+        }
+        return tau;
+    }
+}
+
 // unsigned integers that order like the floats they come from (for an integer atomic maximum)
 EA_DEV unsigned int ordered_bits(float f) {
     const unsigned int u = __float_as_uint(f);
@@ -223,11 +299,10 @@ __global__ __launch_bounds__(1024) void decode_entmax_kernel(DecodeParams p) {
     const int total = cnt_s;
     const bool over = total > CAP;          // then every evaluation streams the kept logits instead
     const int nc = min(total, CAP);
-    if (tid == 0) {
-        const float tau_h = solve_histogram<AM, SLOTS, 32, false, true>(hist, 0, 0, hb, r) + lower;
+    if (wave == 0) {
+        const float tau_h = wave_histogram_root<AM>(hist, hb, r) + lower;
         const float slack = 1e-6f + 2.5e-7f * fabsf(lower);
-        bc[0] = fmaxf(tau_h - slack, lower);
-        bc[1] = tau_h + hb + slack;
+        if (lane == 0) { bc[0] = fmaxf(tau_h - slack, lower); bc[1] = tau_h + hb + slack; }
     }
     __syncthreads();
     float thr = bc[0], blo = thr, bhi = bc[1];

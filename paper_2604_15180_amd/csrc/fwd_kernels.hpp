@@ -31,7 +31,7 @@ namespace ea {
 // non-empty bin, i.e. the largest one whose bound at that edge is below 1: a polynomial in the three
 // sums.  The bound only rises towards lower edges, so whole chunks of eight bins are tried first and the
 // bins of one chunk then; the root is formed once, from the sums of the set.
-// The sums are integers (WIDE: 64 bits, for more than 2^17 counts), so that they do not depend on the order of
+// The sums are integers, so that they do not depend on the order of
 // summation; a scan in fp32 over all 64 bins by each lane took three times the instructions.  Steps, together
 // with the general solve below: alpha = 1.25, 32 heads of 8192 tokens 1633 -> 1447 us, 64 heads of 4096 tokens at
 // alpha = 1.5 907 -> 858 us (d = 64).
@@ -42,11 +42,11 @@ template <int BITS> EA_DEV uint32_t histogram_count(const uint32_t* H, int slot,
     if constexpr (BITS == 32) return w;
     else return (w >> shift) & ((1u << (BITS & 31)) - 1u);
 }
-template <int MOM, int SLOTS, int BITS, bool PAIRED, bool WIDE = false>
+template <int MOM, int SLOTS, int BITS, bool PAIRED>
 EA_DEV float histogram_moment_root(const uint32_t* H, int rot, int shift, float h, float r) {
-    using I = std::conditional_t<WIDE, long long, int>;
+    using I = int;                                     // (at most 2^17 counts: S2 stays below 2^30)
     constexpr int NB = SLOTS - 1, NCH = SLOTS / 8;
-    static_assert(!(WIDE && PAIRED) && NCH % 2 == 0, "sums travel between lanes as 32-bit words");
+    static_assert(NCH % 2 == 0, "chunks are shared by the two lanes of a row");
     const float q = 1.f - 2.f / r;
     // bound at the edge t bins below the top, less its target, of a non-empty set (negative: the set may grow)
     auto inside = [&](I S0, I S1, I S2, int t) {
@@ -106,18 +106,18 @@ EA_DEV float histogram_moment_root(const uint32_t* H, int rot, int shift, float 
     return ((float)NB - t_root) * h;
 }
 // A lower bound of the histogram's root for general alpha, from the closed forms alone
-template <int SLOTS, int BITS, bool PAIRED, bool WIDE = false>
+template <int SLOTS, int BITS, bool PAIRED>
 EA_DEV float histogram_lower_bound(const uint32_t* H, int rot, int shift, float h, float r) {
-    if (r >= 2.f) return histogram_moment_root<3, SLOTS, BITS, PAIRED, WIDE>(H, rot, shift, h, r);
-    if (r >= 1.f) return histogram_moment_root<2, SLOTS, BITS, PAIRED, WIDE>(H, rot, shift, h, r);
-    return histogram_moment_root<1, SLOTS, BITS, PAIRED, WIDE>(H, rot, shift, h, r);
+    if (r >= 2.f) return histogram_moment_root<3, SLOTS, BITS, PAIRED>(H, rot, shift, h, r);
+    if (r >= 1.f) return histogram_moment_root<2, SLOTS, BITS, PAIRED>(H, rot, shift, h, r);
+    return histogram_moment_root<1, SLOTS, BITS, PAIRED>(H, rot, shift, h, r);
 }
 // The root tau_h of f_h(tau) = -1 + sum_k H_k [k h - tau]_+^r (Eq. 9) in units above the origin;
 // -h for an empty histogram.
-template <int AM, int SLOTS, int BITS, bool PAIRED, bool WIDE = false>
+template <int AM, int SLOTS, int BITS, bool PAIRED>
 EA_DEV float solve_histogram(const uint32_t* H, int rot, int shift, float h, float r) {
-    if constexpr (AM == ALPHA_15) return histogram_moment_root<2, SLOTS, BITS, PAIRED, WIDE>(H, rot, shift, h, r);
-    else if constexpr (AM == ALPHA_20) return histogram_moment_root<1, SLOTS, BITS, PAIRED, WIDE>(H, rot, shift, h, r);
+    if constexpr (AM == ALPHA_15) return histogram_moment_root<2, SLOTS, BITS, PAIRED>(H, rot, shift, h, r);
+    else if constexpr (AM == ALPHA_20) return histogram_moment_root<1, SLOTS, BITS, PAIRED>(H, rot, shift, h, r);
     else {
         // PAIRED: a lane takes every other bin.  Eight bins are read together (one at a time, each read
         // waits for the one before), down to the chunk that no lane's threshold reaches.
@@ -155,7 +155,7 @@ EA_DEV float solve_histogram(const uint32_t* H, int rot, int shift, float h, flo
         // alpha <= 2: f_h is convex and decreasing, so Newton from the left is monotone and
         // stays at or below the root; from the closed-form bound it needs three or four steps
         // (bisecting first took sixteen evaluations)
-        float tau = histogram_lower_bound<SLOTS, BITS, PAIRED, WIDE>(H, rot, shift, h, r);
+        float tau = histogram_lower_bound<SLOTS, BITS, PAIRED>(H, rot, shift, h, r);
         for (int i = 0; i < 12; ++i) {
             const float f = eval(tau, d1);
             const float nt = tau - f / d1;             // (d1 = 0, an empty histogram: NaN or inf, not taken)
