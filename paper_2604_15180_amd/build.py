@@ -13,7 +13,7 @@ OBJDIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libentmax_attn.so")
 UNITS = ["api", "decode", "inst_bf16_d64", "inst_bf16_d128", "inst_f32_d64", "inst_f32_d128"]
 HEADERS = [os.path.join(CSRC, f) for f in
-           ("tiles.hpp", "common.hpp", "gather.hpp", "fwd_kernels.hpp", "bwd_kernels.hpp", "launch.hpp", "ops.hpp")] + [
+           ("tiles.hpp", "common.hpp", "gather.hpp", "histogram.hpp", "fwd_kernels.hpp", "bwd_kernels.hpp", "launch.hpp", "ops.hpp")] + [
     os.path.join(os.path.dirname(HERE), "include", "entmax_attn.h"),
     os.path.join(os.path.dirname(HERE), "include", "entmax_attn_aids.h")]
 

@@ -35,14 +35,16 @@ struct DecodeParams {
     int max_iters;
 };
 
-// The histogram solve of fwd_kernels.hpp (histogram_moment_root, solve_histogram) by one whole wave for one
+// The histogram solve of histogram.hpp (histogram_moment_root, solve_histogram) by one whole wave for one
 // histogram of 64 bins from LDS: lane t holds the bin t below the top, the sums of every set of bins from the top are
 // one prefix sum, and an evaluation for general alpha is one power function and a sum over the lanes.  A
 // head has one histogram only; one thread walking its bins was a chain of 64 LDS reads and as many tests
 // (32 heads, 131072 keys: call 171.2 -> 167.5 us).
-// Counts go up to 2^22 (the keys of a head): S2 needs 64 bits.  Every lane returns the root.
+// Counts go up to 2^22 (the keys of a head): S2 needs 64 bits.  Every lane returns the root; tau* is at most h + gap
+// above it.  The histogram starts one unit below the maximum, so that tau* is not below its origin.
 template <int AM>
-EA_DEV float wave_histogram_root(const uint32_t* hist, float h, float r) {
+EA_DEV float wave_histogram_root(const uint32_t* hist, float h, float r, float& gap) {
+    gap = 0.f;
     constexpr int NB = 63;
     const int t = __lane_id();
     const int cnt = (int)hist[NB - t];
@@ -81,33 +83,26 @@ EA_DEV float wave_histogram_root(const uint32_t* hist, float h, float r) {
     if constexpr (AM == ALPHA_15) return bound(std::integral_constant<int, 2>{});
     else if constexpr (AM == ALPHA_20) return bound(std::integral_constant<int, 1>{});
     else {
-        auto eval = [&](float tau, float& f1) {
+        auto eval = [&](float tau, float& F, float& G) {
             const float y = (NB - t) * h - tau;
             const float pr1 = y > 0.f && cnt > 0 ? (float)cnt * pow_r1<AM>(y, r) : 0.f;
             float f = pr1 * y, g = pr1;
 #pragma unroll
             for (int off = 32; off >= 1; off >>= 1) { f += __shfl_xor(f, off); g += __shfl_xor(g, off); }
-            f1 = -r * g;
-            return f - 1.f;
+            F = f; G = g;
         };
-        float d1;
         if (r < 1.f) {                                 // alpha > 2: bisection
             float lo = -h, hi = NB * h;
             for (int i = 0; i < 22; ++i) {
                 const float mid = 0.5f * (lo + hi);
-                if (eval(mid, d1) >= 0.f) lo = mid; else hi = mid;
+                float F, G;
+                eval(mid, F, G);
+                if (F - 1.f >= 0.f) lo = mid; else hi = mid;
             }
             return lo;
         }
-        float tau = r >= 2.f ? bound(std::integral_constant<int, 3>{}) : bound(std::integral_constant<int, 2>{});
-        for (int i = 0; i < 12; ++i) {                 // Newton from the left
-            const float f = eval(tau, d1), nt = tau - f / d1;
-            if (!(d1 < 0.f && nt > tau && nt <= NB * h)) break;
-            const bool far = nt - tau > 1e-7f;
-            tau = nt;
-            if (!far) break;
-        }
-        return tau;
+        const float tau = r >= 2.f ? bound(std::integral_constant<int, 3>{}) : bound(std::integral_constant<int, 2>{});
+        return newton_from_left(eval, fmaxf(tau, 0.f), NB * h, r, gap);
     }
 }
 
@@ -300,9 +295,10 @@ __global__ __launch_bounds__(1024) void decode_entmax_kernel(DecodeParams p) {
     const bool over = total > CAP;          // then every evaluation streams the kept logits instead
     const int nc = min(total, CAP);
     if (wave == 0) {
-        const float tau_h = wave_histogram_root<AM>(hist, hb, r) + lower;
+        float gap;
+        const float tau_h = wave_histogram_root<AM>(hist, hb, r, gap) + lower;
         const float slack = 1e-6f + 2.5e-7f * fabsf(lower);
-        if (lane == 0) { bc[0] = fmaxf(tau_h - slack, lower); bc[1] = tau_h + hb + slack; }
+        if (lane == 0) { bc[0] = fmaxf(tau_h - slack, lower); bc[1] = tau_h + (hb + gap) + slack; }
     }
     __syncthreads();
     float thr = bc[0], blo = thr, bhi = bc[1];

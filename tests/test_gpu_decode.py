@@ -33,9 +33,10 @@ def run(ea, B, H, N, d, dtype, alpha, sigma, seed, planted=False):
     dtau = np.abs(tau.double().cpu().numpy() - ref["tau"]).max()
     assert dO <= TOL[dtype]["O"], f"|dO| = {dO:.3e}"
     assert dtau <= TOL[dtype]["tau"], f"|dtau| = {dtau:.3e}"
-    # support size: exact except for keys whose score lies within the tolerance band of tau
+    # support size: exact except for keys whose score lies within the tolerance band of tau, or whose
+    # probability x^(1/(alpha-1)) lies below the smallest normal fp32 number, 2^-126, and may be zero
     x = (alpha - 1) * ref["z"] - ref["tau"][..., None]
-    lo, hi = (x > 1e-3).sum(-1), (x > -1e-3).sum(-1)
+    lo, hi = (x > max(1e-3, 1.01 * 2.0 ** (-126 * (alpha - 1)))).sum(-1), (x > -1e-3).sum(-1)
     got = support.cpu().numpy()
     assert ((got >= lo) & (got <= hi)).all(), (got, lo, hi)
     assert 1 <= iters.min().item() and iters.max().item() <= (16 if alpha <= 2 else 32)
@@ -51,6 +52,12 @@ def test_decode_fp32_sizes(ea, N):
 @pytest.mark.parametrize("d,alpha", [(64, 1.5), (128, 1.5), (128, 2.0), (64, 1.25), (64, 2.5), (128, 3.0)])
 def test_decode_bf16(ea, d, alpha):
     run(ea, 2, 3, 8192, d, "bf16", alpha, 2.0, seed=91)
+
+
+@pytest.mark.parametrize("alpha,N", [(1.01, 1000), (1.03, 16384)])
+def test_decode_alpha_near_one(ea, alpha, N):
+    # r = 1/(alpha-1) of 33 and 100 (see test_alpha_near_one): candidates in LDS, and streamed
+    run(ea, 1, 2, N, 128, "bf16", alpha, 3.0, seed=97)
 
 
 def test_decode_fp32_head_dim_128(ea):

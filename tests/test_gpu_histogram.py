@@ -203,6 +203,12 @@ def test_histogram_root_from_each_closed_form_bound(ea, dtype, d, alpha, scale, 
     test_histogram_root_brackets_the_threshold(ea, dtype, d, alpha, "gauss", scale, causal)
 
 
+@pytest.mark.parametrize("dtype,d,alpha,scale", [("bf16", 64, 1.01, 3.0), ("bf16", 128, 1.03, 3.0)])
+def test_histogram_root_for_alpha_near_one(ea, dtype, d, alpha, scale):
+    # where the closed-form bound lies many bins below the root (see tests/host/histogram_main.cpp)
+    test_histogram_root_brackets_the_threshold(ea, dtype, d, alpha, "gauss", scale, True)
+
+
 @pytest.mark.parametrize("dtype,d,alpha,causal", [("bf16", 64, 1.5, True), ("bf16", 128, 1.5, False), ("bf16", 64, 2.0, False),
                                                   ("bf16", 128, 1.25, False), ("f32", 64, 1.5, True)])
 def test_histogram_of_rising_maxima(ea, dtype, d, alpha, causal):

@@ -137,6 +137,32 @@ def test_alpha_above_two(ea, dtype, alpha, N, d, causal, sigma):
     run_case(ea, 1, 2, N, d, dtype, causal, alpha, sigma, seed=400 + N)
 
 
+@pytest.mark.parametrize("dtype,alpha,N,overflow", [("bf16", 1.01, 512, False), ("bf16", 1.03, 512, False), ("f32", 1.03, 512, False),
+                                                    ("bf16", 1.01, 4096, True), ("bf16", 1.03, 4096, True)])
+def test_alpha_near_one(ea, dtype, alpha, N, overflow):
+    # r = 1/(alpha-1) of 33 and 100 at wide scores: the closed-form bound of the histogram's root lies far
+    # below it, and a solve that stops short leaves tau* outside its bracket.  Thresholds from the candidate
+    # lists (512 tokens) and from the sweep-based kernel (4096: the lists overflow).  O and the gradients
+    # are held to the usual bars plus what the solver's 1e-4 (fp32: 1e-6) of y changes in P = y^r
+    # (parity.output_slack, parity.conditioning_slack).
+    B, H, d, causal, sigma = 1, 1, 64, True, 3.0
+    print(f"case near one {dtype} alpha={alpha} N={N}", flush=True)
+    q, k, v, do = workloads.gaussian_qkv(B, H, N, d, dtype, sigma, seed=500 + N)
+    Q, K, V, dO = (t.cuda() for t in (q, k, v, do))
+    ws = torch.empty(ea.entmax_attn_workspace_bytes(B, H, N, d, dtype, causal, False), dtype=torch.uint8, device="cuda")
+    O, tau, mask, iters = ea.entmax_attn_fwd(Q, K, V, alpha, causal, want_iters=True, workspace=ws)
+    torch.cuda.synchronize()
+    assert (ea.read_stats(ws)["list_overflow_blocks"] > 0) == overflow
+    ref, info = parity.check_forward(q, k, v, alpha, causal, O, tau, mask, label="near one", rounding_slack=True)
+    if dtype == "f32":
+        dQ, dK, dV = ea.entmax_attn_bwd(Q, K, V, O, dO, tau, alpha, causal, block_mask=mask)
+        torch.cuda.synchronize()
+        _, ginfo = parity.check_backward(q, k, v, do, alpha, causal, dQ, dK, dV, label="near one", tau_ref=ref["tau"])
+        info.update(ginfo)
+    print("  ", info, "max iters", iters.max().item(), flush=True)
+    assert iters.max().item() <= 12
+
+
 def test_bf16_block_sparse_inputs(ea):
     # block-correlated queries: many all-zero 64x64 tiles, exercises the skip paths
     info = run_case(ea, 1, 2, 1024, 64, "bf16", True, 1.5, 3.0, seed=24, block_rho=0.98)
