@@ -126,9 +126,8 @@ __host__ __device__ inline HeadConsts head_consts_of(float alpha, float inv_sqrt
     const float mant = frexpf(k.c, &ex);          // c = mant * 2^ex, 0.5 <= mant < 1
     k.kappa = ldexpf(1.f, ex - 1);
     k.rho = 2.f * mant;
-    k.rho_p = powf(k.rho, k.r);
-    k.rho_u = powf(k.rho, k.r - 1.f);
-    k.pad = 0.f;
+    k.lrho_u = (k.r - 1.f) * log2f(k.rho);
+    k.pad[0] = k.pad[1] = 0.f;
     return k;
 }
 

@@ -339,12 +339,13 @@ __global__ __launch_bounds__(NW * 64) void dq_kernel(Params p) {
 // accumulator registers, so they cost no arithmetic at all: the accumulators of the two stage-1
 // products start from -tau / rho and -delta (read from LDS, four rows per 16-byte read) instead of
 // zero.  With the owned keys scaled by kappa the first product is then y / rho, y = (alpha-1) s -
-// tau, and the second dP - delta; P = y^r and dS = y^(r-1) (dP - delta) come out in units of
-// rho^r and rho^(r-1), which the kernel's epilogue multiplies back in.
+// tau, and the second dP - delta.  alpha 1.5 and 2: P = y^r and dS = y^(r-1) (dP - delta) come out in units of
+// rho^r and rho^(r-1), which the kernel's epilogue multiplies back in.  General alpha: rho^(r-1) goes into the exponent
+// of U = y^(r-1), and P is left in units of rho (at alpha = 1.03 rho^r can be 1e10: P over it is zero in fp16).
 template <class E, class E2, int D, int AM, int SPLIT>
 EA_DEV void dkdv_tile_staggered(const char* qbuf, const char* gbuf, const float* ntau_s, const float* ndel_s,
                                 const Owned<E, D, 1>& kf, const Owned<E, D, 1>& vf, f32x16 (&XV)[D / 32][1],
-                                f32x16 (&XK)[D / 32][1], float r, int h, const Frag1<E, D>& f1,
+                                f32x16 (&XK)[D / 32][1], float r, float lrho_u, int h, const Frag1<E, D>& f1,
                                 const Frag2<E2, D>& f2) {
     constexpr int NS = D / 16, ND = D / 32;
     constexpr int N1 = 2 * NS, N2 = 4 * ND, PF = 4, EPM = 8 / NS;
@@ -372,7 +373,8 @@ EA_DEV void dkdv_tile_staggered(const char* qbuf, const char* gbuf, const float*
         const float yp = fmaxf(S[kb][e], 0.f);
         float u;
         if constexpr (AM == ALPHA_15) u = yp;
-        else u = (yp > 0.f) ? pow_r1<AM>(yp, r) : 0.f;
+        else if constexpr (AM == ALPHA_20) u = (yp > 0.f) ? 1.f : 0.f;
+        else u = (yp > 0.f) ? pow_r1_rho(yp, r, lrho_u) : 0.f;
         S[kb][e] = u * yp;
         P[kb][e] = u * P[kb][e];
         if (e & 1) {
@@ -529,7 +531,7 @@ __global__ __launch_bounds__(NW * 64) void dkdv_kernel(Params p) {
     const int mycol = (wave * 32 * QB) / 64;  // my mask column within the group
     const int jc0 = J * MC;                   // first mask column of the group
     const HeadConsts hc = head_consts(p, bh);
-    const float c = hc.c, r = hc.r;
+    const float r = hc.r, lrho_u = hc.lrho_u;
 
     // ---- column walk of the row-packed mask: list of query tiles with a set bit -------------
     const int i_min = p.causal ? jc0 : 0;
@@ -637,11 +639,12 @@ __global__ __launch_bounds__(NW * 64) void dkdv_kernel(Params p) {
                     const float tq = tq4[e], dq = dq4[e];
 #pragma unroll
                     for (int qb = 0; qb < QB; ++qb) {
-                        // (same units as the staggered body: y / rho, rho^r, rho^(r-1))
+                        // (same units as the staggered body)
                         const float yp = fmaxf(S[kb][qb][v] + tq, 0.f);
                         float u;
                         if constexpr (AM == ALPHA_15) u = yp;
-                        else u = (yp > 0.f) ? pow_r1<AM>(yp, r) : 0.f;
+                        else if constexpr (AM == ALPHA_20) u = (yp > 0.f) ? 1.f : 0.f;
+                        else u = (yp > 0.f) ? pow_r1_rho(yp, r, lrho_u) : 0.f;
                         S[kb][qb][v] = u * yp;
                         dP[kb][qb][v] = u * (dP[kb][qb][v] + dq);
                     }
@@ -665,7 +668,7 @@ __global__ __launch_bounds__(NW * 64) void dkdv_kernel(Params p) {
                 if (!((tl[it] >> (16 + mycol)) & 1)) return;
                 ++ntile_done;
                 const float* tau_s = (const float*)(qbuf + VEC_OFF);
-                dkdv_tile_staggered<E, E2, D, AM, EA_BWD_SPLIT>(qbuf, qbuf + SM::RBYTES, tau_s, tau_s + TILE, kf, vf, XV, XK, r, h, frag1, frag2);
+                dkdv_tile_staggered<E, E2, D, AM, EA_BWD_SPLIT>(qbuf, qbuf + SM::RBYTES, tau_s, tau_s + TILE, kf, vf, XV, XK, r, lrho_u, h, frag1, frag2);
             });
     } else {
         stream_tiles<NBUF>(ntl, set0, NBUF == 2 ? set1 : set0, issue_qg, tile_plain_order);
@@ -675,12 +678,14 @@ __global__ __launch_bounds__(NW * 64) void dkdv_kernel(Params p) {
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) { settle_acc(XV[db][qb]); settle_acc(XK[db][qb]); }
     if (active) {
+        // units of P and U, see dkdv_tile_staggered
+        const float unit_p = AM == ALPHA_15 ? hc.rho * hc.rho : hc.rho, unit_u = AM == ALPHA_15 ? hc.rho : 1.f;
         if (!shared_out) {
-            store_owned_T<D, QB>(p.dV + hoff, kw0, XV, go_amax * hc.rho_p, lane);
-            store_owned_T<D, QB>(p.dK + hoff, kw0, XK, p.inv_sqrt_d * go_amax * hc.rho_u, lane);
+            store_owned_T<D, QB>(p.dV + hoff, kw0, XV, go_amax * unit_p, lane);
+            store_owned_T<D, QB>(p.dK + hoff, kw0, XK, p.inv_sqrt_d * go_amax * unit_u, lane);
         } else {
-            add_owned_T<D, QB>(p.dV + hoff, kw0, XV, go_amax * hc.rho_p, lane);
-            add_owned_T<D, QB>(p.dK + hoff, kw0, XK, p.inv_sqrt_d * go_amax * hc.rho_u, lane);
+            add_owned_T<D, QB>(p.dV + hoff, kw0, XV, go_amax * unit_p, lane);
+            add_owned_T<D, QB>(p.dK + hoff, kw0, XK, p.inv_sqrt_d * go_amax * unit_u, lane);
         }
     }
     {

@@ -53,9 +53,9 @@ struct HeadConsts {
     float c;              // (alpha-1)/sqrt(d): x = c * <q,k>
     float r;              // 1/(alpha-1)
     // c = kappa * rho with kappa a power of two and 1 <= rho < 2 (dK/dV kernel: keys scaled by kappa,
-    // which is exact, scores kept in units of rho); rho_p = rho^r, rho_u = rho^(r-1)
-    float kappa, rho, rho_p, rho_u;
-    float pad;
+    // which is exact, scores kept in units of rho); lrho_u = log2(rho^(r-1))
+    float kappa, rho, lrho_u;
+    float pad[2];
 };
 
 struct Params {
@@ -138,6 +138,10 @@ template <int AM> EA_DEV float pow_r1(float y, float r) {
     if constexpr (AM == ALPHA_15) return y;
     else if constexpr (AM == ALPHA_20) return 1.f;
     else return __builtin_amdgcn_exp2f((r - 1.f) * __builtin_amdgcn_logf(r < 1.f ? fmaxf(y, 1e-6f) : y));
+}
+// U = (rho y)^(r-1) from a y in units of rho (general alpha; lrho_u = log2(rho^(r-1)))
+EA_DEV float pow_r1_rho(float y, float r, float lrho_u) {
+    return __builtin_amdgcn_exp2f(fmaf(r - 1.f, __builtin_amdgcn_logf(r < 1.f ? fmaxf(y, 1e-6f) : y), lrho_u));
 }
 template <int AM> EA_DEV float pow_r2(float y, float r) {
     if constexpr (AM == ALPHA_15) return 1.f;
