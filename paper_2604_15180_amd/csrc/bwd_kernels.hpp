@@ -961,15 +961,13 @@ __global__ __launch_bounds__(256) void bwd_rows_kernel(Params p) {
     const float tau = p.tau[gi];
     const int s0 = p.scnt[gi * 2], tot = s0 + p.scnt[gi * 2 + 1];
     const vec gv = *(const vec*)((const elem*)p.dO + hoff + (long)row * D + L::column(sub));
-    int nmax = tot;                                    // the longest of the wave's four rows
-    nmax = max(nmax, __shfl_xor(nmax, 16));
-    nmax = max(nmax, __shfl_xor(nmax, 32));
-    nmax = __builtin_amdgcn_readfirstlane(nmax);
+    int nmin, nmax;
+    list_range(tot, nmin, nmax);
 
     auto entry_ptr = [&](int i) { return l0 + (i < s0 ? i * 8 : cap8 + (i - s0) * 8); };
     struct Entry { uint32_t key; float u, pr; };
     auto load_entry = [&](int i) {
-        uint2 e = make_uint2(0u, 0u);
+        uint2 e = make_uint2(0u, NO_ENTRY);
         if (i < tot) e = *(const uint2*)entry_ptr(i);
         const float y = fmaf(c, __uint_as_float(e.x), -tau);
         const bool in = i < tot && y > 0.f;
@@ -979,7 +977,7 @@ __global__ __launch_bounds__(256) void bwd_rows_kernel(Params p) {
         x.pr = in ? pow_r<AM>(y, r) : 0.f;
         return x;
     };
-    // dP of a chunk's entries, each left in the lane that holds the entry
+    // dP of a chunk's entries, each left in the lane that holds the entry (0 in one that holds none)
     auto chunk_dP = [&](uint32_t key, int left) {
         float dP = 0.f;
         unroll_steps<L::STEPS / BT>([&](auto b) {
@@ -993,7 +991,7 @@ __global__ __launch_bounds__(256) void bwd_rows_kernel(Params p) {
                 if (L::template holds<S>(sub)) dP = t;
             });
         });
-        return dP;
+        return key == NO_ENTRY ? 0.f : dP;
     };
     Entry ent[KEEPC];
     float dP[KEEPC];
@@ -1025,7 +1023,7 @@ __global__ __launch_bounds__(256) void bwd_rows_kernel(Params p) {
     for (int k = 0; k < EPT; ++k) x[k] = 0.f;
     // file a chunk's entries under their keys and add their share of dQ
     auto finish_chunk = [&](const Entry& e, float dPe, int sl, int i0) {
-        const float dS = e.u * (dPe - delta);
+        const float dS = e.key == NO_ENTRY ? 0.f : e.u * (dPe - delta);
         const int i = i0 + L::entry_of(sub);
         if (i < tot) {
             if (sl < KEY_LIST_CAP) ((KeyEntry*)p.klist)[((long)bh * N + e.key) * KEY_LIST_CAP + sl] = KeyEntry{(uint32_t)row, dS, e.pr};
@@ -1036,6 +1034,7 @@ __global__ __launch_bounds__(256) void bwd_rows_kernel(Params p) {
             if (S0 * L::PAR >= nmax - i0) return;
             vec v[BT];
             unroll_steps<BT>([&](auto u) { v[decltype(u)::value] = *(const vec*)(Kh + (size_t)(L::template of_step<S0 + decltype(u)::value>(e.key) * (uint32_t)D)); });
+            if ((S0 + BT) * L::PAR > nmin - i0) unroll_steps<BT>([&](auto u) { clear_absent(L::template of_step<S0 + decltype(u)::value>(e.key), v[decltype(u)::value]); });
             unroll_steps<BT>([&](auto u) { add_scaled<EPT>(x, L::template of_step<S0 + decltype(u)::value>(dS), v[decltype(u)::value]); });
         });
     };
@@ -1161,10 +1160,8 @@ __global__ __launch_bounds__(256) void bwd_cols_kernel(Params p) {
     const elem* Gh = (const elem*)p.dO + hoff + L::column(sub);
     const bool fresh = *p.nplain == 0;
     const int cnt = min(p.kcnt[kj], KEY_LIST_CAP);
-    int nmax = cnt;                                    // the longest list of the wave's four keys
-    nmax = max(nmax, __shfl_xor(nmax, 16));
-    nmax = max(nmax, __shfl_xor(nmax, 32));
-    nmax = __builtin_amdgcn_readfirstlane(nmax);
+    int nmin, nmax;
+    list_range(cnt, nmin, nmax);
     if (nmax == 0 && !fresh) return;
     const KeyEntry* el = (const KeyEntry*)p.klist + kj * KEY_LIST_CAP;
     auto wave_fence = [] {                             // (the 16 lanes of a key sit in one wave, whose LDS operations execute in issue order)
@@ -1210,7 +1207,7 @@ __global__ __launch_bounds__(256) void bwd_cols_kernel(Params p) {
     for (int k = 0; k < EPT; ++k) { ak[k] = 0.f; av[k] = 0.f; }
     for (int i0 = 0; i0 < nmax; i0 += 16) {
         const int i = i0 + L::entry_of(sub);
-        uint32_t row = 0u;
+        uint32_t row = NO_ENTRY;
         float2 w = make_float2(0.f, 0.f);              // dS, P
         if (i < cnt) { row = row_s[rsel][i]; w = val_s[rsel][i]; }
         unroll_steps<L::STEPS / BT>([&](auto b) {
@@ -1222,6 +1219,12 @@ __global__ __launch_bounds__(256) void bwd_cols_kernel(Params p) {
                 const size_t off = (size_t)(L::template of_step<S0 + U>(row) * (uint32_t)D);
                 qv[U] = *(const vec*)(Qh + off);
                 gv[U] = *(const vec*)(Gh + off);
+            });
+            if ((S0 + BT) * L::PAR > nmin - i0) unroll_steps<BT>([&](auto u) {
+                constexpr int U = decltype(u)::value;
+                const uint32_t of_entry = L::template of_step<S0 + U>(row);
+                clear_absent(of_entry, qv[U]);
+                clear_absent(of_entry, gv[U]);
             });
             unroll_steps<BT>([&](auto u) {
                 constexpr int U = decltype(u)::value;

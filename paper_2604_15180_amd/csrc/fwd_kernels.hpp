@@ -1062,16 +1062,14 @@ __global__ __launch_bounds__(256) void gather_out_kernel(Params p) {
     const float tau = p.tau[gi];
     const int s0 = p.scnt[gi * 2], tot = s0 + p.scnt[gi * 2 + 1];
     const char* l0 = (const char*)p.lists + (size_t)gi * (2 * LIST_CAP * 8);      // the second list follows the first
-    int nmax = tot;                                   // the longest of the wave's four rows
-    nmax = max(nmax, __shfl_xor(nmax, 16));
-    nmax = max(nmax, __shfl_xor(nmax, 32));
-    nmax = __builtin_amdgcn_readfirstlane(nmax);
+    int nmin, nmax;
+    list_range(tot, nmin, nmax);
     float acc[EPT];
 #pragma unroll
     for (int k = 0; k < EPT; ++k) acc[k] = 0.f;
     for (int i0 = 0; i0 < nmax; i0 += 16) {
         const int i = i0 + L::entry_of(sub);
-        uint2 e = make_uint2(0u, 0u);
+        uint2 e = make_uint2(0u, NO_ENTRY);
         if (i < tot) e = *(const uint2*)(l0 + (i < s0 ? i * 8 : LIST_CAP * 8 + (i - s0) * 8));
         const float y = fmaf(c, __uint_as_float(e.x), -tau);
         const float pr = (i < tot && y > 0.f) ? pow_r<AM>(y, r) : 0.f;
@@ -1080,6 +1078,7 @@ __global__ __launch_bounds__(256) void gather_out_kernel(Params p) {
             if (S0 * L::PAR >= nmax - i0) return;
             vec v[BT];
             unroll_steps<BT>([&](auto u) { v[decltype(u)::value] = *(const vec*)(Vh + (size_t)(L::template of_step<S0 + decltype(u)::value>(e.y) * (uint32_t)D)); });
+            if ((S0 + BT) * L::PAR > nmin - i0) unroll_steps<BT>([&](auto u) { clear_absent(L::template of_step<S0 + decltype(u)::value>(e.y), v[decltype(u)::value]); });
             unroll_steps<BT>([&](auto u) { add_scaled<EPT>(acc, L::template of_step<S0 + decltype(u)::value>(pr), v[decltype(u)::value]); });
         });
     }

@@ -9,6 +9,9 @@
 //   step s of a chunk: half p works on the entry held by lane LPE p + s (PAR = 1: lane s)
 //   lane l holds list entry  l (PAR = 1)  or  2 (l % 8) + l / 8 (PAR = 2) of the chunk, so that the
 //   entries of a short list fall into its first steps
+// A lane past the end of its list holds NO_ENTRY, whose offset is that of row 0 (an address in range).  Its
+// weight is 0; what it loads is cleared all the same (clear_absent), because 0 times an infinity is not 0.
+// Only batches past the end of the wave's shortest list pay for that.
 #pragma once
 #include <type_traits>
 #include <utility>
@@ -16,6 +19,8 @@
 #include "common.hpp"
 
 namespace ea {
+
+constexpr uint32_t NO_ENTRY = 0x80000000u;      // (times D, in 32 bits: 0)
 
 template <class F, int... I> EA_DEV void unroll_steps(F&& f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
 // f(0), f(1), ... f(N-1) with the index as a compile-time constant (DPP controls are immediates)
@@ -77,6 +82,23 @@ template <class E, int N, class V> EA_DEV float dot_share(const V& a, const V& b
         for (int k = 0; k < N; ++k) c = fmaf((float)a[k], (float)b[k], c);
     }
     return c;
+}
+// x = 0 where `index` (an entry's key or row) is NO_ENTRY
+template <class V> EA_DEV void clear_absent(uint32_t index, V& x) {
+    constexpr int W = sizeof(V) / 4;
+    typedef uint32_t words __attribute__((ext_vector_type(W)));
+    const uint32_t keep = ~(uint32_t)((int32_t)index >> 31);
+    words w = __builtin_bit_cast(words, x);
+#pragma unroll
+    for (int k = 0; k < W; ++k) w[k] &= keep;
+    x = __builtin_bit_cast(V, w);
+}
+// shortest and longest list of the wave's four rows or keys
+EA_DEV void list_range(int n, int& nmin, int& nmax) {
+    nmin = min(n, __shfl_xor(n, 16));
+    nmax = max(n, __shfl_xor(n, 16));
+    nmin = __builtin_amdgcn_readfirstlane(min(nmin, __shfl_xor(nmin, 32)));
+    nmax = __builtin_amdgcn_readfirstlane(max(nmax, __shfl_xor(nmax, 32)));
 }
 template <int N, class V> EA_DEV void add_scaled(float (&acc)[N], float w, const V& x) {
 #pragma unroll

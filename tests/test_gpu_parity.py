@@ -401,6 +401,46 @@ def test_keys_that_many_rows_attend_to(ea, dtype, d, N, sigma, causal, hubs):
     print("  ", ginfo, flush=True)
 
 
+@pytest.mark.parametrize("dtype,d,fwd_lists", [("bf16", 64, True), ("bf16", 128, False), ("f32", 64, False), ("f32", 128, True)])
+def test_infinite_first_row_stays_with_those_that_attend_to_it(ea, dtype, d, fwd_lists):
+    # lanes of the gather kernels that are past the end of their list point at row 0: what stands there must not
+    # reach rows and keys that have nothing to do with it.  V_0, then dO_0, infinite: whatever does not
+    # depend on it comes out as with a finite one, bit for bit.
+    B, H, N, alpha, causal = 1, 2, 1024, 1.5, False
+    q, k, v, do = workloads.gaussian_qkv(B, H, N, d, dtype, 3.0 if dtype == "bf16" else 1.5, seed=111)
+    Q, K, V, dO = (t.cuda() for t in (q, k, v, do))
+
+    def run(V, dO):
+        wf = torch.empty(ea.entmax_attn_workspace_bytes(B, H, N, d, dtype, causal, False), dtype=torch.uint8, device="cuda")
+        wb = torch.empty(ea.entmax_attn_workspace_bytes(B, H, N, d, dtype, causal, True), dtype=torch.uint8, device="cuda")
+        O, tau, mask, _ = ea.entmax_attn_fwd(Q, K, V, alpha, causal, want_iters=True, workspace=wf)
+        g = ea.entmax_attn_bwd(Q, K, V, O, dO, tau, alpha, causal, block_mask=mask, workspace=wb, fwd_workspace=wf if fwd_lists else None)
+        torch.cuda.synchronize()
+        assert ea.read_stats(wf)["gather_rows"] == B * H * N and ea.read_stats(wb)["bwd_gather_rows"] == B * H * N
+        return (O, tau) + tuple(g)
+
+    O, tau, dQ, dK, dV = run(V, dO)
+    X = (alpha - 1.0) * (Q.double() @ K.double().transpose(2, 3).contiguous()) / d ** 0.5
+    # (entries within 1e-4 of the threshold may or may not be listed)
+    on = X > tau.double()[..., None] - 1e-4
+    V2, dO2 = V.clone(), dO.clone()
+    V2[:, :, 0] = float("inf")
+    dO2[:, :, 0] = float("inf")
+    O2, _, dQ2, dK2, dV2 = run(V2, dO)
+    row_free = ~on[..., 0]                                            # rows that do not attend to key 0
+    key_free = ~(on & on[..., :1]).any(2)                             # keys of which no row does
+    assert row_free.sum() > 0.9 * B * H * N and key_free.sum() > 0.1 * B * H * N
+    attends = X[..., 0] > tau.double() + 1e-3
+    assert not torch.isfinite(O2[attends]).any()
+    assert torch.equal(O2[row_free], O[row_free]) and torch.equal(dQ2[row_free], dQ[row_free])
+    assert torch.equal(dK2[key_free], dK[key_free]) and torch.equal(dV2, dV)
+    O3, _, dQ3, dK3, dV3 = run(V, dO2)
+    key_free = ~on[:, :, 0]                                           # keys that row 0 does not attend to
+    assert key_free.sum() > 0.9 * B * H * N
+    assert torch.equal(O3, O) and torch.equal(dQ3[:, :, 1:], dQ[:, :, 1:])
+    assert torch.equal(dK3[key_free], dK[key_free]) and torch.equal(dV3[key_free], dV[key_free])
+
+
 def test_sparsemax_with_near_uniform_attention(ea):
     # alpha = 2 with small scores: thousands of keys per row, many of them within the band around
     # the threshold where U jumps between 0 and 1; what those entries may change in dQ, dK, dV is
