@@ -41,7 +41,7 @@ thread_local bool g_gather_enabled = true;      // the gather switch of the call
 thread_local bool g_right_edge = false;         // right-edge binning without refinement (approximate forward), same scope
 
 struct Layout {
-    size_t stats, hc, a, b, c, d, delta, ntau, mask, wmask, tmax, rs_lo, rs_hi, rs_f1, rs_state, rs_t0, rs_up0, lists, oflag, scnt, gflag, kcnt, klist, defer, colcnt, total;
+    size_t stats, hc, a, b, c, d, delta, ntau, mask, wmask, tmax, rs_lo, rs_hi, rs_f1, rs_state, rs_t0, rs_up0, lists, oflag, scnt, gflag, kcnt, klist, klog, hub_key, hub_off, colcnt, total;
 };
 
 // element size of the stage-2 copies
@@ -79,6 +79,8 @@ Layout bwd_layout(int B, int H, int N, int d, int t) {
     L.b = off; off += align256(BH * N * d * t_elem(t));
     L.c = off; off += align256(BH * N * d * t_elem(t));
     L.d = off; off += align256(BH * N * d * t_elem(t));
+    L.klog = L.a;                                                // once the matrix kernels have read the copies: the log of hub keys
+    off = off > L.klog + align256(BH * N * LOG_PER_ROW * sizeof(LogEntry)) ? off : L.klog + align256(BH * N * LOG_PER_ROW * sizeof(LogEntry));
     L.delta = off; off += align256(BH * N * 4);
     L.ntau = off; off += align256(BH * N * 4);
     L.mask = off; off += align256(BH * T * W * 4);               // rebuilt mask (mask == NULL)
@@ -87,9 +89,10 @@ Layout bwd_layout(int B, int H, int N, int d, int t) {
     L.lists = off; off += align256(BH * N * (size_t)(2 * BWD_LIST_CAP * 8));
     L.scnt = off; off += align256(BH * N * 2 * 4);
     L.gflag = off; off += align256(BH * ((size_t)N / 128 + 1) * 4);
-    L.kcnt = off; off += align256(BH * N * 4 + 8);               // and a counter: row groups on the matrix path
+    L.kcnt = off; off += align256(BH * N * 4 + 4 + BH * 4 + BH * MAX_LOG_SEGMENTS * 4);   // and counters: row groups on the matrix path, hub keys, log entries
     L.klist = off; off += align256(BH * N * (size_t)KEY_LIST_CAP * sizeof(KeyEntry));
-    L.defer = off; off += align256(BH * N * 4);
+    L.hub_key = off; off += align256(BH * N * 4);
+    L.hub_off = off; off += align256(BH * N * 4);
     L.colcnt = off; off += align256(BH * T * 4);                 // query tiles per key tile's mask column (dkdv_kernel's parts)
     L.total = off;
     return L;
@@ -330,7 +333,13 @@ int bwd_impl(const void* Q, const void* K, const void* V, const void* O, const v
     p.mask_parts = (int32_t*)(ws + L.delta);        // read before the first delta is written; B H N is at least MASK_PARTS
     static_assert(MASK_PARTS <= TILE, "the partial sums fit where delta will be");
     p.klist = ws + L.klist;
-    p.defer = (int32_t*)(ws + L.defer);
+    p.hub_cnt = p.nplain + 1;
+    p.log_cnt = p.hub_cnt + (size_t)B * H;
+    p.klog = (LogEntry*)(ws + L.klog);
+    p.hub_key = (int32_t*)(ws + L.hub_key);
+    p.hub_off = (int32_t*)(ws + L.hub_off);
+    p.hub_index = (uint32_t*)(ws + L.lists);
+    static_assert(LOG_PER_ROW * 4 <= 2 * BWD_LIST_CAP * 8, "the index fits where the row lists were");
     p.colcnt = (int32_t*)(ws + L.colcnt);
     p.list_cap = BWD_LIST_CAP;
     if (fwd_workspace) {

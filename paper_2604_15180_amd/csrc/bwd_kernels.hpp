@@ -711,13 +711,25 @@ __global__ __launch_bounds__(NW * 64) void dkdv_kernel(Params p) {
 //                     column), added to what dkdv_kernel
 //                     stored for the other row groups (or, when none was left to it, written as
 //                     dK_j, dV_j themselves).
-//   bwd_hot_kernel  : the entries of keys with more entries than a key's list holds, added to
-//                     dK, dV with atomics after bwd_cols_kernel.
-// All three read the caller's Q, K, V, dO (not the 16-bit copies) and work in fp32.
+//   bwd_file_kernel : hub keys, which have more entries than a key's list holds: bwd_rows_kernel
+//                     logs the rest, this kernel orders the log by key, and work-groups of
+//                     bwd_cols_kernel sum each hub key's entries, again in the order of their rows.
+// They read the caller's Q, K, V, dO (not the 16-bit copies) and work in fp32.
 // The gather path pays while a marked 64 x 64 tile holds only a few non-zeros: the group is flagged
 // when its lists hold at most bwd_entries_per_tile entries per marked tile (and no list is full);
 // or BWD_ENTRIES_PER_ROW per row (and no list is full); the sweep is left early once the entries
 // so far run a quarter above that rate.
+
+// Entries a row group may list to take the gather path, by its marked tiles and rows.  A group with few
+// marked tiles (the first rows of a causal head) still has one entry or more per row, and is cheap either way: it
+// goes with the rest, so that the matrix kernels' input copies are not made for its sake alone.
+// Never more than LOG_PER_ROW a row, as in the forward: the log of hub keys has room for that.
+template <class E, int D, int AM> EA_DEV int gather_budget(int marked, int rows) {
+    constexpr int PER_ROW_X128 = BWD_ENTRIES_PER_ROW * D * D / 128 / (AM == ALPHA_GEN ? 2 : 1);
+    return min(max(bwd_entries_per_tile(D, sizeof(typename E::elem)) * marked, marked <= BWD_FEW_TILES ? PER_ROW_X128 * rows / 128 : 0),
+               LOG_PER_ROW * rows);
+}
+
 // Set bits of the whole mask, from bwd_begin_kernel's partial sums (called by whole waves)
 EA_DEV long marked_tiles(const Params& p, int lane) {
     static_assert(MASK_PARTS == 64, "one partial sum per lane");
@@ -773,12 +785,7 @@ __global__ __launch_bounds__(NW * 64) void bwd_list_kernel(Params p) {
     }
     build_tile_list(fm, MR, W, tl, tl_count, tid);
     const int nt = *tl_count;
-    // entries the whole group may list (a group with few marked tiles - the first rows of a causal
-    // head - still has one entry or more per row, and is cheap either way: it goes with the rest,
-    // so that the matrix kernels' input copies are not made for its sake alone)
-    constexpr int PER_ROW_X128 = BWD_ENTRIES_PER_ROW * D * D / 128 / (AM == ALPHA_GEN ? 2 : 1);
-    const int budget = max(bwd_entries_per_tile(D, sizeof(elem)) * gsum[1],
-                           gsum[1] <= BWD_FEW_TILES ? PER_ROW_X128 * min(BR, N - (int)((long)I * BR)) / 128 : 0);
+    const int budget = gather_budget<E, D, AM>(gsum[1], min(BR, N - (int)q0));
 
     Owned<E, D, QB> qf;
     load_owned<E, D, QB>(qf, Qh, active ? qw0 : 0, lane);
@@ -911,10 +918,7 @@ __global__ __launch_bounds__(128) void bwd_decide_kernel(Params p) {
     }
     __syncthreads();
     if (tid == 0) {
-            constexpr int PER_ROW_X128 = BWD_ENTRIES_PER_ROW * D * D / 128 / (AM == ALPHA_GEN ? 2 : 1);
-        const int budget = max(bwd_entries_per_tile(D, sizeof(typename E::elem)) * gsum[1],
-                               gsum[1] <= BWD_FEW_TILES ? PER_ROW_X128 * min(BR, N - I * BR) / 128 : 0);
-        gather = gather && gsum[0] <= budget;
+        gather = gather && gsum[0] <= gather_budget<E, D, AM>(gsum[1], min(BR, N - I * BR));
         p.gflag[(long)bh * G + I] = gather;
         if (!gather) atomicAdd(p.nplain, 1);
         else atomicAdd(&p.stats[(blockIdx.x & (STATS_COPIES - 1)) * STATS_WORDS + 11], (unsigned long long)min(BR, N - I * BR));
@@ -924,9 +928,8 @@ __global__ __launch_bounds__(128) void bwd_decide_kernel(Params p) {
 // Sixteen lanes per row (GatherLanes).  Per row, over its entries: dP_j = <dO_r, V_j>, delta = sum u dP / sum u,
 // dQ_r = sum_j dS_j K_j / sqrt(d) with dS = u (dP - delta); every entry is filed under its key as
 // (row, dS, P).  dP of the first KEEP entries stays in registers between the two passes; a longer
-// row computes it a second time.  An entry whose key's list is full is marked (top bit of its key
-// index) and left to bwd_hot_kernel, which adds it to dK, dV atomically once bwd_cols_kernel has
-// stored them.  SCALED: dkdv_kernel works on dO / max|dO|, so the delta handed to it is in those units.
+// row computes it a second time.  An entry whose key's list is full goes to the log of its row's segment;
+// the first of a key reports the key as a hub key.  SCALED: dkdv_kernel works on dO / max|dO|, so the delta handed to it is in those units.
 template <class E, int D, int AM, bool SCALED>
 __global__ __launch_bounds__(256) void bwd_rows_kernel(Params p) {
     using elem = typename E::elem;
@@ -957,7 +960,7 @@ __global__ __launch_bounds__(256) void bwd_rows_kernel(Params p) {
     const elem* Kh = (const elem*)p.K + hoff + L::column(sub);
     const elem* Vh = (const elem*)p.V + hoff + L::column(sub);
     const int cap8 = p.list_cap * 8;                   // bytes of one lane list
-    char* l0 = (char*)p.lists + (size_t)gi * (size_t)(2 * cap8);        // the second list follows the first
+    const char* l0 = (const char*)p.lists + (size_t)gi * (size_t)(2 * cap8);        // the second list follows the first
     const float tau = p.tau[gi];
     const int s0 = p.scnt[gi * 2], tot = s0 + p.scnt[gi * 2 + 1];
     const vec gv = *(const vec*)((const elem*)p.dO + hoff + (long)row * D + L::column(sub));
@@ -993,6 +996,32 @@ __global__ __launch_bounds__(256) void bwd_rows_kernel(Params p) {
         });
         return key == NO_ENTRY ? 0.f : dP;
     };
+    // An entry's slot in its key's list.  In the first chunk, rows of the wave that hold the same key at the same place
+    // of their lists (a sink, the first keys of a head that every row attends to) ask for their slots in one addition: on
+    // such a key the additions queue up
+    // (4 sinks, 32 heads of 4096 tokens, d = 64: backward 363 -> 262 us; one sink, 32 heads of 16384, d = 128: 1464 -> 789).
+    int* const count = p.kcnt + (long)bh * N;
+    auto take_slots_together = [&](uint32_t key, bool mine) __attribute__((always_inline)) {
+        const uint32_t k = mine ? key : NO_ENTRY | (uint32_t)lane;
+        const auto x1 = __builtin_amdgcn_permlane16_swap(k, k, false, false);
+        const uint32_t k1 = (lane & 16) ? x1[0] : x1[1];                           // what lane ^ 16 holds; k2, k3: lane ^ 32, lane ^ 48
+        const auto x2 = __builtin_amdgcn_permlane32_swap(k, k, false, false), x3 = __builtin_amdgcn_permlane32_swap(k1, k1, false, false);
+        const uint32_t k2 = (lane & 32) ? x2[0] : x2[1], k3 = (lane & 32) ? x3[0] : x3[1];
+        const bool e1 = k1 == k, e2 = k2 == k, e3 = k3 == k;
+        int slot = 0;
+        if (!__any(e1 || e2 || e3)) {
+            if (mine) slot = atomicAdd(count + key, 1);
+            return slot;
+        }
+        const int g = lane >> 4;
+        const int rank = (e1 && (g & 1)) + (e2 && (g & 2)) + (e3 && (g & 2));      // (g ^ 3 < g: g is 2 or 3)
+        int lead = g;
+        if (e1) lead = min(lead, g ^ 1);
+        if (e2) lead = min(lead, g ^ 2);
+        if (e3) lead = min(lead, g ^ 3);
+        if (mine && rank == 0) slot = atomicAdd(count + key, 1 + e1 + e2 + e3);
+        return __shfl(slot, (lead << 4) | sub) + rank;
+    };
     Entry ent[KEEPC];
     float dP[KEEPC];
     int slot[KEEPC];
@@ -1003,7 +1032,8 @@ __global__ __launch_bounds__(256) void bwd_rows_kernel(Params p) {
         const int i = 16 * C + L::entry_of(sub);
         ent[C] = load_entry(i);
         slot[C] = 0;
-        if (i < tot) slot[C] = atomicAdd(&p.kcnt[(long)bh * N + ent[C].key], 1);
+        if constexpr (C == 0) slot[C] = take_slots_together(ent[C].key, i < tot);
+        else if (i < tot) slot[C] = atomicAdd(count + ent[C].key, 1);
         dP[C] = chunk_dP(ent[C].key, nmax - 16 * C);
         num = fmaf(ent[C].u, dP[C], num);
         den += ent[C].u;
@@ -1017,18 +1047,30 @@ __global__ __launch_bounds__(256) void bwd_rows_kernel(Params p) {
     den = group_sum<16>(den);
     const float delta = den > 0.f ? num / den : 0.f;
 
+    // this row's segment of the log (the work-group's rows lie in one)
+    const int seg = row / LOG_ROWS, seg_room = LOG_PER_ROW * min(LOG_ROWS, N - seg * LOG_ROWS);
+    LogEntry* const log = p.klog + ((size_t)bh * N + (size_t)seg * LOG_ROWS) * LOG_PER_ROW;
+    auto log_entries = [&](unsigned long long which, uint32_t key, int sl, float dS, float pr) {
+        const int lead = __ffsll((long long)which) - 1;
+        int at = 0;
+        if (lane == lead) at = atomicAdd(&p.log_cnt[bh * MAX_LOG_SEGMENTS + seg], __popcll(which));
+        at = __builtin_amdgcn_readlane(at, lead) + __popcll(which & ((1ull << lane) - 1ull));
+        if (!((which >> lane) & 1)) return;
+        const uint32_t past = (uint32_t)(sl - KEY_LIST_CAP);
+        if (at < seg_room)                             // (always: see gather_budget)
+            log[at] = LogEntry{key | past << ROW_BITS, (uint32_t)row | past >> SLOT_LOW_BITS << ROW_BITS, dS, pr};
+        if (past == 0u) p.hub_key[(long)bh * N + atomicAdd(&p.hub_cnt[bh], 1)] = (int32_t)key;
+    };
     float x[EPT];
-    int ndefer = 0;
 #pragma unroll
     for (int k = 0; k < EPT; ++k) x[k] = 0.f;
     // file a chunk's entries under their keys and add their share of dQ
-    auto finish_chunk = [&](const Entry& e, float dPe, int sl, int i0) {
+    auto finish_chunk = [&](const Entry& e, float dPe, int sl, int i0) __attribute__((always_inline)) {
         const float dS = e.key == NO_ENTRY ? 0.f : e.u * (dPe - delta);
         const int i = i0 + L::entry_of(sub);
-        if (i < tot) {
-            if (sl < KEY_LIST_CAP) ((KeyEntry*)p.klist)[((long)bh * N + e.key) * KEY_LIST_CAP + sl] = KeyEntry{(uint32_t)row, dS, e.pr};
-            else { *(uint32_t*)(entry_ptr(i) + 4) = e.key | 0x80000000u; ndefer = 1; }
-        }
+        if (i < tot && sl < KEY_LIST_CAP) ((KeyEntry*)p.klist)[((long)bh * N + e.key) * KEY_LIST_CAP + sl] = KeyEntry{(uint32_t)row, dS, e.pr};
+        const unsigned long long past = __ballot(i < tot && sl >= KEY_LIST_CAP);
+        if (past) log_entries(past, e.key, sl, dS, e.pr);
         unroll_steps<L::STEPS / BT>([&](auto b) {
             constexpr int S0 = decltype(b)::value * BT;
             if (S0 * L::PAR >= nmax - i0) return;
@@ -1045,87 +1087,225 @@ __global__ __launch_bounds__(256) void bwd_rows_kernel(Params p) {
     for (int i0 = 16 * KEEPC; i0 < nmax; i0 += 16) {
         const Entry e = load_entry(i0 + L::entry_of(sub));
         int sl = 0;
-        if (i0 + L::entry_of(sub) < tot) sl = atomicAdd(&p.kcnt[(long)bh * N + e.key], 1);
+        if (i0 + L::entry_of(sub) < tot) sl = atomicAdd(count + e.key, 1);
         finish_chunk(e, chunk_dP(e.key, nmax - i0), sl, i0);
     }
 #pragma unroll
     for (int k = 0; k < EPT; ++k) x[k] = L::halves_sum(x[k]) * p.inv_sqrt_d;
     L::store(p.dQ + gi * D, x, sub);
-    const unsigned long long deferred = __ballot(ndefer != 0);
     if (sub == 0) {
         p.delta[gi] = -delta / amax;
         p.ntau[gi] = -tau / hc.rho;
-        p.defer[gi] = __popcll((deferred >> (lane & 48)) & 0xffffull);
     }
 }
 
-// The entries bwd_rows_kernel marked: keys that more rows attend to than a key's list holds.  Run
-// after bwd_cols_kernel; a work-group looks through the rows of one row group for deferred entries (most
-// groups hold none and leave after one load per row); sixteen lanes then take a row at a time,
-// recompute the entry's dS and P (delta is the row's stored one) and add its share to the key's
-// rows of dK, dV with fp32 atomics, lane-interleaved
-// (lane `sub` takes elements sub, sub + 16, ...: an instruction then covers whole 64-byte pieces).
-template <class E, int D, int AM, bool SCALED>
-__global__ __launch_bounds__(256) void bwd_hot_kernel(Params p) {
-    using elem = typename E::elem;
-    constexpr int EPT = D / 16, MAX_GROWS = 128;
-    typedef elem vvec __attribute__((ext_vector_type(EPT)));
-    __shared__ int rows_s[MAX_GROWS];
-    __shared__ int nrows;
-    const int tid = threadIdx.x, sub = tid & 15, rsel = tid >> 4;
-    const int N = p.N, G = (N + p.grows - 1) / p.grows;
-    int bh, I;
-    map_block(blockIdx.x, p.BH, G, bh, I);
-    if (!p.gflag[(long)bh * G + I]) return;
-    if (tid == 0) nrows = 0;
-    __syncthreads();
-    if (tid < p.grows && I * p.grows + tid < N && p.defer[(long)bh * N + I * p.grows + tid] != 0) rows_s[atomicAdd(&nrows, 1)] = I * p.grows + tid;
-    __syncthreads();
-    if (nrows == 0) return;
-    const HeadConsts hc = head_consts(p, bh);
-    const float c = hc.c, r = hc.r;
-    float amax = 1.f;
-    if constexpr (SCALED) {
-        amax = __uint_as_float(p.scal[0]);
-        if (!(amax > 0.f)) amax = 1.f;
+// The log by key: where each hub key's part of hub_index starts (by the keys' counts in the order they were
+// reported; every work-group of a head forms the same offsets for itself), and the log entries' places there.
+// Keys with more entries than HUB_BATCH are summed from the log segments themselves.  Nothing to do, and gone
+// after one load, in heads without hub keys.
+constexpr int FILE_GROUPS = 16;          // work-groups per head
+constexpr int HUB_BATCH = 1024;          // entries of a hub key that are put in order in LDS at a time
+static __global__ __launch_bounds__(256) void bwd_file_kernel(Params p) {
+    __shared__ int wsum[4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int N = p.N, bh = blockIdx.x / FILE_GROUPS, part = blockIdx.x % FILE_GROUPS;
+    const int n = p.hub_cnt[bh];
+    if (n == 0) return;
+    const long hk = (long)bh * N;
+    int before = 0;
+    for (int i0 = 0; i0 < n; i0 += 256) {
+        const int i = i0 + tid;
+        int key = 0, len = 0;
+        if (i < n) {
+            key = p.hub_key[hk + i];
+            const int cnt = p.kcnt[hk + key];
+            if (cnt <= HUB_BATCH) len = cnt - KEY_LIST_CAP;
+        }
+        int incl = len;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int t = __shfl_up(incl, off);
+            if (lane >= off) incl += t;
+        }
+        if (lane == 63) wsum[wave] = incl;
+        __syncthreads();
+        int at = before + incl - len;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            at += w < wave ? wsum[w] : 0;
+            before += wsum[w];
+        }
+        if (i < n) p.hub_off[hk + key] = at;
+        __syncthreads();
     }
-    const long hoff = (long)bh * N * D;
-    const elem* Qh = (const elem*)p.Q + hoff;
-    const elem* Vh = (const elem*)p.V + hoff + sub * EPT;
-    const elem* Gh = (const elem*)p.dO + hoff;
-    const int cap8 = p.list_cap * 8;
-    const char* lists_h = (const char*)p.lists + (size_t)bh * N * (size_t)(2 * cap8);
-    for (int q = rsel; q < nrows; q += 16) {
-        const int row = rows_s[q];
-        const long gi = (long)bh * N + row;
-        const float tau = p.tau[gi], delta = -p.delta[gi] * amax;
-        const int s0 = p.scnt[gi * 2], tot = s0 + p.scnt[gi * 2 + 1];
-        char* l0 = const_cast<char*>(lists_h) + (size_t)row * (size_t)(2 * cap8);
-        const vvec gv = *(const vvec*)(Gh + (long)row * D + sub * EPT);
-        for (int i = 0; i < tot; ++i) {
-            char* ep = l0 + (i < s0 ? i * 8 : cap8 + (i - s0) * 8);
-            const uint2 e = *(const uint2*)ep;
-            if (!(e.y >> 31)) continue;
-            const uint32_t key = e.y & 0x7fffffffu;
-            // the mark comes off again: the lists are left as they were found (they may be the forward's)
-            if (sub == 0) *(uint32_t*)(ep + 4) = key;
-            const vvec vv = *(const vvec*)(Vh + (long)key * D);
-            float dot = 0.f;
+    // the offsets are read back by other threads of this work-group: its stores have reached the L2, and
+    // the loads go there
+    wait_loads();
+    __syncthreads();
+    uint32_t* const index = p.hub_index + (size_t)bh * N * LOG_PER_ROW;
+    for (int seg = 0; seg * LOG_ROWS < N; ++seg) {
+        const int m = min(p.log_cnt[bh * MAX_LOG_SEGMENTS + seg], LOG_PER_ROW * min(LOG_ROWS, N - seg * LOG_ROWS));
+        const uint32_t first = (uint32_t)(seg * LOG_ROWS) * LOG_PER_ROW;
+        for (int e = part * 256 + tid; e < m; e += FILE_GROUPS * 256) {
+            const LogEntry* le = p.klog + (size_t)bh * N * LOG_PER_ROW + first + e;
+            const uint32_t key = le->key_slot & ((1u << ROW_BITS) - 1), past = le->key_slot >> ROW_BITS | le->row_slot >> ROW_BITS << SLOT_LOW_BITS;
+            if (p.kcnt[hk + key] > HUB_BATCH) continue;
+            index[__hip_atomic_load(&p.hub_off[hk + key], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + (int)past] = first + e;
+        }
+    }
+}
+
+// dK or dV of one hub key by a whole work-group: its entries in the order of their query rows in LDS, up to
+// HUB_BATCH of them at once, a run of them for every sixteen lanes, and the sixteen partial sums added in order.
+// Up to HUB_BATCH entries are ranked against each other; a key with more is worked off by segments of LOG_ROWS
+// rows, whose entries have a place each by their row.
+// Bound: one work-group reads the rows of a key's entries (2 D bytes each), so that a sink takes as long as its
+// rows take at one CU's rate.  Backward of 32 heads of 16384 tokens (d = 128) with one sink 8640 -> 800 us, 8 heads of
+// 65536 7460 -> 1550 us, against fp32 atomics on the key's rows, whose sums changed from run to run besides; steps with
+// a few hundred small hub keys: 16384 tokens, sigma = 1, 4664 -> 4529, 65536 planted 4250 -> 4146 us.
+template <class E, int D> struct HubLds {
+    uint32_t row[HUB_BATCH];             // in order
+    float w[HUB_BATCH];
+    union {
+        struct { uint32_t filed_row[HUB_BATCH]; float filed_w[HUB_BATCH]; };    // as they were filed
+        struct {
+            float by_row[LOG_ROWS];      // a segment's entries at their row's place,
+            uint32_t bits[LOG_ROWS / 32];               // which rows are there, and how many before each word
+            int before[LOG_ROWS / 32 + 1];
+        };
+        float part[16][D];
+    };
+};
+// Work-groups per head: about two per CU over all heads (those of heads without hub keys cost a work-group's launch each:
+// 64 heads of 4096 tokens, 32 per head against 8: 1.5 us)
+__host__ __device__ constexpr int hub_groups(int BH) { return BH >= 128 ? 4 : BH <= 8 ? 64 : 512 / BH; }
+template <class E, int D>
+EA_DEV void hub_key_sums(const Params& p, HubLds<E, D>& s, int bh, int first_item, int groups, bool fresh) {
+    using elem = typename E::elem;
+    using L = GatherLanes<E, D>;
+    using vec = typename L::vec;
+    constexpr int EPT = L::EPT, BT = 4;
+    static_assert(HUB_BATCH <= 4 * 256 && LOG_ROWS <= HUB_BATCH && LOG_ROWS / 32 < 64, "a segment is a batch, its bits are at most a word per lane");
+    const int tid = threadIdx.x, sub = tid & 15, group = tid >> 4, lane = tid & 63;
+    const int N = p.N, n = p.hub_cnt[bh];
+    const long hk = (long)bh * N;
+    const LogEntry* const log = p.klog + (size_t)hk * LOG_PER_ROW;
+    const uint32_t* const index = p.hub_index + (size_t)hk * LOG_PER_ROW;
+    constexpr uint32_t ROW_MASK = (1u << ROW_BITS) - 1;
+    for (int item = first_item; item < 2 * n; item += groups) {
+        const uint32_t key = (uint32_t)p.hub_key[hk + (item >> 1)];
+        const bool is_dk = !(item & 1);
+        const int cnt = p.kcnt[hk + key];
+        const KeyEntry* const el = (const KeyEntry*)p.klist + (hk + key) * KEY_LIST_CAP;
+        const elem* const rows = (const elem*)(is_dk ? p.Q : p.dO) + hk * D + L::column(sub);
+        float acc[EPT];
 #pragma unroll
-            for (int k = 0; k < EPT; ++k) dot = fmaf((float)gv[k], (float)vv[k], dot);
-            const float dP = group_sum<16>(dot);
-            const float y = fmaf(c, __uint_as_float(e.x), -tau);
-            const float uu = y > 0.f ? pow_r1<AM>(y, r) : 0.f;
-            const float pr = y > 0.f ? pow_r<AM>(y, r) : 0.f;
-            const float ds = uu * (dP - delta) * p.inv_sqrt_d;
-            float* dk = p.dK + ((long)bh * N + key) * D + sub;
-            float* dv = p.dV + ((long)bh * N + key) * D + sub;
+        for (int k = 0; k < EPT; ++k) acc[k] = 0.f;
+        // sum of the m entries now in s.row, s.w, added to acc
+        auto add_batch = [&](int m) {
+            const int share = (m + 15) / 16, mine = min(max(m - group * share, 0), share);
+            int nmin, nmax;
+            list_range(mine, nmin, nmax);
+            for (int i0 = 0; i0 < nmax; i0 += 16) {
+                const int i = i0 + L::entry_of(sub);
+                uint32_t row = NO_ENTRY;
+                float w = 0.f;
+                if (i < mine) { row = s.row[group * share + i]; w = s.w[group * share + i]; }
+                unroll_steps<L::STEPS / BT>([&](auto b) {
+                    constexpr int S0 = decltype(b)::value * BT;
+                    if (S0 * L::PAR >= nmax - i0) return;
+                    vec v[BT];
+                    unroll_steps<BT>([&](auto u) { v[decltype(u)::value] = *(const vec*)(rows + (size_t)(L::template of_step<S0 + decltype(u)::value>(row) * (uint32_t)D)); });
+                    if ((S0 + BT) * L::PAR > nmin - i0) unroll_steps<BT>([&](auto u) { clear_absent(L::template of_step<S0 + decltype(u)::value>(row), v[decltype(u)::value]); });
+                    unroll_steps<BT>([&](auto u) { add_scaled<EPT>(acc, L::template of_step<S0 + decltype(u)::value>(w), v[decltype(u)::value]); });
+                });
+            }
+        };
+        if (cnt <= HUB_BATCH) {
+            const int off = p.hub_off[hk + key];
+            for (int i = tid; i < cnt; i += 256) {
+                uint32_t row;
+                float w;
+                if (i < KEY_LIST_CAP) { row = el[i].row; w = is_dk ? el[i].dS : el[i].pr; }
+                else {
+                    const LogEntry le = log[min(index[off + i - KEY_LIST_CAP], (uint32_t)N * LOG_PER_ROW - 1u)];
+                    row = le.row_slot & ROW_MASK; w = is_dk ? le.dS : le.pr;
+                }
+                s.filed_row[i] = row; s.filed_w[i] = w;
+            }
+            __syncthreads();
+            if (tid < cnt) {
+                uint32_t row[4];
+                int rank[4];
 #pragma unroll
-            for (int k = 0; k < EPT; ++k) {
-                unsafeAtomicAdd(dk + 16 * k, ds * (float)Qh[(long)row * D + sub + 16 * k]);
-                unsafeAtomicAdd(dv + 16 * k, pr * (float)Gh[(long)row * D + sub + 16 * k]);
+                for (int q = 0; q < 4; ++q) { row[q] = s.filed_row[min(tid + 256 * q, cnt - 1)]; rank[q] = 0; }
+                for (int j = 0; j < cnt; ++j) {
+                    const uint32_t rj = s.filed_row[j];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) rank[q] += rj < row[q];
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (tid + 256 * q < cnt) { s.row[rank[q]] = row[q]; s.w[rank[q]] = s.filed_w[tid + 256 * q]; }
+            }
+            __syncthreads();
+            add_batch(cnt);
+        } else {
+            for (int seg = 0; seg * LOG_ROWS < N; ++seg) {
+                const int r0 = seg * LOG_ROWS;
+                if (tid < LOG_ROWS / 32) s.bits[tid] = 0u;
+                __syncthreads();
+                auto put = [&](uint32_t row, float w) {
+                    const uint32_t at = row - (uint32_t)r0;
+                    s.by_row[at] = w;
+                    atomicOr(&s.bits[at >> 5], 1u << (at & 31));
+                };
+                if (tid < KEY_LIST_CAP && (int)(el[tid].row / LOG_ROWS) == seg) put(el[tid].row, is_dk ? el[tid].dS : el[tid].pr);
+                const int m = min(p.log_cnt[bh * MAX_LOG_SEGMENTS + seg], LOG_PER_ROW * min(LOG_ROWS, N - r0));
+                for (int i = tid; i < m; i += 256) {
+                    const LogEntry* le = log + (size_t)r0 * LOG_PER_ROW + i;
+                    if ((le->key_slot & ROW_MASK) == key) put(le->row_slot & ROW_MASK, is_dk ? le->dS : le->pr);
+                }
+                __syncthreads();
+                if (tid < 64) {
+                    const int c = lane < LOG_ROWS / 32 ? __popc(s.bits[lane]) : 0;
+                    int incl = c;
+#pragma unroll
+                    for (int off = 1; off < 64; off <<= 1) {
+                        const int t = __shfl_up(incl, off);
+                        if (lane >= off) incl += t;
+                    }
+                    if (lane <= LOG_ROWS / 32) s.before[lane] = incl - c;
+                }
+                __syncthreads();
+#pragma unroll
+                for (int q = 0; q < LOG_ROWS / 256; ++q) {
+                    const int at = tid + 256 * q;
+                    const uint32_t word = s.bits[at >> 5], bit = 1u << (at & 31);
+                    if (word & bit) {
+                        const int pos = s.before[at >> 5] + __popc(word & (bit - 1u));
+                        s.row[pos] = (uint32_t)(r0 + at);
+                        s.w[pos] = s.by_row[at];
+                    }
+                }
+                __syncthreads();
+                add_batch(s.before[LOG_ROWS / 32]);
+                __syncthreads();
             }
         }
+#pragma unroll
+        for (int k = 0; k < EPT; ++k) acc[k] = L::halves_sum(acc[k]);
+        L::store(s.part[group], acc, sub);
+        __syncthreads();
+        if (tid < D) {
+            float sum = 0.f;
+#pragma unroll
+            for (int g = 0; g < 16; ++g) sum += s.part[g][tid];
+            if (is_dk) sum *= p.inv_sqrt_d;
+            float* out = (is_dk ? p.dK : p.dV) + (hk + key) * D + tid;
+            *out = fresh ? sum : *out + sum;
+        }
+        __syncthreads();
     }
 }
 
@@ -1136,10 +1316,10 @@ __global__ __launch_bounds__(256) void bwd_hot_kernel(Params p) {
 // changes from run to run.  They are summed in the order of their query rows instead (a row files
 // at most one entry per key, so the rows are distinct): every lane holds one entry in sixteen, finds
 // its rank among the key's rows through LDS and leaves it there in its place, and dK, dV of a key come
-// out bit-identical in every run (keys with more entries than a list holds get the rest from
-// bwd_hot_kernel's atomic additions and do not).
+// out bit-identical in every run.  The first work-groups (hub_groups per head) take the hub keys, which the others
+// pass over.
 template <class E, int D>
-__global__ __launch_bounds__(256) void bwd_cols_kernel(Params p) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(typename E::elem) == 2 || D == 64 ? 6 : 5))) void bwd_cols_kernel(Params p) {
     using elem = typename E::elem;
     using L = GatherLanes<E, D>;
     using vec = typename L::vec;
@@ -1147,19 +1327,25 @@ __global__ __launch_bounds__(256) void bwd_cols_kernel(Params p) {
     typedef float f4 __attribute__((ext_vector_type(4)));
     static_assert(BWD_COLS_KEYS == 16, "one key per sixteen lanes");
     constexpr int PER_LANE = KEY_LIST_CAP / 16;        // entries of a key's list per lane of its 16
-    __shared__ uint32_t row_s[16][KEY_LIST_CAP];
-    __shared__ float2 val_s[16][KEY_LIST_CAP];
+    struct KeyLds { uint32_t row[16][KEY_LIST_CAP]; float2 val[16][KEY_LIST_CAP]; };
+    __shared__ union { KeyLds keys; HubLds<E, D> hub; } lds;
+    auto& row_s = lds.keys.row;
+    auto& val_s = lds.keys.val;
     const int tid = threadIdx.x, sub = tid & 15, rsel = tid >> 4;
-    const int N = p.N, G = (N + BWD_COLS_KEYS - 1) / BWD_COLS_KEYS;
+    const int N = p.N, G = (N + BWD_COLS_KEYS - 1) / BWD_COLS_KEYS, HG = hub_groups(p.BH), hub_blocks = p.BH * HG;
+    const bool fresh = *p.nplain == 0;
+    if ((int)blockIdx.x < hub_blocks) {
+        hub_key_sums<E, D>(p, lds.hub, blockIdx.x / HG, blockIdx.x % HG, HG, fresh);
+        return;
+    }
     int bh, I;
-    map_block(blockIdx.x, p.BH, G, bh, I);
+    map_block((int)blockIdx.x - hub_blocks, p.BH, G, bh, I);
     const int key = I * BWD_COLS_KEYS + rsel;
     if (key >= N) return;                              // (N is a multiple of 64: whole work-groups)
     const long kj = (long)bh * N + key, hoff = (long)bh * N * D;
     const elem* Qh = (const elem*)p.Q + hoff + L::column(sub);
     const elem* Gh = (const elem*)p.dO + hoff + L::column(sub);
-    const bool fresh = *p.nplain == 0;
-    const int cnt = min(p.kcnt[kj], KEY_LIST_CAP);
+    const int filed = p.kcnt[kj], cnt = filed > KEY_LIST_CAP ? 0 : filed;
     int nmin, nmax;
     list_range(cnt, nmin, nmax);
     if (nmax == 0 && !fresh) return;
@@ -1233,7 +1419,7 @@ __global__ __launch_bounds__(256) void bwd_cols_kernel(Params p) {
             });
         });
     }
-    if (cnt == 0 && !fresh) return;
+    if (filed > KEY_LIST_CAP || (cnt == 0 && !fresh)) return;
 #pragma unroll
     for (int k = 0; k < EPT; ++k) { ak[k] = L::halves_sum(ak[k]) * p.inv_sqrt_d; av[k] = L::halves_sum(av[k]); }
     float* dk = p.dK + kj * D;
@@ -1251,8 +1437,8 @@ __global__ __launch_bounds__(256) void bwd_cols_kernel(Params p) {
     L::store(dv, av, sub);
 }
 
-// What the backward starts from, in one launch (three of them cost 4 - 5 us each): cleared key counters (and the
-// counter of plain row groups behind them), cleared statistics (stats null: they are cleared already), and the
+// What the backward starts from, in one launch (three of them cost 4 - 5 us each): cleared key counters (and behind them
+// the counters of plain row groups, hub keys and log entries), cleared statistics (stats null: they are cleared already), and the
 // set bits of the mask, a partial sum for each of the first MASK_PARTS blocks.
 static __global__ __launch_bounds__(256) void bwd_begin_kernel(int32_t* counters, long n, unsigned long long* stats, int nstats, unsigned int* scal,
                                                                const int32_t* mask, long nwords, int32_t* mask_parts) {

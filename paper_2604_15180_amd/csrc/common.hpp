@@ -42,6 +42,12 @@ constexpr int MASK_PARTS = 64;
 
 // An entry of a key's list: the query row and its dS and P there.
 struct KeyEntry { uint32_t row; float dS, pr; };
+// Keys that more rows attend to than a list holds (hub keys): what does not fit goes to a log, a segment of it
+// per LOG_ROWS query rows of a head, with room for all entries those rows can have (gather_budget).
+// key_slot holds the key and the low bits of the entry's slot in the key's list, row_slot the row and the high bits.
+struct LogEntry { uint32_t key_slot, row_slot; float dS, pr; };
+constexpr int LOG_ROWS = 1024, LOG_PER_ROW = GATHER_SUP_MAX, MAX_LOG_SEGMENTS = MAX_T * 64 / LOG_ROWS;
+constexpr int ROW_BITS = 17, SLOT_LOW_BITS = 32 - ROW_BITS;
 
 constexpr int ALPHA_15 = 0, ALPHA_20 = 1, ALPHA_GEN = 2;
 constexpr int LIST_CAP = 256;   // candidate entries per (row, lane half)
@@ -90,8 +96,13 @@ struct Params {
     int32_t* kcnt;        // backward [BH][N]: entries in each key's list
     int32_t* nplain;      // backward: number of row groups that stay with dq_kernel / dkdv_kernel
     int32_t* mask_parts;  // backward [MASK_PARTS]: set bits of the whole mask, partial sums
-    int32_t* defer;       // backward [BH][N]: entries of the row left to bwd_hot_kernel
     void* klist;          // backward [BH][N][KEY_LIST_CAP] KeyEntry
+    LogEntry* klog;       // backward [BH][N][LOG_PER_ROW], in segments of LOG_ROWS rows (where the 16-bit copies were: they are read no more)
+    int32_t* log_cnt;     // backward [BH][MAX_LOG_SEGMENTS]: entries in each segment
+    int32_t* hub_cnt;     // backward [BH]: hub keys of the head
+    int32_t* hub_key;     // backward [BH][N]: the hub keys
+    int32_t* hub_off;     // backward [BH][N]: where a hub key's part of hub_index starts
+    uint32_t* hub_index;  // backward [BH][N][LOG_PER_ROW]: log entries by key (where the backward's own row lists were)
     int32_t* oflag;       // [BH][T] 1 = some row of this 64-row block has more candidates than its lists hold
     unsigned long long* stats;
     // bits of non-negative floats kept in the workspace (atomicMax on the bit patterns):

@@ -133,7 +133,7 @@ struct Ops {
         if (p.gflag) {
             ScopedKernelTime t(EA_TIMER_BWD_LIST, s);
             static_assert((32 * QBB * NW_BLIST) % (32 * QB * NW_DQ) == 0 && (32 * QBB * NW_BLIST) % 64 == 0, "a dQ group and a query tile lie inside one row group");
-            hipLaunchKernelGGL(bwd_begin_kernel, dim3(256), dim3(256), 0, s, p.kcnt, (long)p.BH * p.N + 1,      // (nplain is right behind)
+            hipLaunchKernelGGL(bwd_begin_kernel, dim3(256), dim3(256), 0, s, p.kcnt, (long)p.BH * (p.N + 1 + MAX_LOG_SEGMENTS) + 1,      // (nplain, hub_cnt, log_cnt are right behind)
                                rebuild_mask ? nullptr : p.stats, STATS_WORDS * STATS_COPIES, p.scal, p.mask, (long)p.BH * p.T * p.W, p.mask_parts);
             EA_HIP(hipGetLastError());
             if (p.fwd_gflag) {
@@ -186,10 +186,10 @@ struct Ops {
             ScopedKernelTime t(EA_TIMER_BWD_GATHER, s);
             rc = launch(bwd_rows_kernel<E, D, AM, E2::SCALED>, dim3(p.BH * ((p.N + p.grows - 1) / p.grows) * (p.grows / GATHER_ROWS)), 256, s, po);
             if (rc) return rc;
-            rc = launch(bwd_cols_kernel<E, D>, dim3(p.BH * ((p.N + BWD_COLS_KEYS - 1) / BWD_COLS_KEYS)), 256, s, po);
+            static_assert(LOG_ROWS % GATHER_ROWS == 0 && LOG_ROWS % (32 * QBB * NW_BLIST) == 0, "row groups do not straddle log segments");
+            rc = launch(bwd_file_kernel, dim3(p.BH * FILE_GROUPS), 256, s, po);
             if (rc) return rc;
-            static_assert(32 * QBB * NW_BLIST <= 128, "rows of a group bwd_hot_kernel looks through");
-            rc = launch(bwd_hot_kernel<E, D, AM, E2::SCALED>, dim3(p.BH * ((p.N + p.grows - 1) / p.grows)), 256, s, po);
+            rc = launch(bwd_cols_kernel<E, D>, dim3(p.BH * ((p.N + BWD_COLS_KEYS - 1) / BWD_COLS_KEYS + hub_groups(p.BH))), 256, s, po);
             if (rc) return rc;
         }
         return EA_OK;
