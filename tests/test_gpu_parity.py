@@ -292,10 +292,7 @@ def test_sparse_row_groups_gather_their_gradients(ea, dtype, d, alpha, sigma, ma
         dQ2, _, _ = ea.entmax_attn_bwd(Q, K, V, O, dO, tau, alpha, causal, block_mask=mask, workspace=ws, fwd_workspace=wf)
         torch.cuda.synchronize()
         assert torch.equal(dQ, dQ2)
-    # (fp32 inputs: at the score scale where fp32 scores allow the 1e-5 bar no row group is sparse
-    # enough; the fp32 gather path at a larger scale is checked against the matrix path in
-    # test_gather_and_matrix_paths_agree)
-    assert st["bwd_gather_rows"] > 0 or dtype == "f32"
+    assert st["bwd_gather_rows"] > 0
     ref, _ = parity.check_forward(q, k, v, alpha, causal, O, tau, mask, label=f"fwd {dtype} {alpha}")
     _, ginfo = parity.check_backward(q, k, v, do, alpha, causal, dQ, dK, dV, label=f"bwd gather {dtype} {alpha}", tau_ref=ref["tau"])
     print("  ", ginfo, flush=True)
@@ -388,8 +385,8 @@ def test_keys_that_many_rows_attend_to(ea, dtype, d, N, sigma, causal, hubs):
     torch.cuda.synchronize()
     st = ea.read_stats(ws)
     print("  backward gather rows", st["bwd_gather_rows"], "of", B * H * N, flush=True)
+    assert st["bwd_gather_rows"] > 0
     if dtype == "bf16" and d == 128:
-        assert st["bwd_gather_rows"] > 0
         # once more from the forward's lists
         g2 = ea.entmax_attn_bwd(Q, K, V, O, dO, tau, alpha, causal, block_mask=mask, workspace=ws, fwd_workspace=wf)
         torch.cuda.synchronize()
@@ -397,8 +394,44 @@ def test_keys_that_many_rows_attend_to(ea, dtype, d, N, sigma, causal, hubs):
         for name, a, b in zip(("dQ", "dK", "dV"), (dQ, dK, dV), g2):
             assert ((a - b).abs() / (1 + a.abs())).max().item() <= 1e-4, name
     ref, _ = parity.check_forward(q, k, v, alpha, causal, O, tau, mask, label="hubs")
-    _, ginfo = parity.check_backward(q, k, v, do, alpha, causal, dQ, dK, dV, label="hubs", tau_ref=ref["tau"])
+    gref, ginfo = parity.check_backward(q, k, v, do, alpha, causal, dQ, dK, dV, label="hubs", tau_ref=ref["tau"])
     print("  ", ginfo, flush=True)
+    try:
+        ea.entmax_attn_gather_enable(False)
+        g3 = ea.entmax_attn_bwd(Q, K, V, O, dO, tau, alpha, causal, block_mask=mask, workspace=ws)
+        torch.cuda.synchronize()
+    finally:
+        ea.entmax_attn_gather_enable(True)
+    assert ea.read_stats(ws)["bwd_gather_rows"] == 0
+    _, ginfo = parity.check_backward(q, k, v, do, alpha, causal, *g3, ref=gref, label="hubs on the matrix kernels", tau_ref=ref["tau"])
+    print("   matrix kernels", ginfo, flush=True)
+
+
+@pytest.mark.parametrize("dtype,d,N,alpha,sigma,causal", [("bf16", 64, 576, 1.25, 1.5, True), ("bf16", 128, 320, 1.75, 1.5, False), ("bf16", 64, 512, 2.0, 2.0, True),
+                                                          ("bf16", 128, 448, 2.5, 2.0, True), ("f32", 64, 320, 1.25, 1.0, True), ("f32", 128, 192, 2.0, 1.0, False),
+                                                          ("bf16", 64, 320, (1.25, 1.5, 2.0), 1.5, True), ("bf16", 128, 192, (2.5, 1.1, 3.0), 1.5, False)])
+def test_matrix_kernels_alone(ea, dtype, d, N, alpha, sigma, causal):
+    # inputs that the gather path takes when it may, with it switched off: dq_kernel and dkdv_kernel serve every row group
+    H = 3 if isinstance(alpha, tuple) else 2
+    q, k, v, do = workloads.gaussian_qkv(1, H, N, d, dtype, sigma, seed=141)
+    Q, K, V, dO = (t.cuda() for t in (q, k, v, do))
+    ws = torch.empty(ea.entmax_attn_workspace_bytes(1, H, N, d, dtype, causal, True), dtype=torch.uint8, device="cuda")
+    arg = list(alpha) if isinstance(alpha, tuple) else alpha
+    try:
+        ea.entmax_attn_gather_enable(False)
+        O, tau, mask = ea.entmax_attn_fwd(Q, K, V, arg, causal)
+        dQ, dK, dV = ea.entmax_attn_bwd(Q, K, V, O, dO, tau, arg, causal, block_mask=mask, workspace=ws)
+        torch.cuda.synchronize()
+    finally:
+        ea.entmax_attn_gather_enable(True)
+    assert ea.read_stats(ws)["bwd_gather_rows"] == 0
+    for h in range(H):
+        a = alpha[h] if isinstance(alpha, tuple) else alpha
+        sl = slice(h, h + 1)
+        ref, info = parity.check_forward(q[:, sl], k[:, sl], v[:, sl], a, causal, O[:, sl], tau[:, sl], mask[:, sl], label=f"matrix {a}")
+        _, ginfo = parity.check_backward(q[:, sl], k[:, sl], v[:, sl], do[:, sl], a, causal, dQ[:, sl], dK[:, sl], dV[:, sl],
+                                         label=f"matrix {a}", tau_ref=ref["tau"])
+        print(f"  alpha {a}", info, ginfo, flush=True)
 
 
 @pytest.mark.parametrize("dtype,d,fwd_lists", [("bf16", 64, True), ("bf16", 128, False), ("f32", 64, False), ("f32", 128, True)])
