@@ -407,13 +407,13 @@ __global__ __launch_bounds__(NW * 64) void tau_kernel(Params p) {
 // A list that fills up (attention close to uniform: hundreds of non-zeros per row) flags its 64-row
 // block; flagged blocks are redone by the sweep-based tau_kernel, which runs right after and exits
 // at once everywhere else.
-// PAIR (one row per lane only): waves 2w and 2w+1 share the words of one histogram buffer, 16 bits
+// PAIR: waves 2w and 2w+1 share the words of one histogram buffer, 16 bits
 // each - what two rows per lane do within a wave - so that eight one-row waves need the LDS of
 // four and, with half the accumulator and operand registers, four waves fit a SIMD.
-template <class E, int D, int QB, int AM, int NB, int NW, int NBUF, int PAIR = 0>
+template <class E, int D, int AM, int NB, int NW, int NBUF, int PAIR = 0>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 4 : 1))) void tau_list_kernel(Params p) {
-    static_assert(QB == 1 && (!PAIR || NW % 2 == 0), "one row per lane; paired histograms: an even number of waves");
-    using SM = TauSmem<E, D, QB, NB, NW, NBUF>;
+    static_assert(!PAIR || NW % 2 == 0, "paired histograms: an even number of waves");
+    using SM = TauSmem<E, D, 1, NB, NW, NBUF>;
     using KT = RowTile<E, D>;
     using elem = typename E::elem;
     constexpr int THREADS = NW * 64, BR = SM::BR, MR = SM::MR, SLOTS = SM::SLOTS;
@@ -441,19 +441,19 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 
     const int N = p.N, T = p.T, W = p.W;
     int bh, I;
     map_block(blockIdx.x, p.BH, (N + BR - 1) / BR, bh, I);
-    const long q0 = (long)I * BR, qw0 = q0 + wave * 32 * QB;
+    const long q0 = (long)I * BR, qw0 = q0 + wave * 32;
     const bool active = qw0 < N;
     const elem* Qh = (const elem*)p.Q + (long)bh * N * D;
     const elem* Kh = (const elem*)p.K + (long)bh * N * D;
     const int njt = p.causal ? min((int)((q0 + BR) / 64), T) : T;
-    const int wjt = !active ? 0 : p.causal ? (int)((qw0 + 32 * QB - 1) / 64) + 1 : T;
-    const int myrow = (wave * 32 * QB) / 64;
+    const int wjt = !active ? 0 : p.causal ? (int)((qw0 + 31) / 64) + 1 : T;
+    const int myrow = (wave * 32) / 64;
     const HeadConsts hc = head_consts(p, bh);
     const float c = hc.c, r = hc.r;
     constexpr float hb = 1.f / NB;
 
-    Owned<E, D, QB> qf;
-    load_owned<E, D, QB>(qf, Qh, active ? qw0 : 0, lane);
+    Owned<E, D, 1> qf;
+    load_owned<E, D, 1>(qf, Qh, active ? qw0 : 0, lane);
     for (int i = tid; i < HIST_WORDS; i += THREADS) hist[i] = 0u;
 
     // this lane's list: byte offsets from the head's lists
@@ -623,174 +623,142 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 
     if (tid < MR) over_s[tid] = 0;
     if (tid < 4) gsum[tid] = 0;
     __syncthreads();
-    // The lists are read back below by the lanes that wrote them, for the first time in this kernel
-    // (no stale line can sit in the vector cache): it is enough that this wave's stores have
-    // completed.  A device-scope fence here writes the whole L2 back once per work-group, which
-    // cost 0.1 - 0.4 ms per launch.
+    // The lists are read back by the lanes that wrote them and by no others (here, in count_lists while the sweep
+    // goes on, and after the first evaluation has moved entries to the front): a wave's vector memory operations
+    // on one address take effect in program order, so no fence is needed.  A device-scope fence here writes the
+    // whole L2 back once per work-group, which cost 0.1 - 0.4 ms per launch.
     wait_loads();
 
     // ---- solve and refinement on the lists -----------------------------------------------------
     int any_over = 0;
-    float thr[QB];
-    int iters[QB], done[QB], mycnt[QB];
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) { thr[qb] = 0.f; iters[qb] = 0; done[qb] = 1; mycnt[qb] = 0; }
+    float thr = 0.f;
+    int iters = 0, done = 1, mycnt = 0;
     if (active) {
-        float blo[QB], bhi[QB];
+        float blo, bhi;
         if (!counting) count_lists();
-        histogram_bound(thr[0], bhi[0], false);
+        histogram_bound(thr, bhi, false);
         if (h == 0) {
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) {
-                p.rs_t0[(long)bh * N + qw0 + 32 * qb + n] = thr[qb];
-                p.rs_up0[(long)bh * N + qw0 + 32 * qb + n] = bhi[qb];
-            }
+            p.rs_t0[(long)bh * N + qw0 + n] = thr;
+            p.rs_up0[(long)bh * N + qw0 + n] = bhi;
         }
-        float f1_last[QB];
-        int nmax = 0;
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-            any_over |= (cnt > LIST_CAP);
-            mycnt[qb] = min(cnt, LIST_CAP);
-            nmax = max(nmax, mycnt[qb]);
-            blo[qb] = thr[qb]; iters[qb] = 0; done[qb] = 0; f1_last[qb] = -1.f;
-            if (p.right_edge) thr[qb] = bhi[qb];      // tau_h + h >= tau*: the right-edge root, taken as it is
-        }
+        float f1_last = -1.f;
+        any_over = cnt > LIST_CAP;
+        mycnt = min(cnt, LIST_CAP);
+        int nmax = mycnt;
+        blo = thr; done = 0;
+        if (p.right_edge) thr = bhi;      // tau_h + h >= tau*: the right-edge root, taken as it is
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) nmax = max(nmax, __shfl_xor(nmax, off));
         // refinement (Sec. 3.2): evaluations of f, f', f'' over the listed scores; each lane walks
-        // its own lists, sixteen entries per row block at a time with all loads in flight together.
+        // its own list, sixteen entries at a time with all loads in flight together.
         // The first evaluation, at tau_0 <= tau* (every later threshold lies above it), moves the entries it
         // finds above the threshold to the front of their list: those that follow read a fraction of it
         // (steps: sigma = 1, 16384 tokens, lists of about 120 entries, 4886 -> 4780 us; fp32, 256 tokens, 123 -> 113).
-        SecantPrev prev[QB];
+        SecantPrev prev;
         // (alpha > 2: a row with a score within the tolerance of its root ends up bisecting, since f
         // rises vertically there; the sweeps over the lists are cheap, those of the output kernel
         // are not, so the limit is doubled here)
         const int nsweeps = r < 1.f ? 2 * p.max_sweeps : p.max_sweeps;
         for (int sweep = 0; sweep < nsweeps; ++sweep) {
-            float F[QB], G[QB], Hs[QB];
-            uint32_t lastj[QB];
-            int front[QB];
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) { F[qb] = G[qb] = Hs[qb] = 0.f; lastj[qb] = 0xffffffffu; front[qb] = 0; }
+            float F = 0.f, G = 0.f, Hs = 0.f;
+            uint32_t lastj = 0xffffffffu;
+            int front = 0;
             for (int i0 = 0; i0 < nmax; i0 += 16) {
-                uint4 e[QB][8];
+                uint4 e[8];
 #pragma unroll
-                for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        e[qb][u] = make_uint4(0u, 0u, 0u, 0u);
-                        if (i0 + 2 * u < mycnt[qb]) e[qb][u] = *(const uint4*)(lptr + (i0 + 2 * u) * 8);
-                    }
+                for (int u = 0; u < 8; ++u) {
+                    e[u] = make_uint4(0u, 0u, 0u, 0u);
+                    if (i0 + 2 * u < mycnt) e[u] = *(const uint4*)(lptr + (i0 + 2 * u) * 8);
+                }
                 // (all sixteen are in registers before the first is overwritten; front <= i0 + u)
 #pragma unroll
-                for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-                    for (int u = 0; u < 16; ++u) {
-                        uint2 ent;
-                        ent.x = (u & 1) ? e[qb][u >> 1].z : e[qb][u >> 1].x;
-                        ent.y = (u & 1) ? e[qb][u >> 1].w : e[qb][u >> 1].y;
-                        const float y = fmaf(c, __uint_as_float(ent.x), -thr[qb]);
-                        if (i0 + u < mycnt[qb] && y > 0.f) {
-                            if constexpr (AM == ALPHA_15) { F[qb] = fmaf(y, y, F[qb]); G[qb] += y; Hs[qb] += 1.f; }
-                            else if constexpr (AM == ALPHA_20) { F[qb] += y; G[qb] += 1.f; }
-                            else {
-                                const float p2 = pow_r2<AM>(y, r);
-                                Hs[qb] += p2; G[qb] = fmaf(p2, y, G[qb]); F[qb] = fmaf(p2 * y, y, F[qb]);
-                            }
-                            if (sweep == 0) {
-                                *(uint2*)(lptr + 8 * front[qb]) = ent;
-                                ++front[qb];
-                                const uint32_t j = ent.y >> 6;            // its tiles are the working mask
-                                if (j != lastj[qb]) { atomicOr(&wm[myrow * W + (j >> 5)], 1u << (j & 31)); lastj[qb] = j; }
-                            }
+                for (int u = 0; u < 16; ++u) {
+                    uint2 ent;
+                    ent.x = (u & 1) ? e[u >> 1].z : e[u >> 1].x;
+                    ent.y = (u & 1) ? e[u >> 1].w : e[u >> 1].y;
+                    const float y = fmaf(c, __uint_as_float(ent.x), -thr);
+                    if (i0 + u < mycnt && y > 0.f) {
+                        if constexpr (AM == ALPHA_15) { F = fmaf(y, y, F); G += y; Hs += 1.f; }
+                        else if constexpr (AM == ALPHA_20) { F += y; G += 1.f; }
+                        else {
+                            const float p2 = pow_r2<AM>(y, r);
+                            Hs += p2; G = fmaf(p2, y, G); F = fmaf(p2 * y, y, F);
+                        }
+                        if (sweep == 0) {
+                            *(uint2*)(lptr + 8 * front) = ent;
+                            ++front;
+                            const uint32_t j = ent.y >> 6;            // its tiles are the working mask
+                            if (j != lastj) { atomicOr(&wm[myrow * W + (j >> 5)], 1u << (j & 31)); lastj = j; }
                         }
                     }
+                }
             }
             if (sweep == 0) {
-                nmax = 0;
-#pragma unroll
-                for (int qb = 0; qb < QB; ++qb) { mycnt[qb] = front[qb]; nmax = max(nmax, front[qb]); }
+                mycnt = nmax = front;
 #pragma unroll
                 for (int off = 32; off >= 1; off >>= 1) nmax = max(nmax, __shfl_xor(nmax, off));
             }
-            int pending = 0;
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) {
-                const float f = xhalf_sum(F[qb]) - 1.f, g = xhalf_sum(G[qb]), hs = xhalf_sum(Hs[qb]);
-                if (!done[qb]) {
-                    iters[qb] += 1;
-                    f1_last[qb] = -r * g;
-                    if (fabsf(f) <= p.tol || p.right_edge) done[qb] = 1;
-                    else {
-                        const float stol = step_tol(p.tol, thr[qb]);
-                        const float cand_tau = hybrid_step<AM>(thr[qb], f, g, hs, r, hc.alpha, blo[qb], bhi[qb], prev[qb], stol);
-                        if (fabsf(cand_tau - thr[qb]) < stol) done[qb] = 1;
-                        thr[qb] = cand_tau;
-                    }
-                    pending |= !done[qb];
+            const float f = xhalf_sum(F) - 1.f, g = xhalf_sum(G), hs = xhalf_sum(Hs);
+            if (!done) {
+                iters += 1;
+                f1_last = -r * g;
+                if (fabsf(f) <= p.tol || p.right_edge) done = 1;
+                else {
+                    const float stol = step_tol(p.tol, thr);
+                    const float cand_tau = hybrid_step<AM>(thr, f, g, hs, r, hc.alpha, blo, bhi, prev, stol);
+                    if (fabsf(cand_tau - thr) < stol) done = 1;
+                    thr = cand_tau;
                 }
             }
-            if (!__any(pending)) break;
+            if (!__any(!done)) break;
         }
         if (h == 0) {
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) {
-                const long gi = (long)bh * N + qw0 + 32 * qb + n;
-                p.tau[gi] = thr[qb];
-                p.rs_lo[gi] = blo[qb];
-                p.rs_hi[gi] = bhi[qb];
-                p.rs_state[gi] = iters[qb] | (done[qb] << 16);
-                p.rs_f1[gi] = f1_last[qb];
-            }
+            const long gi = (long)bh * N + qw0 + n;
+            p.tau[gi] = thr;
+            p.rs_lo[gi] = blo;
+            p.rs_hi[gi] = bhi;
+            p.rs_state[gi] = iters | (done << 16);
+            p.rs_f1[gi] = f1_last;
         }
     }
     if (__any(any_over) && lane == 0) atomicOr(&over_s[myrow], 1);
 
     // ---- sparse row groups: the support itself, for the gather kernel ---------------------------
-    // The entries above the final tau - the row's support, a handful of keys - are moved to the front of their list, with their key indices; gather_out_kernel then
-    // forms O from those rows of V alone, and the block-sparse output kernel skips the row group.
-    {
-        int obstacle = any_over;
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) obstacle |= !done[qb];
-        if (__any(obstacle) && lane == 0) atomicOr(&gsum[2], 1);
-    }
+    // The entries above the final tau - the row's support, a handful of keys - are moved to the front of their
+    // list, with their key indices; gather_out_kernel then forms O from those rows of V alone, and the
+    // block-sparse output kernel skips the row group.
+    if (__any(any_over || !done) && lane == 0) atomicOr(&gsum[2], 1);
     __syncthreads();
     const int nrows = min(BR, N - (int)q0);
     const bool sparse = p.gflag && gsum[2] == 0;
     if (sparse) {
         int nsup = 0;
         if (active) {
+            int w = 0;
+            uint32_t lastj = 0xffffffffu;
+            for (int i0 = 0; i0 < mycnt; i0 += 16) {
+                uint4 e[8];
 #pragma unroll
-            for (int qb = 0; qb < QB; ++qb) {
-                int w = 0;
-                uint32_t lastj = 0xffffffffu;
-                for (int i0 = 0; i0 < mycnt[qb]; i0 += 16) {
-                    uint4 e[8];
+                for (int u = 0; u < 8; ++u) {
+                    e[u] = make_uint4(0u, 0u, 0u, 0u);
+                    if (i0 + 2 * u < mycnt) e[u] = *(const uint4*)(lptr + (i0 + 2 * u) * 8);
+                }
+                // (all sixteen are in registers before the first is overwritten; w <= i0 + u)
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        e[u] = make_uint4(0u, 0u, 0u, 0u);
-                        if (i0 + 2 * u < mycnt[qb]) e[u] = *(const uint4*)(lptr + (i0 + 2 * u) * 8);
-                    }
-                    // (all sixteen are in registers before the first is overwritten; w <= i0 + u)
-#pragma unroll
-                    for (int u = 0; u < 16; ++u) {
-                        uint2 ent;
-                        ent.x = (u & 1) ? e[u >> 1].z : e[u >> 1].x;
-                        ent.y = (u & 1) ? e[u >> 1].w : e[u >> 1].y;
-                        if (i0 + u < mycnt[qb] && fmaf(c, __uint_as_float(ent.x), -thr[qb]) > 0.f) {
-                            *(uint2*)(lptr + 8 * w) = ent;
-                            ++w;
-                            const uint32_t j = ent.y >> 6;
-                            if (j != lastj) { atomicOr(&fmk[myrow * W + (j >> 5)], 1u << (j & 31)); lastj = j; }
-                        }
+                for (int u = 0; u < 16; ++u) {
+                    uint2 ent;
+                    ent.x = (u & 1) ? e[u >> 1].z : e[u >> 1].x;
+                    ent.y = (u & 1) ? e[u >> 1].w : e[u >> 1].y;
+                    if (i0 + u < mycnt && fmaf(c, __uint_as_float(ent.x), -thr) > 0.f) {
+                        *(uint2*)(lptr + 8 * w) = ent;
+                        ++w;
+                        const uint32_t j = ent.y >> 6;
+                        if (j != lastj) { atomicOr(&fmk[myrow * W + (j >> 5)], 1u << (j & 31)); lastj = j; }
                     }
                 }
-                p.scnt[((long)bh * N + qw0 + 32 * qb + n) * 2 + h] = w;
-                nsup += w;
             }
+            p.scnt[((long)bh * N + qw0 + n) * 2 + h] = w;
+            nsup += w;
         }
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) nsup += __shfl_xor(nsup, off);
@@ -804,10 +772,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 
         if (!gather) atomicAdd(&p.scal[1], 1u);       // a row group out_kernel will have to serve
     }
     if (gather) {
-        if (active && h == 0 && p.iters) {
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) p.iters[(long)bh * N + qw0 + 32 * qb + n] = iters[qb];
-        }
+        if (active && h == 0 && p.iters) p.iters[(long)bh * N + qw0 + n] = iters;
         for (int i = tid; i < MR * W; i += THREADS)
             if (I * MR + i / W < T) p.mask[((long)bh * T + (long)I * MR + i / W) * W + (i % W)] = (int32_t)fmk[i];
     }
@@ -819,7 +784,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 
         if (tid == 0)
             for (int i = 0; i < MR; ++i) nover += over_s[i];
         const int slot[3] = {0, 8, 9};
-        const unsigned long long val[3] = {ntile_done * QB, (unsigned long long)nover, (tid == 0 && gather) ? (unsigned long long)nrows : 0ull};
+        const unsigned long long val[3] = {ntile_done, (unsigned long long)nover, (tid == 0 && gather) ? (unsigned long long)nrows : 0ull};
         flush_counters<3>(blk_stats, p.stats, slot, val, tid, lane);
     }
 }

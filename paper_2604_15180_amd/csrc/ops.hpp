@@ -81,7 +81,7 @@ struct Ops {
             // refinement on the lists
             static_assert((32 * NW_TAUL<E>) % (32 * QB * NW_OUT) == 0, "an output group lies inside one row group of the list kernel");
             p.grows = 32 * NW_TAUL<E>;
-            rc = launch(tau_list_kernel<E, D, 1, AM, NBINS, NW_TAUL<E>, NBUF_TAUL, PAIR_TAUL<E>>, groups(p, NW_TAUL<E>, 1), NW_TAUL<E> * 64, s, p);
+            rc = launch(tau_list_kernel<E, D, AM, NBINS, NW_TAUL<E>, NBUF_TAUL, PAIR_TAUL<E>>, groups(p, NW_TAUL<E>, 1), NW_TAUL<E> * 64, s, p);
             if (rc) return rc;
             // sweep-based fallback for row blocks whose lists overflowed (exits at once elsewhere);
             // two rows per lane (packed 16-bit histogram counters) while a bin cannot overflow
