@@ -95,10 +95,13 @@ template <class V> EA_DEV void clear_absent(uint32_t index, V& x) {
 }
 // shortest and longest list of the wave's four rows or keys
 EA_DEV void list_range(int n, int& nmin, int& nmax) {
-    nmin = min(n, __shfl_xor(n, 16));
-    nmax = max(n, __shfl_xor(n, 16));
-    nmin = __builtin_amdgcn_readfirstlane(min(nmin, __shfl_xor(nmin, 32)));
-    nmax = __builtin_amdgcn_readfirstlane(max(nmax, __shfl_xor(nmax, 32)));
+    const auto x = __builtin_amdgcn_permlane16_swap((uint32_t)n, (uint32_t)n, false, false);
+    nmin = min((int)x[0], (int)x[1]);
+    nmax = max((int)x[0], (int)x[1]);
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)nmin, (uint32_t)nmin, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)nmax, (uint32_t)nmax, false, false);
+    nmin = __builtin_amdgcn_readfirstlane(min((int)lo[0], (int)lo[1]));
+    nmax = __builtin_amdgcn_readfirstlane(max((int)hi[0], (int)hi[1]));
 }
 template <int N, class V> EA_DEV void add_scaled(float (&acc)[N], float w, const V& x) {
 #pragma unroll
