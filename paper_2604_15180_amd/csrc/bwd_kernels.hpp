@@ -1103,7 +1103,7 @@ __global__ __launch_bounds__(256) void bwd_rows_kernel(Params p) {
 // reported; every work-group of a head forms the same offsets for itself), and the log entries' places there.
 // Keys with more entries than HUB_BATCH are summed from the log segments themselves.  Nothing to do, and gone
 // after one load, in heads without hub keys.
-constexpr int FILE_GROUPS = 16;          // work-groups per head
+constexpr int FILE_GROUPS = 16;          // work-groups per head, each with every FILE_GROUPS-th segment of the log
 constexpr int HUB_BATCH = 1024;          // entries of a hub key that are put in order in LDS at a time
 static __global__ __launch_bounds__(256) void bwd_file_kernel(Params p) {
     __shared__ int wsum[4];
@@ -1143,10 +1143,10 @@ static __global__ __launch_bounds__(256) void bwd_file_kernel(Params p) {
     wait_loads();
     __syncthreads();
     uint32_t* const index = p.hub_index + (size_t)bh * N * LOG_PER_ROW;
-    for (int seg = 0; seg * LOG_ROWS < N; ++seg) {
+    for (int seg = part; seg * LOG_ROWS < N; seg += FILE_GROUPS) {
         const int m = min(p.log_cnt[bh * MAX_LOG_SEGMENTS + seg], LOG_PER_ROW * min(LOG_ROWS, N - seg * LOG_ROWS));
         const uint32_t first = (uint32_t)(seg * LOG_ROWS) * LOG_PER_ROW;
-        for (int e = part * 256 + tid; e < m; e += FILE_GROUPS * 256) {
+        for (int e = tid; e < m; e += 256) {
             const LogEntry* le = p.klog + (size_t)bh * N * LOG_PER_ROW + first + e;
             const uint32_t key = le->key_slot & ((1u << ROW_BITS) - 1), past = le->key_slot >> ROW_BITS | le->row_slot >> ROW_BITS << SLOT_LOW_BITS;
             if (p.kcnt[hk + key] > HUB_BATCH) continue;
