@@ -930,8 +930,9 @@ __global__ __launch_bounds__(128) void bwd_decide_kernel(Params p) {
 // (row, dS, P).  dP of the first KEEP entries stays in registers between the two passes; a longer
 // row computes it a second time.  An entry whose key's list is full goes to the log of its row's segment;
 // the first of a key reports the key as a hub key.  SCALED: dkdv_kernel works on dO / max|dO|, so the delta handed to it is in those units.
+// (16-bit inputs: held to the registers of seven waves per SIMD; left to itself the compiler takes 82, five waves.)
 template <class E, int D, int AM, bool SCALED>
-__global__ __launch_bounds__(256) void bwd_rows_kernel(Params p) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(typename E::elem) == 2 ? 7 : 5))) void bwd_rows_kernel(Params p) {
     using elem = typename E::elem;
     using L = GatherLanes<E, D>;
     using vec = typename L::vec;
@@ -957,15 +958,13 @@ __global__ __launch_bounds__(256) void bwd_rows_kernel(Params p) {
         if (!(amax > 0.f)) amax = 1.f;
     }
     const long hoff = (long)bh * N * D, gi = (long)bh * N + row;
-    const elem* Kh = (const elem*)p.K + hoff + L::column(sub);
-    const elem* Vh = (const elem*)p.V + hoff + L::column(sub);
+    const HeadRows<E, D> Kh(p.K, (long)bh * N, N, sub), Vh(p.V, (long)bh * N, N, sub);
     const int cap8 = p.list_cap * 8;                   // bytes of one lane list
     const char* l0 = (const char*)p.lists + (size_t)gi * (size_t)(2 * cap8);        // the second list follows the first
     const float tau = p.tau[gi];
     const int s0 = p.scnt[gi * 2], tot = s0 + p.scnt[gi * 2 + 1];
     const vec gv = *(const vec*)((const elem*)p.dO + hoff + (long)row * D + L::column(sub));
-    int nmin, nmax;
-    list_range(tot, nmin, nmax);
+    const int nmax = longest_list(tot);
 
     auto entry_ptr = [&](int i) { return l0 + (i < s0 ? i * 8 : cap8 + (i - s0) * 8); };
     struct Entry { uint32_t key; float u, pr; };
@@ -987,7 +986,7 @@ __global__ __launch_bounds__(256) void bwd_rows_kernel(Params p) {
             constexpr int S0 = decltype(b)::value * BT;
             if (S0 * L::PAR >= left) return;
             vec v[BT];
-            unroll_steps<BT>([&](auto u) { v[decltype(u)::value] = *(const vec*)(Vh + (size_t)(L::template of_step<S0 + decltype(u)::value>(key) * (uint32_t)D)); });
+            unroll_steps<BT>([&](auto u) { v[decltype(u)::value] = Vh.load(L::template of_step<S0 + decltype(u)::value>(key)); });
             unroll_steps<BT>([&](auto u) {
                 constexpr int S = S0 + decltype(u)::value;
                 const float t = L::entry_sum(dot_share<E, EPT>(gv, v[decltype(u)::value], 0.f));
@@ -1075,8 +1074,7 @@ __global__ __launch_bounds__(256) void bwd_rows_kernel(Params p) {
             constexpr int S0 = decltype(b)::value * BT;
             if (S0 * L::PAR >= nmax - i0) return;
             vec v[BT];
-            unroll_steps<BT>([&](auto u) { v[decltype(u)::value] = *(const vec*)(Kh + (size_t)(L::template of_step<S0 + decltype(u)::value>(e.key) * (uint32_t)D)); });
-            if ((S0 + BT) * L::PAR > nmin - i0) unroll_steps<BT>([&](auto u) { clear_absent(L::template of_step<S0 + decltype(u)::value>(e.key), v[decltype(u)::value]); });
+            unroll_steps<BT>([&](auto u) { v[decltype(u)::value] = Kh.load(L::template of_step<S0 + decltype(u)::value>(e.key)); });
             unroll_steps<BT>([&](auto u) { add_scaled<EPT>(x, L::template of_step<S0 + decltype(u)::value>(dS), v[decltype(u)::value]); });
         });
     };
@@ -1197,15 +1195,14 @@ EA_DEV void hub_key_sums(const Params& p, HubLds<E, D>& s, int bh, int first_ite
         const bool is_dk = !(item & 1);
         const int cnt = p.kcnt[hk + key];
         const KeyEntry* const el = (const KeyEntry*)p.klist + (hk + key) * KEY_LIST_CAP;
-        const elem* const rows = (const elem*)(is_dk ? p.Q : p.dO) + hk * D + L::column(sub);
+        const HeadRows<E, D> rows(is_dk ? p.Q : p.dO, hk, N, sub);
         float acc[EPT];
 #pragma unroll
         for (int k = 0; k < EPT; ++k) acc[k] = 0.f;
         // sum of the m entries now in s.row, s.w, added to acc
         auto add_batch = [&](int m) {
             const int share = (m + 15) / 16, mine = min(max(m - group * share, 0), share);
-            int nmin, nmax;
-            list_range(mine, nmin, nmax);
+            const int nmax = longest_list(mine);
             for (int i0 = 0; i0 < nmax; i0 += 16) {
                 const int i = i0 + L::entry_of(sub);
                 uint32_t row = NO_ENTRY;
@@ -1215,8 +1212,7 @@ EA_DEV void hub_key_sums(const Params& p, HubLds<E, D>& s, int bh, int first_ite
                     constexpr int S0 = decltype(b)::value * BT;
                     if (S0 * L::PAR >= nmax - i0) return;
                     vec v[BT];
-                    unroll_steps<BT>([&](auto u) { v[decltype(u)::value] = *(const vec*)(rows + (size_t)(L::template of_step<S0 + decltype(u)::value>(row) * (uint32_t)D)); });
-                    if ((S0 + BT) * L::PAR > nmin - i0) unroll_steps<BT>([&](auto u) { clear_absent(L::template of_step<S0 + decltype(u)::value>(row), v[decltype(u)::value]); });
+                    unroll_steps<BT>([&](auto u) { v[decltype(u)::value] = rows.load(L::template of_step<S0 + decltype(u)::value>(row)); });
                     unroll_steps<BT>([&](auto u) { add_scaled<EPT>(acc, L::template of_step<S0 + decltype(u)::value>(w), v[decltype(u)::value]); });
                 });
             }
@@ -1343,11 +1339,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(type
     const int key = I * BWD_COLS_KEYS + rsel;
     if (key >= N) return;                              // (N is a multiple of 64: whole work-groups)
     const long kj = (long)bh * N + key, hoff = (long)bh * N * D;
-    const elem* Qh = (const elem*)p.Q + hoff + L::column(sub);
-    const elem* Gh = (const elem*)p.dO + hoff + L::column(sub);
+    const HeadRows<E, D> Qh(p.Q, (long)bh * N, N, sub), Gh(p.dO, (long)bh * N, N, sub);
     const int filed = p.kcnt[kj], cnt = filed > KEY_LIST_CAP ? 0 : filed;
-    int nmin, nmax;
-    list_range(cnt, nmin, nmax);
+    const int nmax = longest_list(cnt);
     if (nmax == 0 && !fresh) return;
     const KeyEntry* el = (const KeyEntry*)p.klist + kj * KEY_LIST_CAP;
     auto wave_fence = [] {                             // (the 16 lanes of a key sit in one wave, whose LDS operations execute in issue order)
@@ -1402,15 +1396,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(type
             vec qv[BT], gv[BT];
             unroll_steps<BT>([&](auto u) {
                 constexpr int U = decltype(u)::value;
-                const size_t off = (size_t)(L::template of_step<S0 + U>(row) * (uint32_t)D);
-                qv[U] = *(const vec*)(Qh + off);
-                gv[U] = *(const vec*)(Gh + off);
-            });
-            if ((S0 + BT) * L::PAR > nmin - i0) unroll_steps<BT>([&](auto u) {
-                constexpr int U = decltype(u)::value;
                 const uint32_t of_entry = L::template of_step<S0 + U>(row);
-                clear_absent(of_entry, qv[U]);
-                clear_absent(of_entry, gv[U]);
+                qv[U] = Qh.load(of_entry);
+                gv[U] = Gh.load(of_entry);
             });
             unroll_steps<BT>([&](auto u) {
                 constexpr int U = decltype(u)::value;

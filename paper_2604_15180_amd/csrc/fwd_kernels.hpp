@@ -1022,13 +1022,12 @@ __global__ __launch_bounds__(256) void gather_out_kernel(Params p) {
     if (row >= N) return;                             // (N is a multiple of 64: whole work-groups)
     const HeadConsts hc = head_consts(p, bh);
     const float c = hc.c, r = hc.r;
-    const elem* Vh = (const elem*)p.V + (long)bh * N * D + L::column(sub);
+    const HeadRows<E, D> Vh(p.V, (long)bh * N, N, sub);
     const long gi = (long)bh * N + row;
     const float tau = p.tau[gi];
     const int s0 = p.scnt[gi * 2], tot = s0 + p.scnt[gi * 2 + 1];
     const char* l0 = (const char*)p.lists + (size_t)gi * (2 * LIST_CAP * 8);      // the second list follows the first
-    int nmin, nmax;
-    list_range(tot, nmin, nmax);
+    const int nmax = longest_list(tot);
     float acc[EPT];
 #pragma unroll
     for (int k = 0; k < EPT; ++k) acc[k] = 0.f;
@@ -1042,8 +1041,7 @@ __global__ __launch_bounds__(256) void gather_out_kernel(Params p) {
             constexpr int S0 = decltype(b)::value * BT;
             if (S0 * L::PAR >= nmax - i0) return;
             vec v[BT];
-            unroll_steps<BT>([&](auto u) { v[decltype(u)::value] = *(const vec*)(Vh + (size_t)(L::template of_step<S0 + decltype(u)::value>(e.y) * (uint32_t)D)); });
-            if ((S0 + BT) * L::PAR > nmin - i0) unroll_steps<BT>([&](auto u) { clear_absent(L::template of_step<S0 + decltype(u)::value>(e.y), v[decltype(u)::value]); });
+            unroll_steps<BT>([&](auto u) { v[decltype(u)::value] = Vh.load(L::template of_step<S0 + decltype(u)::value>(e.y)); });
             unroll_steps<BT>([&](auto u) { add_scaled<EPT>(acc, L::template of_step<S0 + decltype(u)::value>(pr), v[decltype(u)::value]); });
         });
     }
