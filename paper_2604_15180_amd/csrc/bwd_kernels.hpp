@@ -1182,7 +1182,7 @@ EA_DEV void hub_key_sums(const Params& p, HubLds<E, D>& s, int bh, int first_ite
     using elem = typename E::elem;
     using L = GatherLanes<E, D>;
     using vec = typename L::vec;
-    constexpr int EPT = L::EPT, BT = 4;
+    constexpr int EPT = L::EPT, BT = sizeof(elem) == 2 ? 8 : 4;    // rows in flight (one work-group per key: more than elsewhere)
     static_assert(HUB_BATCH <= 4 * 256 && LOG_ROWS <= HUB_BATCH && LOG_ROWS / 32 < 64, "a segment is a batch, its bits are at most a word per lane");
     const int tid = threadIdx.x, sub = tid & 15, group = tid >> 4, lane = tid & 63;
     const int N = p.N, n = p.hub_cnt[bh];
