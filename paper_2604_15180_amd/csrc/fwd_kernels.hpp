@@ -398,8 +398,8 @@ __global__ __launch_bounds__(NW * 64) void tau_kernel(Params p) {
 // work per entry is done for one or two lanes at a time, and moving the window with every new maximum took
 // a third of the vector instructions of sparse rows.  Bound: vector issue (about 110 vector instructions per
 // tile and wave at sigma = 4 beside 16 MFMAs, 380 at sigma = 1, before the histogram was put off and the work
-// per entry cut from 14 instructions to 9).  Kernel, d = 128, 16384 tokens, sigma = 3 / 1: 1230 -> 1070 / 2302 -> 2187 us;
-// alpha = 2, 8192 tokens, d = 64: 378 -> 297 us; 65536 tokens, planted keys: 3767 -> 3440 us.
+// per entry cut from 14 instructions to 9).  Kernel, d = 128, 16384 tokens, sigma = 3 / 1: 1230 -> 1140 / 2302 -> 2200 us;
+// alpha = 2, 8192 tokens, d = 64: 378 -> 310 us; 65536 tokens, planted keys: 3767 -> 3500 us.
 // After the sweep the lists hold a superset of the row's support as exact fp32 scores, and the
 // rest happens on them: the refinement iterations of Sec. 3.2 from tau_0 = tau_h, each an
 // evaluation of f, f', f'' over the listed true scores instead of another sweep of Q K^T.  The key
