@@ -110,7 +110,7 @@ EA_DEV float histogram_lower_bound(const uint32_t* H, int rot, int shift, float 
 // A step on f itself takes F down by about e at a time while F is large (by the power mean's bound F starts at
 // thousands for r = 30 and more).  N = F^(1/r) is a norm of y, so convex as well and 1 at the same root, and its step,
 // (N - 1) / -N' = (F - F^(1 - 1/r)) / G, is the longer one: with one bin it is the root.  Near the root, where the
-// two agree and this one cancels, f's own step is taken.  Steps needed, r = 1.3 - 1000, 1 - 131072 counts: at most 5.
+// two agree and this one cancels, f's own step is taken.  Evaluations needed, r = 1 - 1000, 1 - 131072 counts: at most 5.
 // `gap`: how far above the returned value the root can lie - nothing if the steps have died down, else by
 // convexity f / |f'| at the root, which is at most (F - 1) / r as G >= 1 there (y <= 1).
 constexpr int NEWTON_MAX = 24;
