@@ -386,55 +386,64 @@ __global__ __launch_bounds__(NW * 64) void tau_kernel(Params p) {
 // Phases 1-3 of Alg. 1 from ONE dense sweep.  By Eq. 5, tau* >= max - 1 (in units of (alpha-1) s),
 // and both the maximum and tau* over a prefix of the keys are at most their values over all keys,
 // so a score that lies below a lower bound of the prefix's threshold when it is met can never lie
-// above the final one.  Every other score - a handful per row when attention is sparse - is appended, with
-// its key, to a list private to the lane that computed it (each lane sees 16 of every 32 keys of its row, so
+// above the final one.  Every other score - a handful per row when attention is sparse - is listed, with
+// its key, by the lane that computed it (each lane sees 16 of every 32 keys of its row, so
 // a row has two lists; no atomics, no ordering between lanes).  The lower bound starts as (running maximum - 1);
 // each time a list has grown by a fixed number of entries, the row's LDS histogram of the listed scores (Eq. 6-8;
 // absolute bin grid with a sliding window, as in tau_kernel) is solved (Eq. 9), and its root tau_h, a lower
 // bound of the prefix's tau* by Prop. 1, becomes the new bound.  Scores that were skipped lie below the bound and
 // contribute nothing to f at or above it, so f there, and with it Prop. 1, is that of all scores.
-// The histogram is made from the lists when it is first wanted, by a wave's lanes side by side, and kept up
-// entry by entry from then on (or from the start, where the first tile shows that the lists will be long): the
-// work per entry is done for one or two lanes at a time, and moving the window with every new maximum took
-// a third of the vector instructions of sparse rows.  Bound: vector issue (about 110 vector instructions per
-// tile and wave at sigma = 4 beside 16 MFMAs, 380 at sigma = 1, before the histogram was put off and the work
-// per entry cut from 14 instructions to 9).  Kernel, d = 128, 16384 tokens, sigma = 3 / 1: 1230 -> 1140 / 2302 -> 2200 us;
-// alpha = 2, 8192 tokens, d = 64: 378 -> 310 us; 65536 tokens, planted keys: 3767 -> 3500 us.
 // After the sweep the lists hold a superset of the row's support as exact fp32 scores, and the
 // rest happens on them: the refinement iterations of Sec. 3.2 from tau_0 = tau_h, each an
 // evaluation of f, f', f'' over the listed true scores instead of another sweep of Q K^T.  The key
 // tiles of the entries above tau_0 are the working mask.
+// The histogram is made from the lists, by a wave's lanes side by side, when the bound is refreshed: after 4, 8, 16, ...
+// tiles, if a list has grown enough since - all waves of a work-group at the same tile, as each of them holds up the
+// others at the next barrier.  Rows whose first tile shows that their lists will be long are counted entry by entry instead.
+// Bound: instructions issued, about 4 clocks of a SIMD for one of whatever kind (sigma = 1: 515 a tile and wave, 9000 clocks
+// for the four waves of a SIMD; sigma = 3: 190 and 3700), most of them for candidates where there are many: some lane has one in 15 of a
+// tile's 32 score registers at sigma = 1, though only two of the 64 lanes in each.  Such a register takes 8 instructions
+// (14 if counted; 13 and 17 as the compiler puts it), one without 2, and a tile without candidates about 90, of which 32 are the products and
+// their reads.  Forward, steps: 1088 tokens, d = 64, 87 -> 71 us; 4096 tokens 464 -> 428; 8192 tokens, alpha = 1.25, 787 -> 725; 3136 tokens,
+// d = 128, 153 -> 142; 65536 tokens 3600 -> 3490; 16384 tokens, sigma = 1, level (2515: its list stores are what memory takes).
 // A list that fills up (attention close to uniform: hundreds of non-zeros per row) flags its 64-row
 // block; flagged blocks are redone by the sweep-based tau_kernel, which runs right after and exits
 // at once everywhere else.
-// PAIR: waves 2w and 2w+1 share the words of one histogram buffer, 16 bits
-// each - what two rows per lane do within a wave - so that eight one-row waves need the LDS of
-// four and, with half the accumulator and operand registers, four waves fit a SIMD.
-template <class E, int D, int AM, int NB, int NW, int NBUF, int PAIR = 0>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 4 : 1))) void tau_list_kernel(Params p) {
-    static_assert(!PAIR || NW % 2 == 0, "paired histograms: an even number of waves");
+template <class E, int D, int AM, int NB, int NW, int NBUF>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 8 ? 4 : 1))) void tau_list_kernel(Params p) {
     using SM = TauSmem<E, D, 1, NB, NW, NBUF>;
     using KT = RowTile<E, D>;
     using elem = typename E::elem;
     constexpr int THREADS = NW * 64, BR = SM::BR, MR = SM::MR, SLOTS = SM::SLOTS;
-    // list growth (entries per lane) between two histogram solves (steps with 16 / 24 / 32 / 48: 4096 tokens, d = 64,
-    // 833 / 826 / 812 / 830 us; 16384 tokens, sigma = 1, 4631 / 4620 / 4615 / 4700 us)
-    constexpr int GROW = 32;
-    // groups of eight scores of a wave's first tile (of 256) with a candidate from which its entries are counted
-    // at once.  Most waves of sparse rows never need the histogram while they sweep: 64 / 96 / 112 / 128 give
-    // 3136 tokens, sigma = 2: 170 / 157 / 146 / 145 us; 4096 tokens, sigma = 1.5: 826 / 828 / 829 / 843 us.
-    constexpr int FIRST_TILE_BUSY = 112;
-    __shared__ __align__(1024) char kring[NBUF * KT::BYTES];
-    constexpr int HIST_WORDS = PAIR ? SM::HIST_WORDS / 2 : SM::HIST_WORDS;
-    constexpr int CB = PAIR ? 16 : SM::CBITS;            // bits per counter
-    __shared__ __align__(256) uint32_t hist[HIST_WORDS];
-    // used only once the sweep is over: they live in the key-tile ring
-    static_assert(2 * MR * MAX_W * 4 + MR * 4 + 96 <= NBUF * KT::BYTES, "post-sweep arrays must fit in the ring");
-    uint32_t* const wm = (uint32_t*)kring;                        // working mask (tiles above tau_0)
-    uint32_t* const fmk = (uint32_t*)(kring + MR * MAX_W * 4);    // final mask (tiles of the support)
-    int* const over_s = (int*)(kring + 2 * MR * MAX_W * 4);
-    int* const gsum = (int*)(kring + 2 * MR * MAX_W * 4 + ((MR * 4 + 7) & ~7));   // [1] support size, [2] obstacles
-    unsigned long long* const blk_stats = (unsigned long long*)(kring + 2 * MR * MAX_W * 4 + ((MR * 4 + 7) & ~7) + 16);
+    constexpr int LIST_STEP = 8;
+    // List growth (entries of any lane) since the last refresh of the bound from which the next scheduled one is done, and
+    // from which one is done at once (GROW_COUNTING: of lists counted as they grow).  Steps with GROW 12 / 24 / 48 / 64:
+    // forward of 1088 tokens, d = 64, 75 / 77 / 71 / 70 us, 3136 tokens, sigma = 2, 164 / 155 / 142 / 142, 4096 tokens 414 / 423 / 425 / 442.
+    constexpr int GROW = 48, GROW_COUNTING = 20, GROW_HARD = 64, FIRST_REFRESH = 4;
+    // list length from which on a refresh drops entries below the bound (it takes two passes over memory: later where
+    // the histogram needs no pass of its own; 16384 tokens, sigma = 1, 144 / 208: 2600 / 2546 us)
+    constexpr int PRUNE_FROM = 144, PRUNE_FROM_COUNTING = 208;
+    // Groups of eight scores of a wave's first tile (of 256) with a candidate from which its entries are counted as they are
+    // listed: long lists then need no pass to be counted.  112 / 180 / 230 / never: 4096 tokens, sigma = 1.5, 531 / 428 / 425 / 425,
+    // 16384 tokens, sigma = 1, 2530 / 2530 / 2600 / 3300 us.
+    constexpr int FIRST_TILE_BUSY = 180;
+    constexpr int TILE_ENTRIES = 32;     // entries a lane can list from one tile
+    constexpr int REG_ENTRIES = 16;      // entries per lane held in registers after the sweep
+    // counters: waves 2w and 2w + 1 share the words of one histogram buffer, 16 bits each
+    constexpr int CB = 16;
+    static_assert(NW % 2 == 0 && 2 * LIST_CAP < 65536, "a counter holds what two lists can count");
+    constexpr int RING_BYTES = NBUF * KT::BYTES, HIST_BYTES = NW / 2 * 32 * SLOTS * 4;
+    __shared__ __align__(1024) char lds[RING_BYTES + HIST_BYTES];
+    char* const kring = lds;
+    uint32_t* const hist = (uint32_t*)(lds + RING_BYTES);
+    // used only once the sweep is over: in place of the ring
+    constexpr int POST_BYTES = 2 * MR * MAX_W * 4 + ((MR * 4 + 7) & ~7) + 48;
+    static_assert(POST_BYTES <= RING_BYTES, "post-sweep arrays must fit in the ring");
+    uint32_t* const wm = (uint32_t*)lds;                          // working mask (tiles above tau_0)
+    uint32_t* const fmk = wm + MR * MAX_W;                        // final mask (tiles of the support)
+    int* const over_s = (int*)(fmk + MR * MAX_W);
+    int* const gsum = (int*)((char*)over_s + ((MR * 4 + 7) & ~7));   // [1] support size, [2] obstacles
+    unsigned long long* const blk_stats = (unsigned long long*)(gsum + 4);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 31, h = lane >> 5;
@@ -447,31 +456,45 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 
     const elem* Kh = (const elem*)p.K + (long)bh * N * D;
     const int njt = p.causal ? min((int)((q0 + BR) / 64), T) : T;
     const int wjt = !active ? 0 : p.causal ? (int)((qw0 + 31) / 64) + 1 : T;
+    const int jdiag = p.causal ? (int)(qw0 / 64) : T;     // the first tile that holds keys past a row of this wave
     const int myrow = (wave * 32) / 64;
     const HeadConsts hc = head_consts(p, bh);
-    const float c = hc.c, r = hc.r;
+    const float c = uniform(hc.c), r = uniform(hc.r), alpha = uniform(hc.alpha);     // (in scalar registers)
     constexpr float hb = 1.f / NB;
 
     Owned<E, D, 1> qf;
     load_owned<E, D, 1>(qf, Qh, active ? qw0 : 0, lane);
-    for (int i = tid; i < HIST_WORDS; i += THREADS) hist[i] = 0u;
+    for (int i = tid; i < HIST_BYTES / 4; i += THREADS) hist[i] = 0u;      // (the walk begins with a barrier)
 
-    // this lane's list: byte offsets from the head's lists
-    char* const lists_h = (char*)p.lists + (size_t)bh * N * (2 * LIST_CAP * 8);
-    const uint32_t list0 = (uint32_t)(((active ? (int)qw0 : 0) + n) * 2 + h) * (uint32_t)(LIST_CAP * 8);
-    char* const lptr = lists_h + list0;
-    int cnt = 0, trig = GROW, a_top = INT_MIN;
-    float run = -INFINITY, lowraw = -3.0e38f;
-    const int hwave = PAIR ? (wave >> 1) : wave;         // whose buffer, and which half of its words
-    const int hshift = PAIR ? 16 * (wave & 1) : 0;
-    uint32_t one;                                        // (one count, in a vector register: the LDS addition takes no scalar)
-    asm("v_mov_b32 %0, %1" : "=v"(one) : "s"(1u << hshift));
-    uint32_t* const hrow = hist + (hwave * 32 + n) * SLOTS;
+    // this lane's list: 8-byte entries at lists_w + list0()
+    char* const lists_w = (char*)p.lists + ((size_t)bh * N + (active ? qw0 : 0)) * (size_t)(2 * LIST_CAP * 8);
+    const uint64_t lists_u = uniform_address(lists_w);
+    auto list0 = [] {                                    // (formed anew where it is wanted: no register of the sweep's)
+        const int l = lane_id_opaque();
+        return (uint32_t)((l & 31) * 2 + (l >> 5)) * (uint32_t)(LIST_CAP * LIST_STEP);
+    };
+    uint32_t at = list0();                               // where the next entry goes
+    uint32_t trig = GROW * LIST_STEP, trig_hard = GROW_HARD * LIST_STEP;    // list lengths from which on the bound is refreshed
+    auto entries = [&] { return (int)((at - list0()) / (uint32_t)LIST_STEP); };      // (more than LIST_CAP: entries were lost)
+    auto load_entries = [&](auto& e, int i0, int cnt) __attribute__((always_inline)) {      // entries from i0 on, i0 even (-inf past the list's end)
+        constexpr int K = sizeof(e) / sizeof(e[0]);
+        const char* const l = lists_w + (list0() + (uint32_t)i0 * (uint32_t)LIST_STEP);
+#pragma unroll
+        for (int u = 0; u < K; u += 2) {
+            uint4 x = make_uint4(0xff800000u, 0u, 0xff800000u, 0u);
+            if (i0 + u < cnt) x = *(const uint4*)(l + u * LIST_STEP);
+            e[u] = make_uint2(x.x, x.y);
+            e[u + 1] = make_uint2(i0 + u + 1 < cnt ? x.z : 0xff800000u, x.w);
+        }
+    };
+    auto store_entry = [&](uint32_t to, uint2 e) { *(uint2*)(lists_w + to) = e; };
+    int a_top = INT_MIN;
+    float run = -INFINITY, low = -3.0e38f, lowraw = -3.0e38f;     // running maximum, lower bound, root of the histogram so far (raw scores)
+    const int hshift = 16 * (wave & 1);
+    uint32_t* const hrow = hist + ((wave >> 1) * 32 + n) * SLOTS;
     const uint32_t hrow_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const uint32_t*)hrow;
-    const float inv_c = 1.f / c, cb = c * NB, c4 = 4.f * cb;
-    float k4 = 0.f, top_raw = -INFINITY;
-    int bottom4 = 0;
-    bool counting = false;                               // the same for all lanes: entries are counted as they are listed
+    const float inv_c = uniform(1.f / c), cb = uniform(c * NB), c4 = uniform(4.f * cb);
+    float k4 = 0.f, bottom4 = 0.f, top_raw = -INFINITY;
 
     // Root of the row's histogram (Eq. 9) as it stands (both lanes of a row hold the same): tau_0 =
     // max(tau_h, max - 1) less the fp32 slack, and the bracket's upper end.
@@ -507,7 +530,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 
                 nt += 1; a_lo += 1; rot = a_lo & (SLOTS - 1); kk = 4.f * (float)(rot - a_lo);
             }
             if (a_top != INT_MIN) { first = max(a_top, nt - SLOTS) + 1; last = nt; }
-            a_top = nt; k4 = kk; bottom4 = 4 * rot;
+            a_top = nt; k4 = kk; bottom4 = (float)(4 * rot);
             // scores up to here lie in the window for certain (less than half a bin from its top edge)
             top_raw = fmaxf(run, ((float)nt + 0.5f) * (hb * inv_c));
         }
@@ -518,142 +541,225 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 
             todo &= todo - 1;
             const int f0 = __builtin_amdgcn_readlane(first, src);
             const int ncl = __builtin_amdgcn_readlane(last - first, src);
-            if (((lane - f0) & (SLOTS - 1)) <= ncl) {
-                uint32_t* word = hist + (hwave * 32 + src) * SLOTS + lane;
-                if constexpr (!PAIR) *word = 0u;
-                else lds_and_b32(word, hshift == 0 ? 0xffff0000u : 0x0000ffffu);
-            }
+            if (((lane - f0) & (SLOTS - 1)) <= ncl) lds_and_b32(hist + ((wave >> 1) * 32 + src) * SLOTS + lane, ~(0xffffu << hshift));
         }
     };
-    // Histogram of what the lists hold so far
+    bool counting = false;                               // the same for all lanes: entries are counted as they are listed
+    // What the lists hold beyond the first `counted` entries, counted in the histogram
+    int counted = 0;
     auto count_lists = [&] {
-        move_window();
-        int nmax = min(cnt, LIST_CAP);
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) nmax = max(nmax, __shfl_xor(nmax, off));
+        if (counting) return;
+        if (__any(run > top_raw)) move_window();
+        const uint32_t one = 1u << hshift;
+        const int cnt = min(entries(), LIST_CAP), from = counted & ~1, most = wave_max(cnt - from);
         wait_loads();                                   // this wave's stores have completed
-        for (int i0 = 0; i0 < nmax; i0 += 16) {
-            uint4 e[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                e[u] = make_uint4(0u, 0u, 0u, 0u);
-                if (i0 + 2 * u < cnt) e[u] = *(const uint4*)(lptr + (i0 + 2 * u) * 8);
-            }
+#pragma unroll 1
+        for (int i0 = 0; i0 < most; i0 += 16) {
+            uint2 e[16];
+            load_entries(e, from + i0, cnt);
 #pragma unroll
             for (int u = 0; u < 16; ++u) {
-                const float sc = __uint_as_float((u & 1) ? e[u >> 1].z : e[u >> 1].x);
-                const int rel = (int)fmaf(c4, sc, k4);
+                const float rel = fmaf(c4, __uint_as_float(e[u].x), k4);
                 // (an entry further than one unit below the maximum is below the window, and of no use)
-                if (i0 + u < min(cnt, LIST_CAP) && rel >= bottom4) lds_add_at(hrow_lds + (rel & (4 * SLOTS - 4)), one);
+                if (rel >= bottom4 && (u > 0 || i0 > 0 || from == counted)) lds_add_at(hrow_lds + ((uint32_t)(int)rel & (4 * SLOTS - 4)), one);
             }
         }
-        counting = true;
+        counted = max(counted, cnt);
     };
 
     f32x16 C[2][1];
-    unsigned long long ntile_done = 0;
-    auto sweep_tile = [&](int j, const char* buf) {
-            if (j >= wjt) return;
-            stage1<E, D, 1, EA_FENCE, PAIR ? 0 : 8>(C, buf, qf, lane);
-            if (p.causal && (long)j * 64 + 63 > qw0) causal_hide<1, true>(C, j * 64, (int)qw0, lane);
-            ++ntile_done;
-            // maxima of the four groups of 8 registers, of the lane, of the row
-            float gm[4];
+    float gm[4], lm;
+    // scores of tile j and the maxima of the four groups of 8 registers and of the lane
+    auto tile_scores = [&](int j, const char* buf) {
+        stage1<E, D, 1, EA_FENCE, NW == 8 ? 0 : 8>(C, buf, qf, lane);
+        if (j >= jdiag) causal_hide<1, true>(C, j * 64, (int)qw0, lane);
+        settle_vec<E>(C[0][0], C[1][0]);
 #pragma unroll
-            for (int g = 0; g < 4; ++g) gm[g] = max8_raw(C[g >> 1][0], 8 * (g & 1));
-            const float lm = max2_raw(max3_raw(gm[0], gm[1], gm[2]), gm[3]);
-            const float tm = xhalf_max(lm);
-            run = max2_raw(run, tm);
-            if (j == 0) {
-                // many candidates in the first tile: lists will be long, count from the start
-                int busy = 0;
+        for (int g = 0; g < 4; ++g) gm[g] = max8_raw(C[g >> 1][0], 8 * (g & 1));
+        lm = max2_raw(max3_raw(gm[0], gm[1], gm[2]), gm[3]);
+    };
+    bool listed = false, tight = false;                  // the same for all lanes: lists have grown; two tiles may fill one
+    // candidates: raw scores at or above the row's current lower bound; most tiles of a sparse row block hold none
+    auto list_tile = [&](int j) {
+        if (!__any(lm >= low)) return;                   // (nor does the maximum move: low <= run)
+        __builtin_amdgcn_s_setprio(3);                   // (the others of the group wait for the wave with most candidates)
+        run = max2_raw(run, xhalf_max(lm));
+        low = max2_raw(run - inv_c, lowraw);
+        const uint32_t key0 = (uint32_t)(j * 64 + 8 * h);
+        if (j == 0) {
+            // many candidates in the first tile: lists will be long
+            int busy = 0;
 #pragma unroll
-                for (int g = 0; g < 4; ++g) busy += __popcll(__ballot(gm[g] >= run - inv_c));
-                counting = busy >= FIRST_TILE_BUSY;
-            }
-            if (counting && __any(tm > top_raw)) move_window();
-            // candidates: raw scores at or above the row's current lower bound; most tiles of a
-            // sparse row block hold none, and leave here
-            const float low = max2_raw(run - inv_c, lowraw);
-            if (!__any(lm >= low)) return;
-            const int key0 = j * 64 + 8 * h;
-            uint32_t at = list0 + 8u * (uint32_t)min(cnt, LIST_CAP - 1);
-            const uint32_t at_last = list0 + 8u * (uint32_t)(LIST_CAP - 1);
-            auto scan = [&](auto count) {
+            for (int g = 0; g < 4; ++g) busy += __popcll(__ballot(gm[g] >= low));
+            counting = busy >= FIRST_TILE_BUSY;
+            if (counting) trig_hard = GROW_COUNTING * LIST_STEP;
+        }
+        auto scan = [&](auto count) __attribute__((always_inline)) {
+            unroll_steps<4>([&](auto g) __attribute__((always_inline)) {
+                constexpr int G = decltype(g)::value;
+                if (!__any(gm[G] >= low)) return;
+                // tile row of register v of group g: see causal_hide
+                unroll_steps<8>([&](auto v) __attribute__((always_inline)) {
+                    constexpr int V = decltype(v)::value, OFF = 32 * (G >> 1) + 16 * (G & 1) + V;
+                    const float sc = C[G >> 1][0][8 * (G & 1) + V];
+                    if constexpr (decltype(count)::value) list_and_count_candidate<OFF>(sc, low, key0, at, lists_u, c4, k4, bottom4, hrow_lds, 4 * SLOTS - 4, 1u << hshift);
+                    else list_candidate<OFF>(sc, low, key0, at, lists_u);
+                });
+            });
+        };
+        if (tight) {
+            // (a full list keeps overwriting its last entry: its block is redone anyway)
+            if (counting && __any(run > top_raw)) move_window();
+            const uint32_t last = list0() + (uint32_t)((LIST_CAP - 1) * LIST_STEP);
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    if (!__any(gm[g] >= low)) continue;
+            for (int g = 0; g < 4; ++g)
 #pragma unroll
-                    for (int v = 0; v < 8; ++v) {
-                        const float sc = C[g >> 1][0][8 * (g & 1) + v];
-                        const unsigned long long hit = __ballot(sc >= low);
-                        if (!hit) continue;
-                        asm volatile("");               // (keeps the branch above a scalar one of its own: no lane mask to save and restore)
-                        if (sc >= low) {
-                            if constexpr (decltype(count)::value) {
-                                // slot of the score's bin, times 4 (a score that rounding puts a hair
-                                // below the window goes to its lowest bin)
-                                const int rel = max((int)fmaf(c4, sc, k4), bottom4);
-                                lds_add_at(hrow_lds + (rel & (4 * SLOTS - 4)), one);
-                            }
-                            // a full list keeps overwriting its last entry (its block is redone anyway)
-                            uint2 ent;          // tile row of register v of group g: see causal_hide
-                            ent.x = __float_as_uint(sc); ent.y = (uint32_t)(key0 + 32 * (g >> 1) + 16 * (g & 1) + v);
-                            *(uint2*)(lists_h + at) = ent;
-                            at = min(at + 8u, at_last);
-                            ++cnt;
-                        }
+                for (int v = 0; v < 8; ++v) {
+                    const float sc = C[g >> 1][0][8 * (g & 1) + v];
+                    if (sc >= low) {
+                        store_entry(min(at, last), make_uint2(__float_as_uint(sc), key0 + 32 * (g >> 1) + 16 * (g & 1) + v));
+                        const float rel = fmaf(c4, sc, k4);
+                        if (counting && at <= last && rel >= bottom4) lds_add_at(hrow_lds + ((uint32_t)(int)rel & (4 * SLOTS - 4)), 1u << hshift);
+                        at += LIST_STEP;
                     }
                 }
-            };
-            if (counting) scan(std::true_type{}); else scan(std::false_type{});
-            if (__any(cnt >= trig)) {
-                // a better lower bound from the histogram so far
-                if (!counting) count_lists();
-                float lo, up;
-                histogram_bound(lo, up, true);
-                const float braw = lo * inv_c;
-                lowraw = braw - fabsf(braw) * 1e-6f;
-                trig = cnt <= LIST_CAP ? cnt + GROW : INT_MAX;
-            }
+        } else if (counting) {
+            if (__any(run > top_raw)) move_window();
+            scan(std::true_type{});
+        } else scan(std::false_type{});
+        listed = true;
+        __builtin_amdgcn_s_setprio(0);
     };
-    stream_tiles_ring<NBUF, KT::NINST / NW>(njt, kring, KT::BYTES,
-        [&](int it, char* buf) { issue_rows<E, D, NW>(buf, Kh, (long)it * 64, wave, lane); }, sweep_tile);
-    for (int i = tid; i < MR * W; i += THREADS) { wm[i] = 0u; fmk[i] = 0u; }   // (the walk ended with a barrier: the ring is free)
+    // a better lower bound from the histogram so far
+    auto refresh = [&] {
+        count_lists();
+        float lo, up;
+        histogram_bound(lo, up, true);
+        const float braw = lo * inv_c;
+        lowraw = braw - fabsf(braw) * 1e-6f;
+        low = max2_raw(low, lowraw);
+        int cnt = entries(), most = wave_max(cnt);
+        if (most > (counting ? PRUNE_FROM_COUNTING : PRUNE_FROM) && most <= LIST_CAP) {
+            // long lists: entries below the bound are dropped, the others move to the front in their order (counted they stay:
+            // bins below the histogram's root have no part in it, nor in the root of any later one)
+            uint32_t front = list0();
+#pragma unroll 1
+            for (int i0 = 0; i0 < most; i0 += 8) {
+                uint2 e[8];
+                load_entries(e, i0, cnt);
+                // (all eight are in registers before the first is overwritten)
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    if (__uint_as_float(e[u].x) >= low) { store_entry(front, e[u]); front += LIST_STEP; }
+            }
+            at = front;
+            cnt = counted = entries();
+            most = wave_max(cnt);
+        }
+        trig = (uint32_t)(most + GROW) * LIST_STEP;
+        // (the two tiles before the next look at the lists add up to TILE_ENTRIES each)
+        tight = most > LIST_CAP - 3 * TILE_ENTRIES;
+        trig_hard = most >= LIST_CAP ? UINT_MAX : (uint32_t)(most + (counting ? GROW_COUNTING : GROW_HARD)) * LIST_STEP;
+        if (!tight) trig_hard = min(trig_hard, (uint32_t)(LIST_CAP - 2 * TILE_ENTRIES + 1) * LIST_STEP);
+    };
+    // Tile it + 1 is loaded under the scores of tile it and waited for before the tile's candidates are listed: the
+    // wait covers list stores of tile it - 1, which have had the tile's matrix products to complete, and none of its own.
+    {
+        auto issue = [&](int it) { issue_rows<E, D, NW>(kring + (it % NBUF) * KT::BYTES, Kh, (long)it * 64, wave, lane); };
+        static_assert(NBUF == 2, "double buffer");
+        if (njt > 0) issue(0);
+        wait_vm_at_most<0>();
+        __syncthreads();
+        auto step = [&](int it, const char* buf) __attribute__((always_inline)) {
+            if (it + 1 < njt) issue(it + 1);             // (everyone is done with tile it - 1)
+            if (it < wjt) tile_scores(it, buf);
+            sched_fence();
+            wait_vm_at_most<0>();
+            if (it < wjt) list_tile(it);
+            __syncthreads();                             // tile it + 1 has landed for every wave
+        };
+        auto look = [&](int tiles) __attribute__((always_inline)) {      // after every second tile
+            if (!listed || tiles >= wjt) return;
+            listed = false;
+            const bool scheduled = tiles >= FIRST_REFRESH && (tiles & (tiles - 1)) == 0;
+            if (__any(at - list0() >= (scheduled ? min(trig, trig_hard) : trig_hard))) refresh();
+        };
+        if constexpr (D == 128 && E::EPL == 8) {
+            // (two tiles a turn: the buffers' addresses are then constants, 8 instructions a tile; at d = 64 it is 4, and
+            // the code of one tile body less to fetch counts for more in short sequences)
+            for (int it = 0; it < njt; it += 2) {
+                step(it, kring);
+                if (it + 1 >= njt) break;
+                step(it + 1, kring + KT::BYTES);
+                look(it + 2);
+            }
+        } else {
+            for (int it = 0; it < njt; ++it) {
+                step(it, kring + (it & 1) * KT::BYTES);
+                if (it & 1) look(it + 1);
+            }
+        }
+    }
+    for (int i = tid; i < MR * W; i += THREADS) { wm[i] = 0u; fmk[i] = 0u; }
     if (tid < MR) over_s[tid] = 0;
     if (tid < 4) gsum[tid] = 0;
     __syncthreads();
-    // The lists are read back by the lanes that wrote them and by no others (here, in count_lists while the sweep
-    // goes on, and after the first evaluation has moved entries to the front): a wave's vector memory operations
+    // The lists are read back by the lanes that wrote them and by no others: a wave's vector memory operations
     // on one address take effect in program order, so no fence is needed.  A device-scope fence here writes the
     // whole L2 back once per work-group, which cost 0.1 - 0.4 ms per launch.
     wait_loads();
 
     // ---- solve and refinement on the lists -----------------------------------------------------
-    int any_over = 0;
-    float thr = 0.f;
-    int iters = 0, done = 1, mycnt = 0;
+    float thr = 0.f, thr0 = 0.f;
+    int over = 0, iters = 0, done = 1, mycnt = 0, nmax = 0;
+    uint2 ent[REG_ENTRIES];
+    bool in_regs = false;
+    // body(score, key) for every listed entry, and for some past the list's end with a score of -inf
+    auto from_regs = [&](auto&& body) __attribute__((always_inline)) {
+        unroll_steps<REG_ENTRIES / 8>([&](auto b) __attribute__((always_inline)) {
+            constexpr int I0 = 8 * decltype(b)::value;
+            if (I0 >= nmax) return;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) body(__uint_as_float(ent[I0 + u].x), ent[I0 + u].y);
+        });
+    };
+    auto from_memory = [&](auto&& body) __attribute__((always_inline)) {
+#pragma unroll 1
+        for (int i0 = 0; i0 < nmax; i0 += 16) {
+            uint2 e[16];
+            load_entries(e, i0, mycnt);
+            // (all sixteen are in registers before a body stores the first)
+#pragma unroll
+            for (int u = 0; u < 16; ++u) body(__uint_as_float(e[u].x), e[u].y);
+        }
+    };
     if (active) {
         float blo, bhi;
-        if (!counting) count_lists();
-        histogram_bound(thr, bhi, false);
+        over = entries() > LIST_CAP;
+        mycnt = min(entries(), LIST_CAP);
+        nmax = wave_max(mycnt);
+        in_regs = nmax <= REG_ENTRIES;
+        if (in_regs) load_entries(ent, 0, mycnt);
+        if (in_regs && !counting && !__any(counted)) {
+            if (__any(run > top_raw)) move_window();
+            const uint32_t one = 1u << hshift;
+            from_regs([&](float sc, uint32_t) {
+                const float rel = fmaf(c4, sc, k4);
+                if (rel >= bottom4) lds_add_at(hrow_lds + ((uint32_t)(int)rel & (4 * SLOTS - 4)), one);
+            });
+        } else count_lists();
+        histogram_bound(thr0, bhi, false);
         if (h == 0) {
-            p.rs_t0[(long)bh * N + qw0 + n] = thr;
+            p.rs_t0[(long)bh * N + qw0 + n] = thr0;
             p.rs_up0[(long)bh * N + qw0 + n] = bhi;
         }
         float f1_last = -1.f;
-        any_over = cnt > LIST_CAP;
-        mycnt = min(cnt, LIST_CAP);
-        int nmax = mycnt;
-        blo = thr; done = 0;
-        if (p.right_edge) thr = bhi;      // tau_h + h >= tau*: the right-edge root, taken as it is
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) nmax = max(nmax, __shfl_xor(nmax, off));
-        // refinement (Sec. 3.2): evaluations of f, f', f'' over the listed scores; each lane walks
-        // its own list, sixteen entries at a time with all loads in flight together.
-        // The first evaluation, at tau_0 <= tau* (every later threshold lies above it), moves the entries it
-        // finds above the threshold to the front of their list: those that follow read a fraction of it
-        // (steps: sigma = 1, 16384 tokens, lists of about 120 entries, 4886 -> 4780 us; fp32, 256 tokens, 123 -> 113).
+        blo = thr0;
+        thr = p.right_edge ? bhi : thr0;      // tau_h + h >= tau*: the right-edge root, taken as it is
+        done = 0;
+        // refinement (Sec. 3.2): evaluations of f, f', f'' over the listed scores.  Lists in memory: the first
+        // evaluation, at tau_0 <= tau* (every later threshold lies above it), moves the entries it
+        // finds above the threshold to the front of their list, and those that follow read a fraction of it.
         SecantPrev prev;
         // (alpha > 2: a row with a score within the tolerance of its root ends up bisecting, since f
         // rises vertically there; the sweeps over the lists are cheap, those of the output kernel
@@ -661,42 +767,32 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 
         const int nsweeps = r < 1.f ? 2 * p.max_sweeps : p.max_sweeps;
         for (int sweep = 0; sweep < nsweeps; ++sweep) {
             float F = 0.f, G = 0.f, Hs = 0.f;
-            uint32_t lastj = 0xffffffffu;
-            int front = 0;
-            for (int i0 = 0; i0 < nmax; i0 += 16) {
-                uint4 e[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    e[u] = make_uint4(0u, 0u, 0u, 0u);
-                    if (i0 + 2 * u < mycnt) e[u] = *(const uint4*)(lptr + (i0 + 2 * u) * 8);
+            auto eval = [&](float sc) {
+                const float y = fmaf(c, sc, -thr);
+                if constexpr (AM == ALPHA_15) { const float yp = fmaxf(y, 0.f); F = fmaf(yp, yp, F); G += yp; Hs += y > 0.f ? 1.f : 0.f; }
+                else if constexpr (AM == ALPHA_20) { F += fmaxf(y, 0.f); G += y > 0.f ? 1.f : 0.f; }
+                else if (y > 0.f) {
+                    const float p2 = pow_r2<AM>(y, r);
+                    Hs += p2; G = fmaf(p2, y, G); F = fmaf(p2 * y, y, F);
                 }
-                // (all sixteen are in registers before the first is overwritten; front <= i0 + u)
-#pragma unroll
-                for (int u = 0; u < 16; ++u) {
-                    uint2 ent;
-                    ent.x = (u & 1) ? e[u >> 1].z : e[u >> 1].x;
-                    ent.y = (u & 1) ? e[u >> 1].w : e[u >> 1].y;
-                    const float y = fmaf(c, __uint_as_float(ent.x), -thr);
-                    if (i0 + u < mycnt && y > 0.f) {
-                        if constexpr (AM == ALPHA_15) { F = fmaf(y, y, F); G += y; Hs += 1.f; }
-                        else if constexpr (AM == ALPHA_20) { F += y; G += 1.f; }
-                        else {
-                            const float p2 = pow_r2<AM>(y, r);
-                            Hs += p2; G = fmaf(p2, y, G); F = fmaf(p2 * y, y, F);
-                        }
-                        if (sweep == 0) {
-                            *(uint2*)(lptr + 8 * front) = ent;
-                            ++front;
-                            const uint32_t j = ent.y >> 6;            // its tiles are the working mask
-                            if (j != lastj) { atomicOr(&wm[myrow * W + (j >> 5)], 1u << (j & 31)); lastj = j; }
-                        }
+                return y > 0.f;
+            };
+            if (in_regs) from_regs([&](float sc, uint32_t) { eval(sc); });
+            else {
+                uint32_t front = list0(), lastj = 0xffffffffu;
+                from_memory([&](float sc, uint32_t key) {
+                    if (eval(sc) && sweep == 0) {
+                        store_entry(front, make_uint2(__float_as_uint(sc), key));
+                        front += LIST_STEP;
+                        const uint32_t j = key >> 6;                  // its tiles are the working mask
+                        if (j != lastj) { atomicOr(&wm[myrow * W + (j >> 5)], 1u << (j & 31)); lastj = j; }
                     }
+                });
+                if (sweep == 0) {
+                    mycnt = (int)((front - list0()) / (uint32_t)LIST_STEP); nmax = wave_max(mycnt);
+                    in_regs = nmax <= REG_ENTRIES;
+                    if (in_regs) load_entries(ent, 0, mycnt);
                 }
-            }
-            if (sweep == 0) {
-                mycnt = nmax = front;
-#pragma unroll
-                for (int off = 32; off >= 1; off >>= 1) nmax = max(nmax, __shfl_xor(nmax, off));
             }
             const float f = xhalf_sum(F) - 1.f, g = xhalf_sum(G), hs = xhalf_sum(Hs);
             if (!done) {
@@ -705,7 +801,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 
                 if (fabsf(f) <= p.tol || p.right_edge) done = 1;
                 else {
                     const float stol = step_tol(p.tol, thr);
-                    const float cand_tau = hybrid_step<AM>(thr, f, g, hs, r, hc.alpha, blo, bhi, prev, stol);
+                    const float cand_tau = hybrid_step<AM>(thr, f, g, hs, r, alpha, blo, bhi, prev, stol);
                     if (fabsf(cand_tau - thr) < stol) done = 1;
                     thr = cand_tau;
                 }
@@ -721,51 +817,47 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 
             p.rs_f1[gi] = f1_last;
         }
     }
-    if (__any(any_over) && lane == 0) atomicOr(&over_s[myrow], 1);
+    if (__any(over) && lane == 0) atomicOr(&over_s[myrow], 1);
 
     // ---- sparse row groups: the support itself, for the gather kernel ---------------------------
     // The entries above the final tau - the row's support, a handful of keys - are moved to the front of their
     // list, with their key indices; gather_out_kernel then forms O from those rows of V alone, and the
     // block-sparse output kernel skips the row group.
-    if (__any(any_over || !done) && lane == 0) atomicOr(&gsum[2], 1);
+    if (__any(over || !done) && lane == 0) atomicOr(&gsum[2], 1);
     __syncthreads();
     const int nrows = min(BR, N - (int)q0);
     const bool sparse = p.gflag && gsum[2] == 0;
     if (sparse) {
-        int nsup = 0;
+        int w = 0;
         if (active) {
-            int w = 0;
+            uint32_t front = list0();
             uint32_t lastj = 0xffffffffu;
-            for (int i0 = 0; i0 < mycnt; i0 += 16) {
-                uint4 e[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    e[u] = make_uint4(0u, 0u, 0u, 0u);
-                    if (i0 + 2 * u < mycnt) e[u] = *(const uint4*)(lptr + (i0 + 2 * u) * 8);
+            auto keep = [&](float sc, uint32_t key) {
+                if (fmaf(c, sc, -thr) > 0.f) {
+                    store_entry(front, make_uint2(__float_as_uint(sc), key));
+                    front += LIST_STEP;
+                    const uint32_t j = key >> 6;
+                    if (j != lastj) { atomicOr(&fmk[myrow * W + (j >> 5)], 1u << (j & 31)); lastj = j; }
                 }
-                // (all sixteen are in registers before the first is overwritten; w <= i0 + u)
-#pragma unroll
-                for (int u = 0; u < 16; ++u) {
-                    uint2 ent;
-                    ent.x = (u & 1) ? e[u >> 1].z : e[u >> 1].x;
-                    ent.y = (u & 1) ? e[u >> 1].w : e[u >> 1].y;
-                    if (i0 + u < mycnt && fmaf(c, __uint_as_float(ent.x), -thr) > 0.f) {
-                        *(uint2*)(lptr + 8 * w) = ent;
-                        ++w;
-                        const uint32_t j = ent.y >> 6;
-                        if (j != lastj) { atomicOr(&fmk[myrow * W + (j >> 5)], 1u << (j & 31)); lastj = j; }
-                    }
-                }
-            }
+            };
+            if (in_regs) from_regs(keep); else from_memory(keep);
+            w = (int)((front - list0()) / (uint32_t)LIST_STEP);
             p.scnt[((long)bh * N + qw0 + n) * 2 + h] = w;
-            nsup += w;
         }
+        int nsup = w;
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) nsup += __shfl_xor(nsup, off);
         if (lane == 0) atomicAdd(&gsum[1], nsup);
     }
     __syncthreads();
     const bool gather = sparse && gsum[1] <= GATHER_SUP_MAX * nrows;
+    if (!gather && active && in_regs) {
+        uint32_t lastj = 0xffffffffu;
+        from_regs([&](float sc, uint32_t key) {
+            const uint32_t j = key >> 6;
+            if (fmaf(c, sc, -thr0) > 0.f && j != lastj) { atomicOr(&wm[myrow * W + (j >> 5)], 1u << (j & 31)); lastj = j; }
+        });
+    }
     if (blockIdx.x == 0 && tid == 0) p.scal[2] = p.gflag ? (unsigned int)BR : 0u;     // (0: no flags were written)
     if (p.gflag && tid == 0) {
         p.gflag[(long)bh * ((N + BR - 1) / BR) + I] = gather;
@@ -775,16 +867,18 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PAIR ? 
         if (active && h == 0 && p.iters) p.iters[(long)bh * N + qw0 + n] = iters;
         for (int i = tid; i < MR * W; i += THREADS)
             if (I * MR + i / W < T) p.mask[((long)bh * T + (long)I * MR + i / W) * W + (i % W)] = (int32_t)fmk[i];
+    } else {
+        __syncthreads();
+        for (int i = tid; i < MR * W; i += THREADS)
+            if (I * MR + i / W < T) p.wmask[((long)bh * T + (long)I * MR + i / W) * W + (i % W)] = (int32_t)wm[i];
     }
-    for (int i = tid; i < MR * W; i += THREADS)
-        if (I * MR + i / W < T) p.wmask[((long)bh * T + (long)I * MR + i / W) * W + (i % W)] = (int32_t)wm[i];
     if (tid < MR && I * MR + tid < T) p.oflag[(long)bh * T + (long)I * MR + tid] = over_s[tid];
     {
         int nover = 0;
         if (tid == 0)
             for (int i = 0; i < MR; ++i) nover += over_s[i];
         const int slot[3] = {0, 8, 9};
-        const unsigned long long val[3] = {ntile_done, (unsigned long long)nover, (tid == 0 && gather) ? (unsigned long long)nrows : 0ull};
+        const unsigned long long val[3] = {(unsigned long long)min(wjt, njt), (unsigned long long)nover, (tid == 0 && gather) ? (unsigned long long)nrows : 0ull};
         flush_counters<3>(blk_stats, p.stats, slot, val, tid, lane);
     }
 }

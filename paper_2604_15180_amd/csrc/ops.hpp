@@ -18,7 +18,6 @@ constexpr int NW_TAU = 4, NBUF_TAU = 2, QB_TAU = 2;
 // alpha = 1.25, 32 heads of 8192 tokens, d = 64).  fp32 inputs (tiles and operands twice as large): 4 waves.
 constexpr int NBUF_TAUL = 2;
 template <class E> constexpr int NW_TAUL = E::EPL == 8 ? 8 : 4;
-template <class E> constexpr int PAIR_TAUL = E::EPL == 8 ? 1 : 0;
 constexpr int NW_OUT = 4, NBUF_OUT = 2;
 constexpr int NW_DQ = 2, NBUF_DQ = 2;
 constexpr int NW_DKDV = 2, NBUF_DKDV = 2;
@@ -81,7 +80,7 @@ struct Ops {
             // refinement on the lists
             static_assert((32 * NW_TAUL<E>) % (32 * QB * NW_OUT) == 0, "an output group lies inside one row group of the list kernel");
             p.grows = 32 * NW_TAUL<E>;
-            rc = launch(tau_list_kernel<E, D, AM, NBINS, NW_TAUL<E>, NBUF_TAUL, PAIR_TAUL<E>>, groups(p, NW_TAUL<E>, 1), NW_TAUL<E> * 64, s, p);
+            rc = launch(tau_list_kernel<E, D, AM, NBINS, NW_TAUL<E>, NBUF_TAUL>, groups(p, NW_TAUL<E>, 1), NW_TAUL<E> * 64, s, p);
             if (rc) return rc;
             // sweep-based fallback for row blocks whose lists overflowed (exits at once elsewhere);
             // two rows per lane (packed 16-bit histogram counters) while a bin cannot overflow

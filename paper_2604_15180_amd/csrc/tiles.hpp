@@ -84,6 +84,13 @@ struct F32 {
 // After the last mma_acc on `c` and before its first other use: outlasts the MFMA pipeline.
 EA_DEV void settle_acc(f32x16& c) { asm volatile("s_nop 15\n\ts_nop 7" : "+a"(c)); }
 
+// The same for accumulators in VGPRs that assembly statements are about to read (the compiler keeps the distance for its
+// own instructions only): 32x32 products of 16-bit types take 8 passes, of fp32 16.
+template <class E> EA_DEV void settle_vec(f32x16& a, f32x16& b) {
+    if constexpr (E::EPL == 8) asm volatile("s_nop 13" : "+v"(a), "+v"(b));
+    else asm volatile("s_nop 15\n\ts_nop 3" : "+v"(a), "+v"(b));
+}
+
 // tile row held by accumulator register v (0..15) of block kb in lane half h
 EA_DEV int trow(int kb, int v, int h) { return 32 * kb + 16 * (v >> 3) + 8 * h + (v & 7); }
 // tile row fed to MFMA row m (inverse view of the above)
@@ -136,6 +143,7 @@ EA_DEV uint64_t uniform_address(const void* p) {      // the same value in scala
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a), hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
     return ((uint64_t)hi << 32) | lo;
 }
+EA_DEV float uniform(float x) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(x))); }
 EA_DEV uint32_t lds_address(const void* p) {          // LDS byte address of a pointer into LDS, scalar
     return __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)p);
 }
@@ -181,6 +189,50 @@ EA_DEV void lds_add_at(uint32_t addr, uint32_t v) {   // (LDS byte address at ha
 EA_DEV void lds_and_b32(const void* p, uint32_t v) {
     const uint32_t addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
     asm volatile("ds_and_b32 %0, %1" : : "v"(addr), "v"(v) : "memory");
+}
+// The lanes whose score is at or above `low` append (score, key0 | OFF) at base + at, and move `at` on by the step of a row
+// list (LIST_STEP).  One statement, as the compiler's own form of it takes twice the instructions; all lanes are active.
+template <int OFF> EA_DEV void list_candidate(float score, float low, uint32_t key0, uint32_t& at, uint64_t base_uniform) {
+    asm volatile("v_cmp_ge_f32_e32 vcc, %[sc], %[low]\n\t"
+                 "s_cbranch_vccz .Lno_candidate%=\n\t"
+                 "s_mov_b64 exec, vcc\n\t"
+                 "v_mov_b32_e32 v118, %[sc]\n\t"
+                 "v_or_b32_e32 v119, %[off], %[key0]\n\t"
+                 "global_store_dwordx2 %[at], v[118:119], %[base]\n\t"
+                 "v_add_u32_e32 %[at], 8, %[at]\n\t"
+                 "s_mov_b64 exec, -1\n"
+                 ".Lno_candidate%=:"
+                 : [at] "+v"(at) : [sc] "v"(score), [low] "v"(low), [key0] "v"(key0), [off] "n"(OFF), [base] "s"(base_uniform) : "memory", "vcc", "v118", "v119");
+}
+// The same, and one more (`one`) in the LDS counter of the score's bin: at counters | max(int(c4 score + k4), bottom4) & slots
+// (a score that rounding puts a hair below the lowest bin goes there)
+template <int OFF> EA_DEV void list_and_count_candidate(float score, float low, uint32_t key0, uint32_t& at, uint64_t base_uniform, float c4_uniform, float k4,
+                                                        float bottom4, uint32_t counters, uint32_t slots, uint32_t one_uniform) {
+    asm volatile("v_cmp_ge_f32_e32 vcc, %[sc], %[low]\n\t"
+                 "s_cbranch_vccz .Lno_candidate%=\n\t"
+                 "s_mov_b64 exec, vcc\n\t"
+                 "v_mov_b32_e32 v118, %[sc]\n\t"
+                 "v_or_b32_e32 v119, %[off], %[key0]\n\t"
+                 "v_fma_f32 v120, %[c4], %[sc], %[k4]\n\t"
+                 "global_store_dwordx2 %[at], v[118:119], %[base]\n\t"
+                 "v_max_f32_e32 v120, %[bottom], v120\n\t"
+                 "v_cvt_i32_f32_e32 v120, v120\n\t"
+                 "v_mov_b32_e32 v121, %[one]\n\t"
+                 "v_and_or_b32 v120, v120, %[slots], %[counters]\n\t"
+                 "v_add_u32_e32 %[at], 8, %[at]\n\t"
+                 "ds_add_u32 v120, v121\n\t"
+                 "s_mov_b64 exec, -1\n"
+                 ".Lno_candidate%=:"
+                 : [at] "+v"(at)
+                 : [sc] "v"(score), [low] "v"(low), [key0] "v"(key0), [off] "n"(OFF), [base] "s"(base_uniform), [c4] "s"(c4_uniform), [k4] "v"(k4),
+                   [bottom] "v"(bottom4), [counters] "v"(counters), [slots] "s"(slots), [one] "s"(one_uniform)
+                 : "memory", "vcc", "v118", "v119", "v120", "v121");
+}
+// the lane's number, not to be held in a register from one use to the next
+EA_DEV int lane_id_opaque() {
+    int l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+    return l;
 }
 EA_DEV void lds_settle() { __builtin_amdgcn_s_waitcnt(0xc07f); }   // lgkmcnt(0) only (gfx9 encoding)
 
@@ -453,6 +505,17 @@ template <int G> EA_DEV float group_sum(float v) {
     return v;
 }
 
+// maximum over the wave's lanes, in a scalar register
+EA_DEV int wave_max(int v) {
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x141, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x140, 0xf, 0xf, false));
+    const auto x = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
+    v = max((int)x[0], (int)x[1]);
+    const auto y = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
+    return __builtin_amdgcn_readfirstlane(max((int)y[0], (int)y[1]));
+}
 EA_DEV float wave_max(float v) {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
@@ -471,12 +534,12 @@ EA_DEV void xhalf_both(float v, float& lo, float& hi) {
 // of the instructions.
 EA_DEV float max3_raw(float a, float b, float c) { float r; asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c)); return r; }
 EA_DEV float max2_raw(float a, float b) { float r; asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b)); return r; }
-// maximum of registers off .. off+7 of an accumulator
+// maximum of registers off .. off+7 of an accumulator (one statement: the compiler puts a wait state after each)
 EA_DEV float max8_raw(const f32x16& C, int off) {
-    float m = max3_raw(C[off], C[off + 1], C[off + 2]);
-    m = max3_raw(m, C[off + 3], C[off + 4]);
-    m = max3_raw(m, C[off + 5], C[off + 6]);
-    return max2_raw(m, C[off + 7]);
+    float m;
+    asm("v_max3_f32 %0, %1, %2, %3\n\tv_max3_f32 %0, %0, %4, %5\n\tv_max3_f32 %0, %0, %6, %7\n\tv_max_f32 %0, %0, %8"
+        : "=&v"(m) : "v"(C[off]), "v"(C[off + 1]), "v"(C[off + 2]), "v"(C[off + 3]), "v"(C[off + 4]), "v"(C[off + 5]), "v"(C[off + 6]), "v"(C[off + 7]));
+    return m;
 }
 EA_DEV float xhalf_max(float v) { float a, b; xhalf_both(v, a, b); return max2_raw(a, b); }
 EA_DEV float xhalf_sum(float v) { float a, b; xhalf_both(v, a, b); return a + b; }
