@@ -24,15 +24,16 @@ constexpr int BWD_COLS_KEYS = 16;        // keys per work-group of bwd_cols_kern
 // Backward: support entries per lane list (two lists per row) and entries per key in the lists by key.
 constexpr int BWD_LIST_CAP = 64, KEY_LIST_CAP = 128;
 // Non-zeros per marked 64 x 64 tile up to which a row group's backward takes the gather path.  Gather
-// and matrix time of both directions: about 0.09 ns per entry and 6.3 ns per tile at head dim 64 (64 heads of 4096 tokens,
-// sigma = 1.5: with a limit of 8 / 32 / 64 / 128 the backward takes 1023 / 391 / 366 / 361 us), 0.13 and
-// 13.4 ns at head dim 128, where the gather's rows are twice as long (16384 tokens, sigma = 1, 32 / 40 / 64 / 128:
-// 2133 / 2047 / 1958 / 1924 us; the limit dates from when hub keys were summed by atomics, and 64 and 128 were slower).
-// The power functions of general alpha weigh on both sides alike.
+// and matrix time of both directions: about 0.09 ns per entry and 6.3 ns per tile at head dim 64, 0.13 and
+// 13.4 ns at head dim 128, where the gather's rows are twice as long: level near 70 and 100 entries.  A few groups left to
+// the matrix kernels cost more than their tiles, though: the fp16 copies, max |dO| and a partly filled launch of each.  Step with 64 / 128 at
+// head dim 64: 1088 tokens 152 / 139 us, 8192 tokens, alpha = 2, 808 / 746, 8192, alpha = 1.25, 1265 / 1243, 4096, sigma = 1.5, level (783 / 791);
+// with 40 / 96 at head dim 128: 16384 tokens, sigma = 1, 4415 / 4281, block-structured 1857 / 1722.  (The smaller limits dated from when hub keys
+// were summed by atomics.)  The power functions of general alpha weigh on both sides alike.
 // fp32 matrix products run at a sixteenth of the 16-bit rate, 72 ns per tile: 16 heads of 2048 tokens at d = 64,
 // sigma = 1, backward with 40 / 128 / 512: 631 / 265 / 121 us.  Attention sinks do not change the picture: 32 heads
 // of 4096 tokens at d = 64 with one, gather 149, matrix 311 us; with four 268 and 225.
-constexpr int bwd_entries_per_tile(int d, int elem_bytes) { return elem_bytes == 4 ? 512 : d == 64 ? 64 : 40; }
+constexpr int bwd_entries_per_tile(int d, int elem_bytes) { return elem_bytes == 4 ? 512 : d == 64 ? 128 : 96; }
 // ... or, in a group with at most BWD_FEW_TILES marked tiles, BWD_ENTRIES_PER_ROW per row (at head dim 128).
 constexpr int BWD_ENTRIES_PER_ROW = 6, BWD_FEW_TILES = 40;
 // The gather kernels' fixed cost is a few passes over dK and dV, 0.3 - 0.45 ns per row: what the matrix
