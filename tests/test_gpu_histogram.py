@@ -203,6 +203,13 @@ def test_histogram_root_from_each_closed_form_bound(ea, dtype, d, alpha, scale, 
     test_histogram_root_brackets_the_threshold(ea, dtype, d, alpha, "gauss", scale, causal)
 
 
+@pytest.mark.parametrize("dtype,d,alpha,scale,causal", [("bf16", 64, 1.5, 0.45, False), ("bf16", 64, 1.5, 0.6, False), ("bf16", 128, 1.5, 0.6, True),
+                                                        ("bf16", 128, 1.25, 0.8, False), ("bf16", 64, 2.0, 0.3, False), ("f32", 64, 1.5, 0.6, False)])
+def test_histogram_of_long_lists(ea, dtype, d, alpha, scale, causal):
+    # supports of one to several hundred keys: lists that are counted as they grow, pruned at a refresh of the bound, or full
+    test_histogram_root_brackets_the_threshold(ea, dtype, d, alpha, "gauss", scale, causal)
+
+
 @pytest.mark.parametrize("dtype,d,alpha,scale", [("bf16", 64, 1.01, 3.0), ("bf16", 128, 1.03, 3.0)])
 def test_histogram_root_for_alpha_near_one(ea, dtype, d, alpha, scale):
     # where the closed-form bound lies many bins below the root (see tests/host/histogram_main.cpp)
