@@ -423,15 +423,18 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 8
     // list length from which on a refresh drops entries below the bound (it takes two passes over memory: later where
     // the histogram needs no pass of its own; 16384 tokens, sigma = 1, 144 / 208: 2600 / 2546 us)
     constexpr int PRUNE_FROM = 144, PRUNE_FROM_COUNTING = 208;
+    // prunes of a wave at most: what they drop stays counted.  (A list that is full after them flags its block, as any other.)
+    constexpr int MAX_PRUNES = 120;
     // Groups of eight scores of a wave's first tile (of 256) with a candidate from which its entries are counted as they are
     // listed: long lists then need no pass to be counted.  112 / 180 / 230 / never: 4096 tokens, sigma = 1.5, 531 / 428 / 425 / 425,
     // 16384 tokens, sigma = 1, 2530 / 2530 / 2600 / 3300 us.
     constexpr int FIRST_TILE_BUSY = 180;
     constexpr int TILE_ENTRIES = 32;     // entries a lane can list from one tile
     constexpr int REG_ENTRIES = 16;      // entries per lane held in registers after the sweep
-    // counters: waves 2w and 2w + 1 share the words of one histogram buffer, 16 bits each
+    // counters: waves 2w and 2w + 1 share the words of one histogram buffer, 16 bits each.  A row counts what its two lists
+    // hold in the end and what prunes dropped from them.
     constexpr int CB = 16;
-    static_assert(NW % 2 == 0 && 2 * LIST_CAP < 65536, "a counter holds what two lists can count");
+    static_assert(NW % 2 == 0 && 2 * LIST_CAP * (MAX_PRUNES + 1) < 65536, "a counter holds what a row can count");
     constexpr int RING_BYTES = NBUF * KT::BYTES, HIST_BYTES = NW / 2 * 32 * SLOTS * 4;
     __shared__ __align__(1024) char lds[RING_BYTES + HIST_BYTES];
     char* const kring = lds;
@@ -630,6 +633,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 8
         listed = true;
         __builtin_amdgcn_s_setprio(0);
     };
+    int prunes = 0;
     // a better lower bound from the histogram so far
     auto refresh = [&] {
         count_lists();
@@ -639,7 +643,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 8
         lowraw = braw - fabsf(braw) * 1e-6f;
         low = max2_raw(low, lowraw);
         int cnt = entries(), most = wave_max(cnt);
-        if (most > (counting ? PRUNE_FROM_COUNTING : PRUNE_FROM) && most <= LIST_CAP) {
+        if (most > (counting ? PRUNE_FROM_COUNTING : PRUNE_FROM) && most <= LIST_CAP && prunes < MAX_PRUNES) {
+            ++prunes;
             // long lists: entries below the bound are dropped, the others move to the front in their order (counted they stay:
             // bins below the histogram's root have no part in it, nor in the root of any later one)
             uint32_t front = list0();

@@ -144,7 +144,7 @@ def test_maximum_sequence_length(ea, recipe):
 def test_flat_attention_at_65536_tokens(ea):
     # From 65536 keys on a histogram bin can hold more keys than a 16-bit counter, so the sweep-based
     # threshold kernel switches to its variant with 32-bit counters; the list kernel's shared 16-bit
-    # counters only ever count listed candidates (at most 512 per row).  Tiny scores put every
+    # counters only ever count listed candidates (at most 512 per row at a time, and what prunes dropped).  Tiny scores put every
     # visible key within one unit of the row's maximum: all but the first rows overflow their
     # lists, are redone by the sweep-based kernel, and have thousands of keys in the support.
     B, H, N, d, alpha, causal = 1, 1, 65536, 64, 1.5, True

@@ -6,7 +6,7 @@ import pytest
 import torch
 
 import workloads
-from tests import parity
+from tests import list_replay, parity
 
 pytestmark = pytest.mark.gpu
 
@@ -246,3 +246,69 @@ def test_histogram_of_rising_maxima(ea, dtype, d, alpha, causal):
     diff = np.abs(t0[0, 0] - want)
     # a score that fp32 puts on the other side of a bin edge moves one count by one bin
     assert (diff <= 1e-4 * (1.0 + np.abs(want))).mean() >= 0.995 and diff.max() <= 1.0 / nb + 1e-4
+
+
+def rising_root_scores():
+    """Scores (alpha = 1.5) of one row whose threshold rises through a single histogram bin in 232 steps: 24 keys in the top bin put the
+    root 12.86 bins below it, and each step's key, two bins above the root, raises it by a few hundredths of a bin.  All other
+    keys lie just above the root of their step: each is listed, and dropped by the next prune.  Steps are as long
+    as the two lists of the row have room for (n kept entries per list, 64 or so more in each pair of tiles)."""
+    nb = 63.0
+    key = np.arange(64)
+    halves = [key[(key >> 3) & 1 == s] for s in (0, 1)]
+
+    def root(n):                                     # 24 (0 - tau)^2 + n (-11/63 - tau)^2 = 1
+        a, b, c = 24.0 + n, 2 * n * 11 / nb, n * (11 / nb) ** 2 - 1.0
+        return (-b - np.sqrt(b * b - 4 * a * c)) / (2 * a)
+
+    top = np.full(64, -3.0)
+    top[np.concatenate([s[:12] for s in halves])] = 0.5 / nb
+    tiles, kept = [top, np.full(64, -3.0)], 12
+    for n in range(232):
+        pairs = 3 if kept + 192 <= 256 else 2
+        step = np.full((2 * pairs, 64), root(n) + 1e-5)
+        step[-1, halves[n & 1][5]] = -10.5 / nb
+        tiles.extend(step)
+        kept = 12 + (n + 2) // 2
+    return np.concatenate(tiles)
+
+
+def test_counters_of_pruned_lists_do_not_overflow(ea):
+    # A prune drops entries that stay counted, so a row's counters can take in far more than its lists ever hold at once.  Rows
+    # 0 - 31 would put 72000 keys into one bin if their lists were pruned at every chance; their 16-bit counters lie beside those of
+    # rows 32 - 63, whose two keys of support a carry would hide: the carry lands five bins below their maximum.
+    alpha, nb, d = 1.5, ea.entmax_attn_histogram_bins(), 64
+    x = rising_root_scores()
+    N = x.size
+    print(f"counters of pruned lists, N={N}", flush=True)
+    freely = list_replay.replay_wave(np.broadcast_to(x, (32, N)), alpha, nb, MAX_PRUNES=1 << 30)
+    assert freely["max_count"] > 65536 and not freely["overflow"], freely
+    assert list_replay.replay_wave(np.broadcast_to(x, (32, N)), alpha, nb)["max_count"] < 65536
+    other = np.full(N, -3.0)
+    other[20], other[N - 10] = (51 + 5.5) / nb, (51 + 5.5) / nb - 0.9
+    # the scores as sums of three bf16 parts each, which the queries' ones pick: x = (alpha - 1) <q, k> / 8 with q = 16
+    k, q = torch.zeros(N, d), torch.zeros(N, d)
+    for first, scores in ((0, x), (3, other)):
+        left = torch.from_numpy(scores).clone()
+        for i in range(3):
+            k[:, first + i] = left.to(torch.bfloat16).float()
+            left -= k[:, first + i].double()
+    k[7, 6] = 4.0
+    q[:32, 0:3], q[32:64, 3:6], q[64:, 6] = 16.0, 16.0, 16.0
+    v = torch.randn(N, d, generator=torch.Generator().manual_seed(3))
+    q, k, v = (t.to(torch.bfloat16)[None, None] for t in (q, k, v))
+    ws = torch.empty(ea.entmax_attn_workspace_bytes(1, 1, N, d, "bf16", False, False), dtype=torch.uint8, device="cuda")
+    O, tau, _ = ea.entmax_attn_fwd(q.cuda(), k.cuda(), v.cuda(), alpha, False, workspace=ws)
+    tau0, upper = ea.entmax_attn_fwd_histogram_bounds(ws, 1, 1, N, d, "bf16")
+    torch.cuda.synchronize()
+    X = parity.to_np64(k)[0, 0, :, :6] @ np.repeat(np.eye(2), 3, 0)
+    for rows, scores in ((slice(0, 32), X[:, 0]), (slice(32, 64), X[:, 1])):
+        lo, hi = scores.max() - 1.0, scores.max()
+        for _ in range(60):
+            mid = 0.5 * (lo + hi)
+            lo, hi = (mid, hi) if (np.maximum(scores - mid, 0.0) ** 2).sum() >= 1.0 else (lo, mid)
+        P = np.maximum(scores - lo, 0.0) ** 2
+        t0, up, t, o = (parity.to_np64(a)[0, 0, rows] for a in (tau0, upper, tau, O))
+        print("  tau*", lo, "tau_0", t0.min(), t0.max(), "upper", up.min(), up.max(), flush=True)
+        assert (t0 <= lo + 3e-5).all() and (lo <= up + 3e-5).all() and (up - t0 <= 1.0 / nb + 1e-4).all()
+        assert np.abs(t - lo).max() <= parity.TOL[torch.bfloat16]["tau"] and np.abs(o - P @ parity.to_np64(v)[0, 0]).max() <= parity.TOL[torch.bfloat16]["O"]
