@@ -423,6 +423,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 8
     // list length from which on a refresh drops entries below the bound (it takes two passes over memory: later where
     // the histogram needs no pass of its own; 16384 tokens, sigma = 1, 144 / 208: 2600 / 2546 us)
     constexpr int PRUNE_FROM = 144, PRUNE_FROM_COUNTING = 208;
+    // ... and only while the row with most keys of support so far, and the count that it will grow to if it keeps rising with the
+    // logarithm of the keys seen, leave room in the lists: a prune of every wave costs as much as the fallback kernel, and one that drops
+    // little only puts the overflow off.  Forward, 32 heads of 4096 tokens, d = 64, pruned always / by this rule / never: alpha = 1.5, sigma = 0.4,
+    // 3260 / 1800 / 1220 us, alpha = 1.25, sigma = 1.2, 2620 / 1520 / 1260; where the lists hold out in the end a few rows in the fallback
+    // kernel cost all its time: alpha = 1.25, sigma = 1.5, 680 / 680 / 1145, 8 heads of 16384, sigma = 0.7, 1260 / 1260 / 2240.
+    constexpr int PRUNE_SUPPORT = 352;
+    constexpr float PRUNE_SUPPORT_END = 576.f;
     // prunes of a wave at most: what they drop stays counted.  (A list that is full after them flags its block, as any other.)
     constexpr int MAX_PRUNES = 120;
     // Groups of eight scores of a wave's first tile (of 256) with a candidate from which its entries are counted as they are
@@ -458,7 +465,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 8
     const elem* Qh = (const elem*)p.Q + (long)bh * N * D;
     const elem* Kh = (const elem*)p.K + (long)bh * N * D;
     const int njt = p.causal ? min((int)((q0 + BR) / 64), T) : T;
-    const int wjt = !active ? 0 : p.causal ? (int)((qw0 + 31) / 64) + 1 : T;
+    int wjt = !active ? 0 : p.causal ? (int)((qw0 + 31) / 64) + 1 : T;      // tiles this wave works on
     const int jdiag = p.causal ? (int)(qw0 / 64) : T;     // the first tile that holds keys past a row of this wave
     const int myrow = (wave * 32) / 64;
     const HeadConsts hc = head_consts(p, bh);
@@ -501,17 +508,17 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 8
 
     // Root of the row's histogram (Eq. 9) as it stands (both lanes of a row hold the same): tau_0 =
     // max(tau_h, max - 1) less the fp32 slack, and the bracket's upper end.
-    // (coarse: while the sweep runs only a lower bound is wanted; for general alpha, whose exact
+    // (`support`, the counts above it: while the sweep runs only a lower bound is wanted; for general alpha, whose exact
     // solve takes power functions per bin, the closed-form bound then stands in for the root)
-    auto histogram_bound = [&](float& lo, float& up, bool coarse) {
+    auto histogram_bound = [&](float& lo, float& up, int* support) {
         lds_settle();
         const int a_lo = a_top == INT_MIN ? 0 : a_top - (SLOTS - 1);
         const float origin = (float)a_lo * hb;                        // left edge of the window
         float tau_h, gap = 0.f;
-        if (AM == ALPHA_GEN && coarse)
-            tau_h = histogram_lower_bound<SLOTS, CB, true>(hrow, a_lo & (SLOTS - 1), hshift, hb, r) + origin;
+        if (AM == ALPHA_GEN && support)
+            tau_h = histogram_lower_bound<SLOTS, CB, true>(hrow, a_lo & (SLOTS - 1), hshift, hb, r, support) + origin;
         else
-            tau_h = solve_histogram<AM, SLOTS, CB, true>(hrow, a_lo & (SLOTS - 1), hshift, hb, r, fmaf(c, run, -1.f) - origin, gap) + origin;
+            tau_h = solve_histogram<AM, SLOTS, CB, true>(hrow, a_lo & (SLOTS - 1), hshift, hb, r, fmaf(c, run, -1.f) - origin, gap, support) + origin;
         const float slack = 1e-6f + 2.5e-7f * fabsf(origin);          // fp32 rounding of bins and closed form
         lo = fmaxf(tau_h - slack, fmaf(c, run, -1.f));
         up = tau_h + (hb + gap) + slack;
@@ -634,16 +641,22 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 8
         __builtin_amdgcn_s_setprio(0);
     };
     int prunes = 0;
-    // a better lower bound from the histogram so far
-    auto refresh = [&] {
+    // a better lower bound from the histogram so far, after `tiles` tiles
+    auto refresh = [&](int tiles) {
         count_lists();
         float lo, up;
-        histogram_bound(lo, up, true);
+        int support;
+        histogram_bound(lo, up, &support);
         const float braw = lo * inv_c;
         lowraw = braw - fabsf(braw) * 1e-6f;
         low = max2_raw(low, lowraw);
         int cnt = entries(), most = wave_max(cnt);
-        if (most > (counting ? PRUNE_FROM_COUNTING : PRUNE_FROM) && most <= LIST_CAP && prunes < MAX_PRUNES) {
+        if (most > LIST_CAP) { wjt = tiles; return; }    // the block is redone: nothing more is listed
+        auto room = [&] {
+            const int s = wave_max(support);
+            return s <= PRUNE_SUPPORT && (float)s * (1.f + 0.69f * __builtin_amdgcn_logf((float)wjt / (float)tiles)) <= PRUNE_SUPPORT_END;
+        };
+        if (most > (counting ? PRUNE_FROM_COUNTING : PRUNE_FROM) && prunes < MAX_PRUNES && room()) {
             ++prunes;
             // long lists: entries below the bound are dropped, the others move to the front in their order (counted they stay:
             // bins below the histogram's root have no part in it, nor in the root of any later one)
@@ -664,7 +677,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 8
         trig = (uint32_t)(most + GROW) * LIST_STEP;
         // (the two tiles before the next look at the lists add up to TILE_ENTRIES each)
         tight = most > LIST_CAP - 3 * TILE_ENTRIES;
-        trig_hard = most >= LIST_CAP ? UINT_MAX : (uint32_t)(most + (counting ? GROW_COUNTING : GROW_HARD)) * LIST_STEP;
+        trig_hard = (uint32_t)min(most + (counting ? GROW_COUNTING : GROW_HARD), LIST_CAP + 1) * LIST_STEP;
         if (!tight) trig_hard = min(trig_hard, (uint32_t)(LIST_CAP - 2 * TILE_ENTRIES + 1) * LIST_STEP);
     };
     // Tile it + 1 is loaded under the scores of tile it and waited for before the tile's candidates are listed: the
@@ -687,7 +700,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 8
             if (!listed || tiles >= wjt) return;
             listed = false;
             const bool scheduled = tiles >= FIRST_REFRESH && (tiles & (tiles - 1)) == 0;
-            if (__any(at - list0() >= (scheduled ? min(trig, trig_hard) : trig_hard))) refresh();
+            if (__any(at - list0() >= (scheduled ? min(trig, trig_hard) : trig_hard))) refresh(tiles);
         };
         if constexpr (D == 128 && E::EPL == 8) {
             // (two tiles a turn: the buffers' addresses are then constants, 8 instructions a tile; at d = 64 it is 4, and
@@ -753,7 +766,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 8
                 if (rel >= bottom4) lds_add_at(hrow_lds + ((uint32_t)(int)rel & (4 * SLOTS - 4)), one);
             });
         } else count_lists();
-        histogram_bound(thr0, bhi, false);
+        histogram_bound(thr0, bhi, nullptr);
         if (h == 0) {
             p.rs_t0[(long)bh * N + qw0 + n] = thr0;
             p.rs_up0[(long)bh * N + qw0 + n] = bhi;

@@ -29,14 +29,14 @@ namespace ea {
 // with the general solve below: alpha = 1.25, 32 heads of 8192 tokens 1633 -> 1447 us, 64 heads of 4096 tokens at
 // alpha = 1.5 907 -> 858 us (d = 64).
 // Returns the root in units above the origin - the root tau_h of f_h (Eq. 9) itself where equality
-// holds, else a value below it; -h for an empty histogram.
+// holds, else a value below it; -h for an empty histogram.  *active, if wanted: the counts of the active set.
 template <int BITS> EA_DEV uint32_t histogram_count(const uint32_t* H, int slot, int shift) {
     const uint32_t w = H[slot];
     if constexpr (BITS == 32) return w;
     else return (w >> shift) & ((1u << (BITS & 31)) - 1u);
 }
 template <int MOM, int SLOTS, int BITS, bool PAIRED>
-EA_DEV float histogram_moment_root(const uint32_t* H, int rot, int shift, float h, float r) {
+EA_DEV float histogram_moment_root(const uint32_t* H, int rot, int shift, float h, float r, int* active = nullptr) {
     using I = int;                                     // (at most 2^17 counts: S2 stays below 2^30)
     constexpr int NB = SLOTS - 1, NCH = SLOTS / 8;
     static_assert(NCH % 2 == 0, "chunks are shared by the two lanes of a row");
@@ -85,6 +85,7 @@ EA_DEV float histogram_moment_root(const uint32_t* H, int rot, int shift, float 
         S0 += c; S1 += (I)t * c; S2 += (I)(t * t) * c;
         if (c > 0 && inside(S0, S1, S2, t)) { B0 = S0; B1 = S1; B2 = S2; }
     }
+    if (active) *active = B0;
     if (B0 == 0) return -h;
     const float n = (float)B0, inv = 1.f / n;
     float t_root;
@@ -100,10 +101,10 @@ EA_DEV float histogram_moment_root(const uint32_t* H, int rot, int shift, float 
 }
 // A lower bound of the histogram's root for general alpha, from the closed forms alone
 template <int SLOTS, int BITS, bool PAIRED>
-EA_DEV float histogram_lower_bound(const uint32_t* H, int rot, int shift, float h, float r) {
-    if (r >= 2.f) return histogram_moment_root<3, SLOTS, BITS, PAIRED>(H, rot, shift, h, r);
-    if (r >= 1.f) return histogram_moment_root<2, SLOTS, BITS, PAIRED>(H, rot, shift, h, r);
-    return histogram_moment_root<1, SLOTS, BITS, PAIRED>(H, rot, shift, h, r);
+EA_DEV float histogram_lower_bound(const uint32_t* H, int rot, int shift, float h, float r, int* active = nullptr) {
+    if (r >= 2.f) return histogram_moment_root<3, SLOTS, BITS, PAIRED>(H, rot, shift, h, r, active);
+    if (r >= 1.f) return histogram_moment_root<2, SLOTS, BITS, PAIRED>(H, rot, shift, h, r, active);
+    return histogram_moment_root<1, SLOTS, BITS, PAIRED>(H, rot, shift, h, r, active);
 }
 // Newton steps from the left for f = F - 1, F(tau) = sum_k c_k [y_k]_+^r with r >= 1: f is convex and falls with tau,
 // so the iterates rise and stay at or below the root.  eval(tau, F, G) gives F and G = sum c y^(r-1).
@@ -133,12 +134,12 @@ template <class Eval> EA_DEV float newton_from_left(Eval eval, float tau, float 
 
 // The root tau_h of f_h(tau) = -1 + sum_k H_k [k h - tau]_+^r (Eq. 9) in units above the origin;
 // -h for an empty histogram.  general alpha: `start` is a point known to lie at or below tau* (the row's maximum
-// - 1), and tau* is at most h + gap above the result; otherwise neither is used.
+// - 1), and tau* is at most h + gap above the result; otherwise neither is used.  `active`: closed forms only.
 template <int AM, int SLOTS, int BITS, bool PAIRED>
-EA_DEV float solve_histogram(const uint32_t* H, int rot, int shift, float h, float r, float start, float& gap) {
+EA_DEV float solve_histogram(const uint32_t* H, int rot, int shift, float h, float r, float start, float& gap, int* active = nullptr) {
     gap = 0.f;
-    if constexpr (AM == ALPHA_15) return histogram_moment_root<2, SLOTS, BITS, PAIRED>(H, rot, shift, h, r);
-    else if constexpr (AM == ALPHA_20) return histogram_moment_root<1, SLOTS, BITS, PAIRED>(H, rot, shift, h, r);
+    if constexpr (AM == ALPHA_15) return histogram_moment_root<2, SLOTS, BITS, PAIRED>(H, rot, shift, h, r, active);
+    else if constexpr (AM == ALPHA_20) return histogram_moment_root<1, SLOTS, BITS, PAIRED>(H, rot, shift, h, r, active);
     else {
         // PAIRED: a lane takes every other bin.  Eight bins are read together (one at a time, each read
         // waits for the one before), down to the chunk that no lane's threshold reaches.

@@ -12,7 +12,7 @@ _CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 def constants():
     text = "".join(open(os.path.join(_CSRC, f)).read() for f in ("common.hpp", "fwd_kernels.hpp"))
-    names = ("LIST_CAP", "GROW", "GROW_COUNTING", "GROW_HARD", "FIRST_REFRESH", "PRUNE_FROM", "PRUNE_FROM_COUNTING", "MAX_PRUNES",
+    names = ("LIST_CAP", "GROW", "GROW_COUNTING", "GROW_HARD", "FIRST_REFRESH", "PRUNE_FROM", "PRUNE_FROM_COUNTING", "MAX_PRUNES", "PRUNE_SUPPORT", "PRUNE_SUPPORT_END",
              "FIRST_TILE_BUSY", "TILE_ENTRIES")
     return {n: int(re.search(r"\b%s = (\d+)" % n, text).group(1)) for n in names}
 
@@ -82,7 +82,11 @@ def replay_wave(X, alpha, nb, **override):
         max_count = max(max_count, int(counts.max()))
         root = np.maximum(_roots(edges, counts, r, h), run - 1.0)
         low = np.maximum(low, root)
-        if most > k["PRUNE_FROM_COUNTING" if counting else "PRUNE_FROM"] and most <= k["LIST_CAP"] and prunes < k["MAX_PRUNES"]:
+        if most > k["LIST_CAP"]:
+            break                                            # the block is redone: nothing more is listed
+        support = int((counts * (edges[None] > root[:, None])).sum(1).max())
+        if (most > k["PRUNE_FROM_COUNTING" if counting else "PRUNE_FROM"] and prunes < k["MAX_PRUNES"] and support <= k["PRUNE_SUPPORT"]
+                and support * (1.0 + np.log(tiles / (j + 1))) <= k["PRUNE_SUPPORT_END"]):
             before = sum(map(len, lists))
             lists = [[e for e in entries if e[0] >= low[lane & 31]] for lane, entries in enumerate(lists)]
             prunes += 1
@@ -92,7 +96,7 @@ def replay_wave(X, alpha, nb, **override):
         out["longest"] = max(out["longest"], most)
         trig = most + k["GROW"]
         tight = most > k["LIST_CAP"] - 3 * k["TILE_ENTRIES"]
-        trig_hard = most + k["GROW_COUNTING" if counting else "GROW_HARD"] if most < k["LIST_CAP"] else 1 << 30
+        trig_hard = min(most + k["GROW_COUNTING" if counting else "GROW_HARD"], k["LIST_CAP"] + 1)
         if not tight:
             trig_hard = min(trig_hard, k["LIST_CAP"] - 2 * k["TILE_ENTRIES"] + 1)
     out.update(counting=counting, prunes=prunes, max_count=max_count, longest=max(out["longest"], max(map(len, lists))))

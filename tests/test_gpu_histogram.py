@@ -312,3 +312,23 @@ def test_counters_of_pruned_lists_do_not_overflow(ea):
         print("  tau*", lo, "tau_0", t0.min(), t0.max(), "upper", up.min(), up.max(), flush=True)
         assert (t0 <= lo + 3e-5).all() and (lo <= up + 3e-5).all() and (up - t0 <= 1.0 / nb + 1e-4).all()
         assert np.abs(t - lo).max() <= parity.TOL[torch.bfloat16]["tau"] and np.abs(o - P @ parity.to_np64(v)[0, 0]).max() <= parity.TOL[torch.bfloat16]["O"]
+
+
+@pytest.mark.parametrize("dtype,d,alpha,scale", [("bf16", 64, 1.5, 0.3), ("bf16", 128, 1.25, 0.6), ("f32", 64, 1.5, 0.3)])
+def test_walks_whose_lists_overflowed_end_early(ea, dtype, d, alpha, scale):
+    # Flat attention without a mask: every row has more keys of support than its lists hold.  A wave whose list overflowed has nothing more
+    # to list: it works on about the same number of tiles at 1024 and at 2048 tokens, on 10 of 16 and of 32.  (The fallback kernel works
+    # on every tile the same number of times, so per tile of the scores the counter falls by the list kernel's share.)
+    B, H, seen = 1, 2, {}
+    for N in (1024, 2048):
+        print(f"overflowed lists {dtype} d={d} alpha={alpha} N={N}", flush=True)
+        q, k, v, _ = workloads.gaussian_qkv(B, H, N, d, dtype, scale, seed=47)
+        ws = torch.empty(ea.entmax_attn_workspace_bytes(B, H, N, d, dtype, False, False), dtype=torch.uint8, device="cuda")
+        O, tau, mask = ea.entmax_attn_fwd(q.cuda(), k.cuda(), v.cuda(), alpha, False, workspace=ws)
+        torch.cuda.synchronize()
+        st = ea.read_stats(ws)
+        seen[N] = st["tau_subtiles"] / (B * H * (N / 32) * (N / 64))
+        print("  tiles", seen[N], "overflow", st["list_overflow_blocks"], flush=True)
+        assert st["list_overflow_blocks"] == B * H * N // 64
+        parity.check_forward(q, k, v, alpha, False, O, tau, mask, label=f"overflowed lists N={N}")
+    assert seen[1024] - seen[2048] > 0.25
