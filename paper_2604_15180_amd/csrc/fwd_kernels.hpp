@@ -389,7 +389,7 @@ __global__ __launch_bounds__(NW * 64) void tau_kernel(Params p) {
 // above the final one.  Every other score - a handful per row when attention is sparse - is listed, with
 // its key, by the lane that computed it (each lane sees 16 of every 32 keys of its row, so
 // a row has two lists; no atomics, no ordering between lanes).  The lower bound starts as (running maximum - 1);
-// each time a list has grown by a fixed number of entries, the row's LDS histogram of the listed scores (Eq. 6-8;
+// when it is refreshed (see below), the row's LDS histogram of the listed scores (Eq. 6-8;
 // absolute bin grid with a sliding window, as in tau_kernel) is solved (Eq. 9), and its root tau_h, a lower
 // bound of the prefix's tau* by Prop. 1, becomes the new bound.  Scores that were skipped lie below the bound and
 // contribute nothing to f at or above it, so f there, and with it Prop. 1, is that of all scores.
