@@ -332,3 +332,47 @@ def test_walks_whose_lists_overflowed_end_early(ea, dtype, d, alpha, scale):
         assert st["list_overflow_blocks"] == B * H * N // 64
         parity.check_forward(q, k, v, alpha, False, O, tau, mask, label=f"overflowed lists N={N}")
     assert seen[1024] - seen[2048] > 0.25
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64)])
+def test_lists_that_are_pruned_or_nearly_full(ea, dtype, d):
+    # 64-row blocks of eight kinds: four spreads of the scores, and a first tile like the others, so that list entries are counted as they
+    # are listed, or one with two keys near the maximum and the rest far below, so that the lists are counted at a refresh.  Which
+    # branches the lists go through is asked of the replay: pruned (some to an odd length, where the count resumes in the middle of
+    # a load), walked on where the next tiles may fill them, and full, in both modes.
+    from oracle import entmax_oracle as eo
+    B, H, N, alpha = 1, 1, 2048, 1.5
+    print(f"pruned and nearly full lists {dtype} d={d}", flush=True)
+    q, k, v, _ = workloads.gaussian_qkv(B, H, N, d, "f32", 1.0, seed=61)
+    block = torch.arange(N) // 64
+    q *= torch.tensor([0.1, 0.2, 0.3, 0.35])[block % 4][None, None, :, None]
+    q[..., 0] = torch.where(block // 4 % 2 == 0, 16.0, 0.0)
+    k[..., 0], k[:, :, :64, 0] = 0.0, -4.0
+    k[:, :, 5, 0] = k[:, :, 13, 0] = 0.0
+    q, k, v = (t.to(torch.bfloat16 if dtype == "bf16" else torch.float32) for t in (q, k, v))
+    ws = torch.empty(ea.entmax_attn_workspace_bytes(B, H, N, d, dtype, False, False), dtype=torch.uint8, device="cuda")
+    O, tau, mask = ea.entmax_attn_fwd(q.cuda(), k.cuda(), v.cuda(), alpha, False, workspace=ws)
+    tau0, upper = ea.entmax_attn_fwd_histogram_bounds(ws, B, H, N, d, dtype)
+    torch.cuda.synchronize()
+    nb = ea.entmax_attn_histogram_bins()
+    Qn, Kn = parity.to_np64(q), parity.to_np64(k)
+    X = (alpha - 1.0) * (Qn[0, 0] @ Kn[0, 0].T) / np.sqrt(d)
+    waves = [list_replay.replay_wave(X[w:w + 32], alpha, nb) for w in range(0, N, 32)]
+    longest = [max(a["longest"], b["longest"]) for a, b in zip(waves[::2], waves[1::2])]
+    cap = list_replay.constants()["LIST_CAP"]
+    redone = [n > cap - 8 for n in longest]          # (or nearly: fp32 scores may decide otherwise on an entry or two)
+    assert sum(n > cap + 8 for n in longest) <= ea.read_stats(ws)["list_overflow_blocks"] <= sum(redone)
+    for counting in (False, True):
+        mine = [w for i, w in enumerate(waves) if w["counting"] == counting and not redone[i // 2]]
+        print("  counting", counting, [{n: int(w[n]) for n in ("refreshes", "prunes", "pruned", "tight_tiles", "longest")} for w in mine[:6]], flush=True)
+        assert any(w["prunes_leaving_odd_lists"] for w in mine) and any(w["prunes"] > 1 for w in mine) and any(w["tight_tiles"] for w in mine)
+        assert any(w["counting"] == counting and w["longest"] > cap + 8 for w in waves)
+    ref = eo.attn_fwd(Qn, Kn, parity.to_np64(v), alpha, False, tile=64)
+    parity.check_forward(q, k, v, alpha, False, O, tau, mask, ref=ref, label=f"pruned and nearly full lists {dtype} {d}")
+    t0, up, ts = parity.to_np64(tau0), parity.to_np64(upper), ref["tau"]
+    eps = 3e-5 * (1.0 + np.abs(ts))
+    assert (t0 <= ts + eps).all() and (ts <= up + eps).all() and (up - t0 <= 1.0 / nb + 1e-4).all()
+    want = np.array([max(th, m - 1.0) for th, m in (grid_histogram_root(row, alpha, nb) for row in X)])
+    # (a score that fp32 puts on the other side of a bin edge moves one count by one bin: among n counts the root moves by 1 / (n nb))
+    diff = np.abs(t0[0, 0] - want)
+    assert (diff <= 1e-4 * (1.0 + np.abs(want))).mean() >= 0.5 and diff.max() <= 0.25 / nb, (diff.max(), (diff > 1e-4).mean())
