@@ -716,19 +716,22 @@ __global__ __launch_bounds__(NW * 64) void dkdv_kernel(Params p) {
 //                     bwd_cols_kernel sum each hub key's entries, again in the order of their rows.
 // They read the caller's Q, K, V, dO (not the 16-bit copies) and work in fp32.
 // The gather path pays while a marked 64 x 64 tile holds only a few non-zeros: the group is flagged
-// when its lists hold at most bwd_entries_per_tile entries per marked tile (and no list is full);
-// or BWD_ENTRIES_PER_ROW per row (and no list is full); the sweep is left early once the entries
+// when its lists hold at most bwd_entries_per_tile entries per marked tile (and no list is full;
+// which of the two limits: see there); or BWD_ENTRIES_PER_ROW per row (and no list is full); the sweep is left early once the entries
 // so far run a quarter above that rate.
 
 // Entries a row group may list to take the gather path, by its marked tiles and rows.  A group with few
 // marked tiles (the first rows of a causal head) still has one entry or more per row, and is cheap either way: it
 // goes with the rest, so that the matrix kernels' input copies are not made for its sake alone.
 // Never more than LOG_PER_ROW a row, as in the forward: the log of hub keys has room for that.
-template <class E, int D, int AM> EA_DEV int gather_budget(int marked, int rows) {
+template <class E, int D, int AM> EA_DEV int gather_budget(int marked, int rows, bool higher) {
     constexpr int PER_ROW_X128 = BWD_ENTRIES_PER_ROW * D * D / 128 / (AM == ALPHA_GEN ? 2 : 1);
-    return min(max(bwd_entries_per_tile(D, sizeof(typename E::elem)) * marked, marked <= BWD_FEW_TILES ? PER_ROW_X128 * rows / 128 : 0),
+    return min(max(bwd_entries_per_tile(D, sizeof(typename E::elem), higher) * marked, marked <= BWD_FEW_TILES ? PER_ROW_X128 * rows / 128 : 0),
                LOG_PER_ROW * rows);
 }
+
+// Whether the higher limit holds for a group by what the mask alone says: `marked` of `all` marked tiles, `groups` row groups
+EA_DEV bool higher_limit(int marked, long all, int groups) { return groups <= BWD_FEW_GROUPS || 4l * marked * groups <= all; }
 
 // Set bits of the whole mask, from bwd_begin_kernel's partial sums (called by whole waves)
 EA_DEV long marked_tiles(const Params& p, int lane) {
@@ -766,7 +769,9 @@ __global__ __launch_bounds__(NW * 64) void bwd_list_kernel(Params p) {
 
     // a mask with few marked tiles altogether: the matrix kernels are done before the gather
     // kernels' passes over dK, dV would be
-    if (marked_tiles(p, lane) < (long)BWD_MIN_TILES_PER_BLOCK * p.BH * T) {
+    const int G = (N + BR - 1) / BR;
+    const long all_marked = marked_tiles(p, lane);
+    if (all_marked < (long)BWD_MIN_TILES_PER_BLOCK * p.BH * T) {
         if (tid == 0) {
             p.gflag[(long)bh * ((N + BR - 1) / BR) + I] = 0;
             atomicAdd(p.nplain, 1);
@@ -785,7 +790,7 @@ __global__ __launch_bounds__(NW * 64) void bwd_list_kernel(Params p) {
     }
     build_tile_list(fm, MR, W, tl, tl_count, tid);
     const int nt = *tl_count;
-    const int budget = gather_budget<E, D, AM>(gsum[1], min(BR, N - (int)q0));
+    const int budget = gather_budget<E, D, AM>(gsum[1], min(BR, N - (int)q0), higher_limit(gsum[1], all_marked, p.BH * G));
 
     Owned<E, D, QB> qf;
     load_owned<E, D, QB>(qf, Qh, active ? qw0 : 0, lane);
@@ -892,7 +897,8 @@ __global__ __launch_bounds__(NW * 64) void bwd_list_kernel(Params p) {
 // again: for the row groups whose output the forward gathered, the front of its candidate lists is
 // the support (raw score, key index), with the counts beside it.  This kernel takes the place of
 // bwd_list_kernel's sweep: per row group of the backward it applies the same rule - at most so many
-// support entries per marked tile, or per row where few tiles are marked - to the forward's counts.
+// support entries per marked tile, or per row where few tiles are marked - to the forward's counts; at head dim 128 the higher limit
+// also where the entries per key let it.
 template <class E, int D, int AM>
 __global__ __launch_bounds__(128) void bwd_decide_kernel(Params p) {
     __shared__ int gsum[2];
@@ -901,7 +907,8 @@ __global__ __launch_bounds__(128) void bwd_decide_kernel(Params p) {
     int bh, I;
     map_block(blockIdx.x, p.BH, G, bh, I);
     const int fwd_grows = (int)p.fwd_scal[2];
-    bool gather = marked_tiles(p, tid & 63) >= (long)BWD_MIN_TILES_PER_BLOCK * p.BH * T && fwd_grows > 0
+    const long all_marked = marked_tiles(p, tid & 63);
+    bool gather = all_marked >= (long)BWD_MIN_TILES_PER_BLOCK * p.BH * T && fwd_grows > 0
                   && p.fwd_gflag[(long)bh * ((N + fwd_grows - 1) / fwd_grows) + (I * BR) / fwd_grows] != 0;
     if (tid < 2) gsum[tid] = 0;
     __syncthreads();
@@ -918,7 +925,16 @@ __global__ __launch_bounds__(128) void bwd_decide_kernel(Params p) {
     }
     __syncthreads();
     if (tid == 0) {
-        gather = gather && gsum[0] <= gather_budget<E, D, AM>(gsum[1], min(BR, N - I * BR));
+        if (gather) {
+            const int ent = gsum[0], marked = gsum[1], rows = min(BR, N - I * BR);
+            bool higher = higher_limit(marked, all_marked, p.BH * G);
+            if (D == 128 && !higher) {
+                // entries of a key of the group's rows if the rows after it (without a causal mask: all rows) attend to as many keys
+                const float later = p.causal ? 0.69314718f * __builtin_amdgcn_logf((float)N / ((float)(I * BR) + 0.5f * (float)rows)) : 1.f;
+                higher = (float)ent * later <= BWD_KEY_ENTRIES * (float)rows;
+            }
+            gather = ent <= gather_budget<E, D, AM>(marked, rows, higher);
+        }
         p.gflag[(long)bh * G + I] = gather;
         if (!gather) atomicAdd(p.nplain, 1);
         else atomicAdd(&p.stats[(blockIdx.x & (STATS_COPIES - 1)) * STATS_WORDS + 11], (unsigned long long)min(BR, N - I * BR));

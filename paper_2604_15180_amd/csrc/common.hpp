@@ -25,15 +25,29 @@ constexpr int BWD_COLS_KEYS = 16;        // keys per work-group of bwd_cols_kern
 constexpr int BWD_LIST_CAP = 64, KEY_LIST_CAP = 128;
 // Non-zeros per marked 64 x 64 tile up to which a row group's backward takes the gather path.  Gather
 // and matrix time of both directions: about 0.09 ns per entry and 6.3 ns per tile at head dim 64, 0.13 and
-// 13.4 ns at head dim 128, where the gather's rows are twice as long: level near 70 and 100 entries.  A few groups left to
-// the matrix kernels cost more than their tiles, though: the fp16 copies, max |dO| and a partly filled launch of each.  Step with 64 / 128 at
-// head dim 64: 1088 tokens 152 / 139 us, 8192 tokens, alpha = 2, 808 / 746, 8192, alpha = 1.25, 1265 / 1243, 4096, sigma = 1.5, level (783 / 791);
-// with 40 / 96 at head dim 128: 16384 tokens, sigma = 1, 4415 / 4281, block-structured 1857 / 1722.  (The smaller limits dated from when hub keys
-// were summed by atomics.)  The power functions of general alpha weigh on both sides alike.
+// 13.4 ns at head dim 128, where the gather's rows are twice as long: level near 70 and 100 entries.  The lower limit
+// holds for every group; up to the higher one a group goes by gather where leaving it to the matrix kernels costs more than its tiles:
+// * it has at most a quarter of the mean marked tiles (the first rows of causal heads): with all others gathered the matrix
+//   kernels would run for these alone, and make their fp16 copies and max |dO|.  Backward with the lower limit alone / the higher one, head dim
+//   64: 32 heads of 8192 tokens, alpha = 2, sigma = 2, lists found again, 445 / 385 us, alpha = 1.25, sigma = 2, 549 / 531.  Higher for
+//   every group: 64 heads of 2048, sigma = 0.8, 386 / 430, sigma = 1, 333 / 381, without a mask, sigma = 0.7, 509 / 703, 16
+//   heads of 4096, sigma = 0.7, 282 / 384, sigma = 0.8, 304 / 393, 32 of 8192, sigma = 0.8, 1106 / 1250; lists found again, whose sweep
+//   ends where the limit is out of reach, 64 of 2048, sigma = 0.7, 430 / 543, head dim 128, 32 of 4096, sigma = 0.7, 864 / 1198;
+// * there are at most BWD_FEW_GROUPS row groups, so that a quarter of the CUs has none of the matrix kernels' work-groups, whose walks then set their
+//   time: head dim 64, 16 heads of 1088 tokens, sigma = 1 / 1.5, 112 / 95 and 81 / 73, 8 of 2048, sigma = 1, 128 / 106; near the limit, where only a
+//   few groups qualify, it costs: 8 of 2048, sigma = 0.7, 142 / 167;
+// * head dim 128, forward's lists: its rows' keys would have at most BWD_KEY_ENTRIES entries each if all later rows attended to as many
+//   keys (hub keys, with more than KEY_LIST_CAP, are several times the work): 32 heads of 8192 tokens, sigma = 0.7 / 0.8 / 1 (at most 72 entries):
+//   2894 / 1980, 1902 / 1449, 1027 / 899; 16 of 16384, sigma = 0.7 / 0.8 (124, 100): 2880 / 3545, 1900 / 1943.
+// The power functions of general alpha weigh on both sides alike.
 // fp32 matrix products run at a sixteenth of the 16-bit rate, 72 ns per tile: 16 heads of 2048 tokens at d = 64,
 // sigma = 1, backward with 40 / 128 / 512: 631 / 265 / 121 us.  Attention sinks do not change the picture: 32 heads
 // of 4096 tokens at d = 64 with one, gather 149, matrix 311 us; with four 268 and 225.
-constexpr int bwd_entries_per_tile(int d, int elem_bytes) { return elem_bytes == 4 ? 512 : d == 64 ? 128 : 96; }
+constexpr int bwd_entries_per_tile(int d, int elem_bytes, bool higher) {
+    return elem_bytes == 4 ? 512 : d == 64 ? (higher ? 128 : 64) : (higher ? 96 : 40);
+}
+constexpr int BWD_FEW_GROUPS = 192;
+constexpr float BWD_KEY_ENTRIES = 80.f;
 // ... or, in a group with at most BWD_FEW_TILES marked tiles, BWD_ENTRIES_PER_ROW per row (at head dim 128).
 constexpr int BWD_ENTRIES_PER_ROW = 6, BWD_FEW_TILES = 40;
 // The gather kernels' fixed cost is a few passes over dK and dV, 0.3 - 0.45 ns per row: what the matrix

@@ -696,3 +696,43 @@ def test_gathered_rows_of_every_length(ea, dtype, d, N, top):
     ref, info = parity.check_forward(q, k, v, alpha, causal, O, tau, mask, label=f"lengths {dtype} {d}", rounding_slack=dtype == "f32")
     _, ginfo = parity.check_backward(q, k, v, do, alpha, causal, dQ, dK, dV, label=f"lengths {dtype} {d}", tau_ref=ref["tau"])
     print("  ", info, ginfo, flush=True)
+
+
+@pytest.mark.parametrize("d,H,N,alpha,sigma,causal,lists", [(64, 13, 2048, 1.5, 0.9, True, True), (64, 13, 2048, 1.5, 0.9, True, False), (64, 4, 2048, 1.5, 0.9, True, True),
+                                                            (64, 13, 2048, 1.5, 0.8, False, True), (64, 4, 8192, 2.0, 1.0, True, False), (128, 13, 2048, 1.5, 1.0, True, True),
+                                                            (128, 13, 2048, 1.5, 1.0, True, False)])
+def test_which_row_groups_the_backward_gathers(ea, d, H, N, alpha, sigma, causal, lists):
+    # The route of each row group of 128 rows, from its support and its marked tiles as float64 scores give them: up to 64 (head dim 128:
+    # 40) entries per marked tile always, up to 128 (96) in groups with a quarter of the mean marked tiles, in launches of at most 192
+    # groups, and at head dim 128 with the forward's lists where keys would get at most 80 entries.
+    print(f"routes d={d} H={H} N={N} alpha={alpha} sigma={sigma} causal={causal} lists={lists}", flush=True)
+    q, k, v, do = (t.cuda() for t in workloads.gaussian_qkv(1, H, N, d, "bf16", sigma, seed=131))
+    wf = torch.empty(ea.entmax_attn_workspace_bytes(1, H, N, d, "bf16", causal, False), dtype=torch.uint8, device="cuda")
+    wb = torch.empty(ea.entmax_attn_workspace_bytes(1, H, N, d, "bf16", causal, True), dtype=torch.uint8, device="cuda")
+    O, tau, mask = ea.entmax_attn_fwd(q, k, v, alpha, causal, workspace=wf)
+    ea.entmax_attn_bwd(q, k, v, O, do, tau, alpha, causal, block_mask=mask, workspace=wb, fwd_workspace=wf if lists else None)
+    torch.cuda.synchronize()
+    got = ea.read_stats(wb)["bwd_gather_rows"]
+    G = N // 128
+    entries, marked = torch.zeros(H, G), torch.zeros(H, G)
+    for h in range(H):
+        on = (alpha - 1.0) * (q[0, h].double() @ k[0, h].double().T.contiguous()) / d ** 0.5 > tau[0, h].double()[:, None]
+        if causal:
+            on = on.tril()
+        entries[h] = on.view(G, -1).sum(1).cpu()
+        marked[h] = on.view(G, 2, 64, N // 64, 64).any(4).any(2).sum((1, 2)).cpu()
+    later = torch.log(N / (128.0 * torch.arange(G) + 64.0)) if causal else torch.ones(G)
+
+    def rows(slack):
+        higher = (marked * 4 * G * H <= marked.sum()) | (H * G <= 192)
+        if d == 128 and lists:
+            higher |= entries / 128 * later * slack <= 80
+        limit = torch.where(higher, 128 if d == 64 else 96, 64 if d == 64 else 40) * marked
+        if d == 128:
+            limit = torch.maximum(limit, torch.where(marked <= 40, 6.0 * 128, 0.0))
+        return int((entries * slack <= limit.clamp(max=96 * 128)).sum()) * 128
+
+    print("  rows by gather", got, "expected", rows(1.0), "of", H * N, flush=True)
+    # (a group within 2 per cent of its limit may go either way: scores at the threshold, and the sweep's early end)
+    assert rows(1.02) <= got <= rows(0.98)
+    assert 0 <= rows(1.0) < H * N
