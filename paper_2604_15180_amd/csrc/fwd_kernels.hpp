@@ -419,9 +419,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 8
     // List growth (entries of any lane) since the last refresh of the bound from which the next scheduled one is done, and
     // from which one is done at once (GROW_COUNTING: of lists counted as they grow).  Steps with GROW 12 / 24 / 48 / 64:
     // forward of 1088 tokens, d = 64, 75 / 77 / 71 / 70 us, 3136 tokens, sigma = 2, 164 / 155 / 142 / 142, 4096 tokens 414 / 423 / 425 / 442.
+    // GROW_COUNTING 12 / 20 / 32: alpha = 2, 8192 tokens, d = 64, sigma = 0.6, 706 / 723 / 745 us, 64 heads of 2048, sigma = 0.8, 368 / 369 / 378, fp32, 1024
+    // tokens, 134 / 131 / 130, 16384 tokens, sigma = 1, 2350 / 2345 / 2383.  GROW_HARD 48 / 64 / 96: 4096 tokens 446 / 407 / 401, alpha = 1.25, 8192 tokens,
+    // 756 / 717 / 689, 1088 tokens 75 / 69 / 69.  The first scheduled refresh after 4 or 8 tiles: level.
     constexpr int GROW = 48, GROW_COUNTING = 20, GROW_HARD = 64, FIRST_REFRESH = 4;
     // list length from which on a refresh drops entries below the bound (it takes two passes over memory: later where
-    // the histogram needs no pass of its own; 16384 tokens, sigma = 1, 144 / 208: 2600 / 2546 us)
+    // the histogram needs no pass of its own; 16384 tokens, sigma = 1, 144 / 208: 2600 / 2546 us;
+    // PRUNE_FROM 144 or 192: level at alpha = 1.25, 1.5 and 2, few lists of sparse rows come that far)
     constexpr int PRUNE_FROM = 144, PRUNE_FROM_COUNTING = 208;
     // ... and only while the row with most keys of support so far, and the count that it will grow to if it keeps rising with the
     // logarithm of the keys seen, leave room in the lists: a prune of every wave costs as much as the fallback kernel, and one that drops
@@ -437,7 +441,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 8
     // 16384 tokens, sigma = 1, 2530 / 2530 / 2600 / 3300 us.
     constexpr int FIRST_TILE_BUSY = 180;
     constexpr int TILE_ENTRIES = 32;     // entries a lane can list from one tile
-    constexpr int REG_ENTRIES = 16;      // entries per lane held in registers after the sweep
+    // entries per lane held in registers after the sweep (8 / 16: 4096 tokens 413 / 407 us, alpha = 2, sigma = 0.6, 8192 tokens 729 / 723, 1088 tokens 70.4 / 69.5)
+    constexpr int REG_ENTRIES = 16;
     // counters: waves 2w and 2w + 1 share the words of one histogram buffer, 16 bits each.  A row counts what its two lists
     // hold in the end and what prunes dropped from them.
     constexpr int CB = 16;
