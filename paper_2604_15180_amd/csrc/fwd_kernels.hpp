@@ -429,10 +429,12 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 8
     constexpr int PRUNE_FROM = 144, PRUNE_FROM_COUNTING = 208;
     // ... and only while the row with most keys of support so far, and the count that it will grow to if it keeps rising with the
     // logarithm of the keys seen, leave room in the lists: a prune of every wave costs as much as the fallback kernel, and one that drops
-    // little only puts the overflow off.  Forward, 32 heads of 4096 tokens, d = 64, pruned always / by this rule / never: alpha = 1.5, sigma = 0.4,
-    // 3260 / 1800 / 1220 us, alpha = 1.25, sigma = 1.2, 2620 / 1520 / 1260; where the lists hold out in the end a few rows in the fallback
-    // kernel cost all its time: alpha = 1.25, sigma = 1.5, 680 / 680 / 1145, 8 heads of 16384, sigma = 0.7, 1260 / 1260 / 2240.
-    constexpr int PRUNE_SUPPORT = 352;
+    // little only puts the overflow off; where the lists hold out in the end a few rows in the fallback kernel cost all its time.  Forward, d = 64, pruned
+    // always / by this rule / never: 32 heads of 4096 tokens, alpha = 1.5, sigma = 0.4, 3310 / 2090 / 1350 us, 64 of 2048 without a mask 3410 / 1280 / 1100,
+    // alpha = 1.25, sigma = 1.2, 2600 / 1760 / 1460, 1.5, 695 / 686 / 1175, 64 of 4096, alpha = 1.25, sigma = 1.5, 1245 / 1253 / 1808, 8 of 16384,
+    // sigma = 0.7, 1260 / 1258 / 2390.  With (352, 576) instead: 1800, 1180, 1520, 680, 1790 and 1260, and d = 128, alpha = 1.25,
+    // sigma = 1.4, 1500 against 930; with (416, 640): 2265, 2747, 1888, 698, 1250 and 1260.
+    constexpr int PRUNE_SUPPORT = 416;
     constexpr float PRUNE_SUPPORT_END = 576.f;
     // prunes of a wave at most: what they drop stays counted.  (A list that is full after them flags its block, as any other.)
     constexpr int MAX_PRUNES = 120;
